@@ -918,11 +918,37 @@ void launch_offsets(const Layout& L, Consts kc, int d, void* ws, hipStream_t st,
                        extreme_parts(L), (const double*)nullptr, 0, at<double>(ws, L.H));
 }
 
-// Owns the captured iteration graph of a solve call: destroyed on every return path.
-struct GraphGuard {
+// The iteration loop of a solve call on its stream.  GRAPH_ITERS iterations are captured once
+// into a graph that is replayed (every kernel reads t, the schedule and the stop flag from
+// device memory); queue() enqueues exactly `count` iterations: whole replays, the remainder
+// launched directly.  Capturing costs the host 8 us per iteration (0.49 ms for 64) before the
+// first one can start, and an iteration queued past the end still costs its launches, so the
+// graph is short and nothing is queued past the call's last iteration: 4096 x 4096 points,
+// 16 iterations: 3.4 -> 0.98 ms.  Fewer than 2 GRAPH_ITERS iterations are launched directly.
+// The graph is destroyed on every return path.
+constexpr int GRAPH_ITERS = 8;
+
+struct IterLoop {
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
-    ~GraphGuard() {
+
+    template <typename F>
+    lamp_status queue(int64_t count, hipStream_t st, F&& iteration) {
+        if (!exec && count >= 2 * GRAPH_ITERS) {
+            HIPCHK(hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal));
+            for (int k = 0; k < GRAPH_ITERS; ++k) iteration();
+            const hipError_t ce = hipStreamEndCapture(st, &graph);
+            if (ce != hipSuccess) return fail(LAMP_EDEVICE, "graph capture failed: %s", hipGetErrorString(ce));
+            HIPCHK(hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0));
+        }
+        if (exec)
+            for (; count >= GRAPH_ITERS; count -= GRAPH_ITERS) HIPCHK(hipGraphLaunch(exec, st));
+        for (; count > 0; --count) iteration();
+        HIPCHK(hipGetLastError());
+        return LAMP_OK;
+    }
+
+    ~IterLoop() {
         if (exec) (void)hipGraphExecDestroy(exec);
         if (graph) (void)hipGraphDestroy(graph);
     }
@@ -1426,10 +1452,12 @@ void batch_iteration(const BatchRun& run, void* ws, hipStream_t st) {
     const int* na = at<int>(ws, B.nact);
     const dim3 gr((unsigned)std::max(1, std::min(run.grid, B.cap_items[0])));
     const dim3 gc((unsigned)std::max(1, std::min(run.grid, B.cap_items[2])));
-    hipLaunchKernelGGL(batch_row_sweep, gr, dim3(BLOCK), 0, st, pd, at<Item>(ws, B.items[0]), na, sch, ctr);
+    hipLaunchKernelGGL(batch_row_sweep, gr, dim3(BLOCK), 0, st, pd, at<Item>(ws, B.items[0]), na, sch, ctr,
+                       count);
     hipLaunchKernelGGL(batch_row_finish, dim3((unsigned)B.cap_items[1]), dim3(BLOCK), 0, st, pd,
                        at<Item>(ws, B.items[1]), B.cap_items[1], sch, ctr);
-    hipLaunchKernelGGL(batch_col_sweep, gc, dim3(BLOCK), 0, st, pd, at<Item>(ws, B.items[2]), na + 1, sch, ctr + 1);
+    hipLaunchKernelGGL(batch_col_sweep, gc, dim3(BLOCK), 0, st, pd, at<Item>(ws, B.items[2]), na + 1, sch, ctr + 1,
+                       count);
     hipLaunchKernelGGL(batch_dual_update, dim3((unsigned)B.cap_items[3]), dim3(BLOCK), 0, st, pd,
                        at<Item>(ws, B.items[3]), B.cap_items[3], sch, ctr + 1);
     hipLaunchKernelGGL(batch_dual_finish, dim3((unsigned)count), dim3(BLOCK), 0, st, pd, sch);
@@ -1658,22 +1686,15 @@ lamp_status lamp_solve(const lamp_problem* prob, const lamp_params* params, lamp
     launch_offsets(L, kc, prob->d, ws, st);
     HIPCHK(hipGetLastError());
 
-    // capture K iterations once; the kernels read t, the schedule and the stop flag
-    // from device memory, so the same graph is replayed for every chunk
-    GraphGuard gg;
-    if (t_stop > t0) {
-        HIPCHK(hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal));
-        for (int k = 0; k < K; ++k) launch_iteration(prob, L, kc, ws, ia, st);
-        hipError_t ce = hipStreamEndCapture(st, &gg.graph);
-        if (ce != hipSuccess) return fail(LAMP_EDEVICE, "graph capture failed: %s", hipGetErrorString(ce));
-        HIPCHK(hipGraphInstantiate(&gg.exec, gg.graph, nullptr, nullptr, 0));
-    }
+    IterLoop loop;
     int64_t t_cur = t0;
     lamp_status result = LAMP_OK;
     while (t_cur < t_stop) {
-        // two chunks in flight: the kernels of a chunk that starts after the stop exit at once
-        HIPCHK(hipGraphLaunch(gg.exec, st));
-        HIPCHK(hipGraphLaunch(gg.exec, st));
+        // two checks' worth of iterations in flight (those after the stop exit at once), none past
+        // the end of the call or of the schedule epoch
+        e = loop.queue(std::min<int64_t>(2 * (int64_t)K, t_end - t_cur), st,
+                       [&] { launch_iteration(prob, L, kc, ws, ia, st); });
+        if (e != LAMP_OK) return e;
         HIPCHK(hipMemcpyAsync(&hc, at<Ctrl>(ws, L.ctrl), sizeof(Ctrl), hipMemcpyDeviceToHost, st));
         HIPCHK(hipStreamSynchronize(st));
         if (hc.err) {
@@ -1697,7 +1718,8 @@ lamp_status lamp_solve(const lamp_problem* prob, const lamp_params* params, lamp
             lam_epoch = lam_next_epoch;
             lam_next_epoch = fill_sched(tab.data(), TAB, lam_epoch, R.tau1, params->eta);
             HIPCHK(hipMemcpyAsync(at<Sched>(ws, L.sched), tab.data(), sizeof(Sched) * TAB, hipMemcpyHostToDevice, st));
-            hc.t_end = std::min(t_stop, t_base + TAB);
+            t_end = std::min(t_stop, t_base + TAB);
+            hc.t_end = t_end;
             hc.t_base = t_base;
             HIPCHK(hipMemcpyAsync(at<Ctrl>(ws, L.ctrl), &hc, sizeof(Ctrl), hipMemcpyHostToDevice, st));
         }
@@ -2158,14 +2180,7 @@ lamp_status lamp_solve_batched(const lamp_problem* probs, int32_t count, const l
     if ((e = batch_setup(probs, count, params, states, ws, st, cand, t_stop, &run)) != LAMP_OK) return e;
     const BatchPlan& B = run.B;
     const int K = params->check_every > 0 ? params->check_every : 64;
-    GraphGuard gg;
-    if (t_stop > t0) {
-        HIPCHK(hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal));
-        for (int k = 0; k < K; ++k) batch_iteration(run, ws, st);
-        hipError_t ce = hipStreamEndCapture(st, &gg.graph);
-        if (ce != hipSuccess) return fail(LAMP_EDEVICE, "graph capture failed: %s", hipGetErrorString(ce));
-        HIPCHK(hipGraphInstantiate(&gg.exec, gg.graph, nullptr, nullptr, 0));
-    }
+    IterLoop loop;
     std::vector<Ctrl> hc(count);
     std::vector<char> active(count, 1);
     Ctrl* hc_dev = at<Ctrl>(ws, B.ctrlv);
@@ -2176,8 +2191,9 @@ lamp_status lamp_solve_batched(const lamp_problem* probs, int32_t count, const l
     int64_t t_cur = t0;
     lamp_status result = LAMP_OK;
     while (t_cur < t_stop) {
-        HIPCHK(hipGraphLaunch(gg.exec, st));
-        HIPCHK(hipGraphLaunch(gg.exec, st));
+        e = loop.queue(std::min<int64_t>(2 * (int64_t)K, std::min(t_stop, t_base + TAB) - t_cur), st,
+                       [&] { batch_iteration(run, ws, st); });
+        if (e != LAMP_OK) return e;
         HIPCHK(hipMemcpyAsync(hc.data(), hc_dev, sizeof(Ctrl) * count, hipMemcpyDeviceToHost, st));
         HIPCHK(hipStreamSynchronize(st));
         bool all_done = true, any_err = false, newly_done = false;
