@@ -432,7 +432,6 @@ void by_cost_type(int cost_type, F&& f) {
 }
 
 // ------------------------------------------------------------------ dispatch by d
-#define LAMP_FOR_D(X) X(1) X(2) X(3) X(4) X(5) X(6) X(7) X(8) X(16)
 template <int V>
 using IC = std::integral_constant<int, V>;
 
@@ -461,13 +460,44 @@ bool valu_dispatch(int d, F&& launch) {
     return false;
 }
 
+// The iteration's sweeps and the offset pass: every dimension up to 16 for the squared Euclidean
+// cost (from 17 on the matrix cores take over), up to 8 for l1 / l_inf.  The compiled form keeps
+// the lane's point in registers and reads the streamed one through scalar loads; the run-time
+// form loads both per pair and is bound by those loads: 20011 x 9973 points, d = 12, one sweep
+// 7.5 ms against 0.14 ms.  Same operations in the same order, so the results are bit-identical.
+template <int M, typename F>
+bool sweep_dispatch(int d, F&& launch) {
+    if (valu_dispatch<M>(d, launch)) return true;
+    if constexpr (M == METRIC_SQEUCLID) {
+        switch (d) {
+            case 9: launch(IC<9>{}); return true;
+            case 10: launch(IC<10>{}); return true;
+            case 11: launch(IC<11>{}); return true;
+            case 12: launch(IC<12>{}); return true;
+            case 13: launch(IC<13>{}); return true;
+            case 14: launch(IC<14>{}); return true;
+            case 15: launch(IC<15>{}); return true;
+            default: break;
+        }
+    } else {
+        switch (d) {
+            case 5: launch(IC<5>{}); return true;
+            case 6: launch(IC<6>{}); return true;
+            case 7: launch(IC<7>{}); return true;
+            case 8: launch(IC<8>{}); return true;
+            default: break;
+        }
+    }
+    return false;
+}
+
 // The certificate's pair passes: the compiled dimensions of the vector-ALU sweeps and, for the
 // squared Euclidean cost, 32 and 64 (the thread's own point in registers and the streamed
 // point through scalar loads; the run-time form loads both points' coordinates per pair,
 // 6.6 s for a certificate at n = m = 2^16, d = 64).
 template <int M, typename F>
 bool cert_dispatch(int d, F&& launch) {
-    if (valu_dispatch<M>(d, launch)) return true;
+    if (sweep_dispatch<M>(d, launch)) return true;
     if constexpr (M == METRIC_SQEUCLID) {
         if (d == 32) {
             launch(IC<32>{});
@@ -527,7 +557,7 @@ void launch_row_extreme(const Layout& L, Consts kc, int d, void* ws, const doubl
     const double* xc = at<double>(ws, L.xc);
     const double* yc = at<double>(ws, L.yc);
     const bool done = by_metric(kc.metric, [&](auto m) {
-        return valu_dispatch<decltype(m)::value>(d, [&](auto dd) {
+        return sweep_dispatch<decltype(m)::value>(d, [&](auto dd) {
             hipLaunchKernelGGL((row_extreme<decltype(m)::value, decltype(dd)::value>), g, dim3(BLOCK), 0, st, kc,
                                xc, yc, a, sgn, part, L.split_r);
         });
@@ -659,7 +689,7 @@ void launch_row_sweep(const Layout& L, Consts kc, int d, void* ws, hipStream_t s
     const double* H = at<double>(ws, L.H);
     double2* part = at<double2>(ws, L.rpart);
     const bool done = by_metric(kc.metric, [&](auto m) {
-        return valu_dispatch<decltype(m)::value>(d, [&](auto dd) {
+        return sweep_dispatch<decltype(m)::value>(d, [&](auto dd) {
             hipLaunchKernelGGL((row_sweep<decltype(m)::value, decltype(dd)::value>), g, dim3(BLOCK), 0, st, ctrl,
                                sch, kc, xc, yc, gt, H, part, L.split_r);
         });
@@ -697,7 +727,7 @@ void launch_col_sweep(const Layout& L, Consts kc, int d, void* ws, hipStream_t s
     const double2* ck = at<double2>(ws, L.rowck);
     double2* part = at<double2>(ws, L.cpart);
     const bool done = by_metric(kc.metric, [&](auto m) {
-        return valu_dispatch<decltype(m)::value>(d, [&](auto dd) {
+        return sweep_dispatch<decltype(m)::value>(d, [&](auto dd) {
             hipLaunchKernelGGL((col_sweep<decltype(m)::value, decltype(dd)::value>), g, dim3(BLOCK), 0, st, ctrl,
                                sch, kc, xc, yc, gt, rv, ck, part, L.split_c);
         });

@@ -32,7 +32,9 @@ struct Item {
     int32_t prob, bx, by, pad;
 };
 
-#define LAMP_BATCH_D(X) X(1) X(2) X(3) X(4) X(8) X(16)
+// Every dimension the single-problem sweeps compile for the squared Euclidean cost.
+#define LAMP_BATCH_D(X) \
+    X(1) X(2) X(3) X(4) X(5) X(6) X(7) X(8) X(9) X(10) X(11) X(12) X(13) X(14) X(15) X(16)
 
 // The descriptor's pointers are loaded from memory, so the compiler cannot tell their
 // address space (it would use flat loads) nor that the column data are read-only during

@@ -298,11 +298,14 @@ __device__ __forceinline__ void row_extreme_body(Consts kc, const double* __rest
     const int64_t j1 = min(kc.m, j0 + split);
     const int64_t ii = i < kc.n ? i : kc.n - 1;
     double x[D];
+    // a_j + sgn P(x_i, y_j): the inner product takes the sign on x and starts from a_j, the
+    // distances, and the dimensions 9 to 15, take both after (the order of the run-time form,
+    // which an offset shares to the last bit: a trajectory keeps its FP32 roundings)
+    constexpr bool FROM_A = M == METRIC_SQEUCLID && (D <= 8 || D == 16);
 #pragma unroll
-    for (int k = 0; k < D; ++k) x[k] = (M == METRIC_SQEUCLID ? sgn : 1.0) * xc[ii * D + k];
-    // a_j + sgn P(x_i, y_j): the inner product takes the sign on x, the distances after
+    for (int k = 0; k < D; ++k) x[k] = (FROM_A ? sgn : 1.0) * xc[ii * D + k];
     auto term = [&](const double* yj, double aj) {
-        return M == METRIC_SQEUCLID ? pair_term<M, D>(x, yj, aj) : fma(sgn, pair_term<M, D>(x, yj, 0.0), aj);
+        return FROM_A ? pair_term<M, D>(x, yj, aj) : fma(sgn, pair_term<M, D>(x, yj, 0.0), aj);
     };
     // blocks of UNROLL columns with independent chains, as in the sweeps: the column data
     // are wave-uniform and their scalar loads overlap the arithmetic of the block
