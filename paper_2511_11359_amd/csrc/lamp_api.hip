@@ -20,6 +20,7 @@
 #include "../../include/lamp.h"
 #include "lamp_kernels.hpp"
 #include "lamp_mfma.hpp"
+#include "lamp_coarse.hpp"
 #include "lamp_batch.hpp"
 #include "lamp_cost.hpp"
 #include "lamp_measure.hpp"
@@ -98,6 +99,10 @@ struct Layout {
     int KP64;
     int64_t n_pad64, m_pad64, tps_r64, P_r64, tps_c64, P_c64;
     size_t xop64, yop64;
+    // their extreme passes with coarse INT8 products first (digit planes of the points)
+    bool coarse;
+    int KP8;
+    size_t xop8, yop8;
     // sweeps over an explicit cost matrix
     bool cost;
     int64_t split_rx, P_rx, split_cx, P_cx;
@@ -175,6 +180,11 @@ Layout layout(int64_t n, int64_t m, int d, int prec = LAMP_FP32, int64_t target 
     L.use64 = L.KP64 > 0 && metric == METRIC_SQEUCLID &&
               (uint64_t)std::max(L.n_pad64, L.m_pad64) * (uint64_t)(L.KP64 * 8) < (1ull << 32) &&
               std::max(n, m) < ((int64_t)1 << 28);
+    // Coarse products pay once the FP64 pass (0.11 ms per 2^31 padded products) outlasts their six
+    // extra launches; operand planes below 4 GiB as above.
+    L.KP8 = d <= 64 ? 64 : 128;
+    L.coarse = L.use64 && (double)n * (double)m * L.KP64 >= 0x1p31 &&
+               (uint64_t)std::max(L.n_pad64, L.m_pad64) * (uint64_t)(COARSE_DIGITS * L.KP8) < (1ull << 32);
     L.cost = metric == METRIC_EXPLICIT;
     if (L.cost) {
         // row sweep: 32 rows per block, column splits in whole steps; column sweep:
@@ -253,6 +263,10 @@ Layout layout(int64_t n, int64_t m, int d, int prec = LAMP_FP32, int64_t target 
         L.xop64 = take(sizeof(double) * L.n_pad64 * L.KP64);
         L.yop64 = take(sizeof(double) * L.m_pad64 * L.KP64);
     }
+    if (L.coarse) {
+        L.xop8 = take((size_t)COARSE_DIGITS * L.KP8 * L.n_pad64);
+        L.yop8 = take((size_t)COARSE_DIGITS * L.KP8 * L.m_pad64);
+    }
     L.total = off;
     return L;
 }
@@ -273,9 +287,11 @@ struct Resolved {
     double dscale = 1.0;   // 1 / (range scale)^2 of the split FP16 operands, else 1
 };
 
-// Slot of the small-scalar area holding the split FP16 form's range scale (prep -> resolve);
-// the next slot holds the running maximum its reduction folds into.
+// Slot of the small-scalar area holding the range scale of the split FP16 operands (prep ->
+// resolve) and of the digit planes; the next slot holds the running maximum its reduction folds into.
 constexpr int SPLIT_SCALE_SLOT = 40;
+// The refined cost maximum (8 bytes), its number of candidate tiles and the flag of the digit planes.
+constexpr int REFINE_SLOT = 42;
 
 lamp_status check_problem(const lamp_problem* p) {
     if (!p) return fail(LAMP_EINVAL, "problem is NULL");
@@ -365,6 +381,18 @@ void prep_ops(const lamp_problem* p, const Layout& L, void* ws, hipStream_t st) 
                        p->d, L.KP, L.m_pad, at<T>(ws, L.yop));
 }
 
+// 2^(7 - e) for the largest |coordinate| in [2^e, 2^(e+1)) of both clouds, into its slot.
+void launch_range_scale(const Layout& L, int64_t n, int64_t m, int d, void* ws, hipStream_t st) {
+    double* scale = at<double>(ws, L.small) + SPLIT_SCALE_SLOT;
+    auto* mbits = reinterpret_cast<unsigned long long*>(scale + 1);
+    const int64_t cnt = std::max(n, m) * d;
+    const int blocks = (int)std::min<int64_t>(2048, std::max<int64_t>(1, cdiv(cnt, BLOCK)));
+    hipLaunchKernelGGL(split_scale_clear, dim3(1), dim3(1), 0, st, mbits);
+    hipLaunchKernelGGL(split_scale_max, dim3(blocks), dim3(BLOCK), 0, st, (const double*)at<double>(ws, L.xc),
+                       n * d, (const double*)at<double>(ws, L.yc), m * d, mbits);
+    hipLaunchKernelGGL(split_scale_final, dim3(1), dim3(1), 0, st, (const unsigned long long*)mbits, scale);
+}
+
 lamp_status prep_L(const lamp_problem* p, const Layout& L, void* ws, hipStream_t st) {
     const int prec = L.prec;
     if (L.cost) {
@@ -392,13 +420,7 @@ lamp_status prep_L(const lamp_problem* p, const Layout& L, void* ws, hipStream_t
             prep_ops<__bf16>(p, L, ws, st);
         } else if (prec == LAMP_FP16X3_MFMA) {
             double* scale = at<double>(ws, L.small) + SPLIT_SCALE_SLOT;
-            auto* mbits = reinterpret_cast<unsigned long long*>(scale + 1);
-            const int64_t cnt = std::max(p->n, p->m) * p->d;
-            const int blocks = (int)std::min<int64_t>(2048, std::max<int64_t>(1, cdiv(cnt, BLOCK)));
-            hipLaunchKernelGGL(split_scale_clear, dim3(1), dim3(1), 0, st, mbits);
-            hipLaunchKernelGGL(split_scale_max, dim3(blocks), dim3(BLOCK), 0, st, (const double*)at<double>(ws, L.xc),
-                               p->n * p->d, (const double*)at<double>(ws, L.yc), p->m * p->d, mbits);
-            hipLaunchKernelGGL(split_scale_final, dim3(1), dim3(1), 0, st, (const unsigned long long*)mbits, scale);
+            launch_range_scale(L, p->n, p->m, p->d, ws, st);
             hipLaunchKernelGGL(prep_operands_split, grid1(L.n_pad * L.KP), dim3(BLOCK), 0, st,
                                (const double*)at<double>(ws, L.xc), p->n, p->d, L.KP, L.n_pad, (const double*)scale,
                                0, at<_Float16>(ws, L.xop));
@@ -527,6 +549,46 @@ void row_extreme64(const Layout& L, Consts kc, void* ws, const double* a, double
     hipLaunchKernelGGL((row_extreme_mfma64<KP>), g, dim3(BLOCK), 0, st, kc, at<double>(ws, L.xop64),
                        at<double>(ws, L.yop64), a, sgn, at<double>(ws, L.rpart), L.tps_r64, (int)L.P_r64,
                        L.m_pad64 / 16, n_waves);
+}
+
+// Bits of the refined maximum, candidate count, digit flag (REFINE_SLOT).
+struct Refined {
+    double max;
+    int tiles, bad;
+};
+
+// The digit planes of both clouds.
+void launch_digits(const Layout& L, Consts kc, int d, void* ws, hipStream_t st) {
+    const double* range = at<double>(ws, L.small) + SPLIT_SCALE_SLOT;
+    auto* ref = reinterpret_cast<Refined*>(at<double>(ws, L.small) + REFINE_SLOT);
+    launch_range_scale(L, kc.n, kc.m, d, ws, st);
+    hipLaunchKernelGGL(clear_words, dim3(1), dim3(64), 0, st, (int)(sizeof(Refined) / sizeof(int)), (int*)ref);
+    hipLaunchKernelGGL(prep_digits, grid1(L.n_pad64 * (L.KP8 / 4)), dim3(BLOCK), 0, st, at<double>(ws, L.xc), kc.n, d,
+                       L.KP8, L.n_pad64, range, at<int8_t>(ws, L.xop8), &ref->bad);
+    hipLaunchKernelGGL(prep_digits, grid1(L.m_pad64 * (L.KP8 / 4)), dim3(BLOCK), 0, st, at<double>(ws, L.yc), kc.m, d,
+                       L.KP8, L.m_pad64, range, at<int8_t>(ws, L.yop8), &ref->bad);
+}
+
+template <int KP, int KP64, bool PICK>
+void row_extreme_coarse_kp(const Layout& L, Consts kc, int d, void* ws, const double* a, double sgn,
+                           const double* coarse, hipStream_t st) {
+    const int64_t n_tiles = L.n_pad64 / 16;
+    dim3 g((unsigned)(cdiv(n_tiles, 4 * coarse_rows(KP)) * L.P_r64));
+    auto* ref = reinterpret_cast<Refined*>(at<double>(ws, L.small) + REFINE_SLOT);
+    hipLaunchKernelGGL((row_extreme_coarse<KP, KP64, PICK>), g, dim3(BLOCK), 0, st, kc, d, at<int8_t>(ws, L.xop8),
+                       at<int8_t>(ws, L.yop8), at<double>(ws, L.small) + SPLIT_SCALE_SLOT, a, sgn, coarse,
+                       (const int*)&ref->bad, at<double>(ws, L.xop64), at<double>(ws, L.yop64),
+                       at<double>(ws, L.rpart), L.tps_r64, (int)L.P_r64, L.m_pad64 / 16, n_tiles);
+}
+
+template <bool PICK>
+void launch_row_extreme_coarse(const Layout& L, Consts kc, int d, void* ws, const double* a, double sgn,
+                               const double* coarse, hipStream_t st) {
+    switch (L.KP64) {
+        case 32: row_extreme_coarse_kp<64, 32, PICK>(L, kc, d, ws, a, sgn, coarse, st); return;
+        case 64: row_extreme_coarse_kp<64, 64, PICK>(L, kc, d, ws, a, sgn, coarse, st); return;
+        default: row_extreme_coarse_kp<128, 128, PICK>(L, kc, d, ws, a, sgn, coarse, st); return;
+    }
 }
 
 // Number of partial minima written by launch_row_extreme.
@@ -797,13 +859,47 @@ lamp_status max_sqdist_L(const lamp_problem* p, const Layout& L, void* ws, hipSt
     kc.cost_type = p->metric == LAMP_EXPLICIT ? p->cost_type : COST_F32;
     double* a = at<double>(ws, L.scratch);
     double* rowmax = a + std::max(p->n, p->m);
+    double* top = at<double>(ws, L.small);
+    const double* xn2 = at<double>(ws, L.xn2);
     hipLaunchKernelGGL(fill_scaled, grid1(p->m), dim3(BLOCK), 0, st, p->m, -0.5, at<double>(ws, L.yn2), a);
+    auto merge = [&] {
+        hipLaunchKernelGGL(row_extreme_merge, grid1(p->n), dim3(BLOCK), 0, st, kc, at<double>(ws, L.rpart),
+                           extreme_parts(L), xn2, 1, rowmax);
+        hipLaunchKernelGGL(reduce_max, dim3(1), dim3(1024), 0, st, rowmax, p->n, top);
+    };
+    if (L.coarse) {
+        // the few row tiles near the coarse maximum are evaluated in FP64; with many of them
+        // (points on a sphere, one-hot features) or a coordinate that is not finite, every pair is
+        auto* ref = reinterpret_cast<Refined*>(top + REFINE_SLOT);
+        int* list = reinterpret_cast<int*>(rowmax + std::max(p->n, p->m));
+        const double* range = top + SPLIT_SCALE_SLOT;
+        launch_digits(L, kc, p->d, ws, st);
+        launch_row_extreme_coarse<false>(L, kc, p->d, ws, a, +1.0, nullptr, st);
+        merge();
+        hipLaunchKernelGGL(select_max_tiles, grid1(p->n), dim3(BLOCK), 0, st, p->n, p->d, (const double*)rowmax,
+                           (const double*)top, range, list, &ref->tiles);
+        auto refine = [&](auto kp) {
+            hipLaunchKernelGGL((refine_max<decltype(kp)::value>), dim3(COARSE_MAX_TILES * COARSE_MAX_SPLITS),
+                               dim3(BLOCK), 0, st, kc, (const double*)at<double>(ws, L.xop64),
+                               (const double*)at<double>(ws, L.yop64), xn2, (const double*)a, (const int*)list,
+                               (const int*)&ref->tiles, L.m_pad64 / 16, reinterpret_cast<unsigned long long*>(ref));
+        };
+        if (L.KP64 == 32) refine(IC<32>{});
+        else if (L.KP64 == 64) refine(IC<64>{});
+        else refine(IC<128>{});
+        HIPCHK(hipGetLastError());
+        Refined got;
+        HIPCHK(hipMemcpyAsync(&got, ref, sizeof(got), hipMemcpyDeviceToHost, st));
+        HIPCHK(hipStreamSynchronize(st));
+        if (!got.bad && got.tiles <= COARSE_MAX_TILES) {
+            *out_host = got.max;
+            return LAMP_OK;
+        }
+    }
     launch_row_extreme(L, kc, p->d, ws, a, +1.0, st);
-    hipLaunchKernelGGL(row_extreme_merge, grid1(p->n), dim3(BLOCK), 0, st, kc, at<double>(ws, L.rpart),
-                       extreme_parts(L), at<double>(ws, L.xn2), 1, rowmax);
-    hipLaunchKernelGGL(reduce_max, dim3(1), dim3(1024), 0, st, rowmax, p->n, at<double>(ws, L.small));
+    merge();
     HIPCHK(hipGetLastError());
-    HIPCHK(hipMemcpyAsync(out_host, at<double>(ws, L.small), sizeof(double), hipMemcpyDeviceToHost, st));
+    HIPCHK(hipMemcpyAsync(out_host, top, sizeof(double), hipMemcpyDeviceToHost, st));
     HIPCHK(hipStreamSynchronize(st));
     return LAMP_OK;
 }
@@ -943,9 +1039,20 @@ void launch_offsets(const Layout& L, Consts kc, int d, void* ws, hipStream_t st,
     double* a = at<double>(ws, L.scratch);
     hipLaunchKernelGGL(offset_coeffs, grid1(kc.m), dim3(BLOCK), 0, st, ctrl ? ctrl : at<Ctrl>(ws, L.ctrl),
                        sched ? sched : at<Sched>(ws, L.sched), kc, at<double2>(ws, L.gtab), a);
-    launch_row_extreme(L, kc, d, ws, a, -1.0, st);
-    hipLaunchKernelGGL(row_extreme_merge, grid1(kc.n), dim3(BLOCK), 0, st, kc, at<double>(ws, L.rpart),
-                       extreme_parts(L), (const double*)nullptr, 0, at<double>(ws, L.H));
+    auto merge = [&](double* out) {
+        hipLaunchKernelGGL(row_extreme_merge, grid1(kc.n), dim3(BLOCK), 0, st, kc, at<double>(ws, L.rpart),
+                           extreme_parts(L), (const double*)nullptr, 0, out);
+    };
+    if (L.coarse) {
+        double* coarse = a + std::max(kc.n, kc.m);
+        launch_digits(L, kc, d, ws, st);
+        launch_row_extreme_coarse<false>(L, kc, d, ws, a, -1.0, nullptr, st);
+        merge(coarse);
+        launch_row_extreme_coarse<true>(L, kc, d, ws, a, -1.0, coarse, st);
+    } else {
+        launch_row_extreme(L, kc, d, ws, a, -1.0, st);
+    }
+    merge(at<double>(ws, L.H));
 }
 
 // The iteration loop of a solve call on its stream.  GRAPH_ITERS iterations are captured once
