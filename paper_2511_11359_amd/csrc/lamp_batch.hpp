@@ -116,7 +116,7 @@ __global__ __launch_bounds__(BLOCK) void batch_row_finish(const ProbDesc* __rest
         const Item it = items[k];
         const ProbDesc& P = pd[it.prob];
         row_finish_body(P.ctrl, sched, P.kc, P.d, P.xc, P.yc, P.gtab, P.r, P.xn2, P.rpart, P.P_r, P.H, P.rowvar,
-                        P.rowck, nullptr, nullptr, RowVarF32{nullptr, 0}, it.bx, it.by, 0);
+                        P.rowck, nullptr, nullptr, RowVarF32{nullptr, 0}, P.ctrl->done, it.bx);
     }
 }
 
@@ -169,7 +169,7 @@ __global__ __launch_bounds__(BLOCK) void batch_dual_update(const ProbDesc* __res
 // Block p completes the iteration of problem p (residual, stop decision, t + 1).
 __global__ __launch_bounds__(BLOCK) void batch_dual_finish(const ProbDesc* __restrict__ pd, const Sched* sched) {
     const ProbDesc& P = pd[blockIdx.x];
-    dual_finish_body(P.ctrl, sched, P.respart, nullptr, P.n_dual_blocks);
+    complete_iteration(P.ctrl, sched, P.respart, nullptr, P.n_dual_blocks);
 }
 
 }  // namespace lampk

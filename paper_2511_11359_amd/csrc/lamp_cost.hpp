@@ -45,8 +45,8 @@ __global__ __launch_bounds__(BLOCK) void row_sweep_cost(const Ctrl* ctrl, const 
                                                         const double2* __restrict__ gtab2,
                                                         const double* __restrict__ H,
                                                         double2* __restrict__ part, int64_t split) {
-    if (halted(ctrl)) return;
-    const int64_t t = ctrl->t;
+    if (halted_row(ctrl)) return;
+    const int64_t t = ctrl->t_row;
     const Sched sc = sched[t - ctrl->t_base];
     const double cA = 2.0 * kc.s * sc.lamA * LOG2E;
     const double cB = 2.0 * kc.s * sc.lamB * LOG2E;

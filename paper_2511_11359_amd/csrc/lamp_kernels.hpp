@@ -37,6 +37,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 namespace lampk {
 
 constexpr double LOG2E = 1.4426950408889634074;
@@ -47,12 +49,16 @@ constexpr int UNROLL = 8;
 // Device-side control block (lives in the workspace).
 struct Ctrl {
     int64_t t;          // index of the iteration the next kernels execute
+    int64_t t_row;      // the same for the row sweep and row finish: ahead of t by one between the
+                        // dual update of iteration t and its completion (complete_iteration)
     int64_t t_end;      // exclusive end of this call's iterations
     int64_t t_base;     // schedule index base: sched[t - t_base]
     int64_t t_done;     // iteration whose residual met tol (-1 otherwise)
     int32_t done;       // 1 once res_t <= tol
     int32_t err;        // bit 0: non-finite value in the dual update
-    int32_t fallbacks;  // rows recomputed exactly
+    int32_t fallbacks;  // rows recomputed exactly, in the iterations whose dual update ran
+    int32_t fallbacks_row;   // those of the running iteration
+    int32_t done_seen;  // done as of the last dual update
     uint32_t pad0;
     double tol;         // 0: never stop early
     double res_last;    // ||col(X^t) - c||_1 of the last completed iteration
@@ -188,6 +194,10 @@ struct RowVar {
 
 __device__ __forceinline__ bool halted(const Ctrl* ctrl) {
     return ctrl->done != 0 || ctrl->t >= ctrl->t_end;
+}
+
+__device__ __forceinline__ bool halted_row(const Ctrl* ctrl) {
+    return ctrl->done != 0 || ctrl->t_row >= ctrl->t_end;
 }
 
 // Sweeps over (blocks of the owned points) x (P splits of the streamed range of length len,
@@ -428,8 +438,8 @@ __device__ __forceinline__ void row_sweep_body(const Ctrl* ctrl, const Sched* sc
                                                    const double* __restrict__ xn2 = nullptr,
                                                    const double* __restrict__ yn2 = nullptr,
                                                    double* __restrict__ tpart = nullptr) {
-    if (halted(ctrl)) return;
-    const int64_t t = ctrl->t;
+    if (halted_row(ctrl)) return;
+    const int64_t t = ctrl->t_row;
     const Sched sc = sched[t - ctrl->t_base];
     const double cA = 2.0 * kc.s * sc.lamA * LOG2E;
     const double cB = 2.0 * kc.s * sc.lamB * LOG2E;
@@ -516,6 +526,82 @@ __global__ __launch_bounds__(BLOCK) void row_sweep(const Ctrl* ctrl, const Sched
     row_sweep_body<M, D>(ctrl, sched, kc, xc, yc, gtab2, H, part, split, sb.bx, sb.p, 0);
 }
 
+// Column groups of a split summed in parallel by the waves of a block (see row_sweep_par).
+__device__ __forceinline__ float* group_sums() {
+    extern __shared__ __align__(16) float lds_group_sums[];
+    return lds_group_sums;
+}
+
+// The FP64 sums of a split from its FP32 group sums in LDS ([2][groups][64]), in group order: the
+// first two waves of the block take one coupling each.
+__device__ __forceinline__ double sum_groups(const float* sums, int groups, int lane) {
+    double s = 0.0;
+#pragma unroll 8
+    for (int c = 0; c < groups; ++c) s += (double)sums[c * 64 + lane];
+    return s;
+}
+
+// Row sweep for grids that leave the chip short of waves: a block owns 64 rows of a split and its
+// waves share the split's groups of UNROLL columns; the group sums meet in LDS and are added in
+// the order of row_sweep, so that the results are the same to the last bit.
+template <int M, int D>
+__global__ __launch_bounds__(1024) void row_sweep_par(const Ctrl* ctrl, const Sched* sched, Consts kc,
+                                                      const double* __restrict__ xc, const double* __restrict__ yc,
+                                                      const double2* __restrict__ gtab2,
+                                                      const double* __restrict__ H, double2* __restrict__ part,
+                                                      int64_t split) {
+    if (halted_row(ctrl)) return;
+    const int64_t t = ctrl->t_row;
+    const Sched sc = sched[t - ctrl->t_base];
+    const double cA = 2.0 * kc.s * sc.lamA * LOG2E;
+    const double cB = 2.0 * kc.s * sc.lamB * LOG2E;
+    const double2* __restrict__ g = gtab2 + (t & 1) * kc.m;
+    const SweepBlock sb = sweep_block(kc.m, split);
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int waves = blockDim.x >> 6;
+    const int64_t i = sb.bx * 64 + lane;
+    const int64_t j0 = sb.p * split;
+    const int len = (int)(min(kc.m, j0 + split) - j0);
+    const int groups = (len + UNROLL - 1) / UNROLL;
+    const int64_t ii = i < kc.n ? i : kc.n - 1;
+    double x[D];
+#pragma unroll
+    for (int k = 0; k < D; ++k) x[k] = xc[ii * D + k];
+    const double h = H[ii];
+    float* sums = group_sums();
+    const int c1 = (wave + 1) * groups / waves;
+    for (int c = wave * groups / waves; c < c1; ++c) {
+        const double* __restrict__ yp = yc + (j0 + c * UNROLL) * D;
+        const double2* __restrict__ gp = g + j0 + c * UNROLL;
+        float accA = 0.f, accB = 0.f;
+        if ((c + 1) * UNROLL <= len) {
+            float pA[UNROLL], pB[UNROLL];
+#pragma unroll
+            for (int u = 0; u < UNROLL; ++u) row_terms<M, D>(x, h, yp + u * D, gp[u], cA, cB, pA[u], pB[u]);
+            accA = pA[0];
+            accB = pB[0];
+#pragma unroll
+            for (int u = 1; u < UNROLL; ++u) {
+                accA += pA[u];
+                accB += pB[u];
+            }
+        } else {
+            for (int u = 0; u < len - c * UNROLL; ++u) {
+                float a, b;
+                row_terms<M, D>(x, h, yp + u * D, gp[u], cA, cB, a, b);
+                accA += a;
+                accB += b;
+            }
+        }
+        sums[c * 64 + lane] = accA;
+        sums[(groups + c) * 64 + lane] = accB;
+    }
+    __syncthreads();
+    if (wave < 2 && i < kc.n)
+        reinterpret_cast<double*>(part)[2 * (sb.p * kc.n + i) + wave] = sum_groups(sums + wave * groups * 64, groups, lane);
+}
+
 // The row sweep of a D_t-tracked iteration: the row sweep above plus the B coupling's cost
 // sums, tpart: [P][n].
 template <int M, int D>
@@ -538,8 +624,8 @@ __device__ __forceinline__ void row_sweep_dyn_body(const Ctrl* ctrl, const Sched
                                                        const double2* __restrict__ gtab2,
                                                        const double* __restrict__ H,
                                                        double2* __restrict__ part, int64_t split, int64_t bx_, int64_t by_, int64_t nb_) {
-    if (halted(ctrl)) return;
-    const int64_t t = ctrl->t;
+    if (halted_row(ctrl)) return;
+    const int64_t t = ctrl->t_row;
     const Sched sc = sched[t - ctrl->t_base];
     const double cA = 2.0 * kc.s * sc.lamA * LOG2E;
     const double cB = 2.0 * kc.s * sc.lamB * LOG2E;
@@ -594,6 +680,30 @@ __device__ double exact_sigma(const Consts& kc, const double* __restrict__ xi, c
     return mx + log2(s);
 }
 
+// The sums over the splits, in split order, from the partials of point i ([P][len]): blocks of 32
+// and 8 independent loads (a merge is bound by the latency of its loads: with 8 in flight at most
+// 32 splits of 4096 rows took 4.6 us).
+__device__ __forceinline__ double2 merge_splits(const double2* __restrict__ part, int P, int64_t len, int64_t i) {
+    double a = 0.0, b = 0.0;
+    int p = 0;
+    auto take = [&](auto cnt) {
+        constexpr int U = decltype(cnt)::value;
+        double2 v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = part[(int64_t)(p + u) * len + i];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            a += v[u].x;
+            b += v[u].y;
+        }
+        p += U;
+    };
+    while (p + 32 <= P) take(std::integral_constant<int, 32>{});
+    while (p + 8 <= P) take(std::integral_constant<int, 8>{});
+    while (p < P) take(std::integral_constant<int, 1>{});
+    return make_double2(a, b);
+}
+
 // Merge the row partials; derive sigma^A, sigma^B, the next offsets and the
 // column-sweep row data; optional natural-log normalisers.
 // FP32 row data of the matrix-core column sweep (nullable): {k, w^A, w^B, 0} per row,
@@ -609,21 +719,16 @@ __device__ __forceinline__ void row_finish_body(Ctrl* ctrl, const Sched* sched, 
                            const double2* __restrict__ gtab2, const double* __restrict__ r,
                            const double* __restrict__ xn2, const double2* __restrict__ part, int P,
                            double* __restrict__ H, RowVar* __restrict__ rowvar, double2* __restrict__ rowck,
-                           double* __restrict__ log_za, double* __restrict__ log_zb, RowVarF32 rf, int64_t bx_, int64_t by_, int64_t nb_) {
-    if (halted(ctrl)) return;
+                           double* __restrict__ log_za, double* __restrict__ log_zb, RowVarF32 rf, int32_t done, int64_t bx_) {
+    if (done || ctrl->err || ctrl->t_row >= ctrl->t_end) return;
     int64_t i = (int64_t)bx_ * blockDim.x + threadIdx.x;
     if (i >= kc.n) return;
-    const int64_t t = ctrl->t;
+    const int64_t t = ctrl->t_row;
     const Sched sc = sched[t - ctrl->t_base];
     const double cA = 2.0 * kc.s * sc.lamA * LOG2E;
     const double cB = 2.0 * kc.s * sc.lamB * LOG2E;
-    double SA = 0.0, SB = 0.0;
-#pragma unroll 8   // independent loads in flight; the sum order is unchanged
-    for (int p = 0; p < P; ++p) {
-        double2 v = part[(int64_t)p * kc.n + i];
-        SA += v.x;
-        SB += v.y;
-    }
+    const double2 S = merge_splits(part, P, kc.n, i);
+    const double SA = S.x, SB = S.y;
     const double h = rf.f32_offsets ? (double)(float)H[i] : H[i];
     double sigA, sigB;
     const double lo = 0x1p-60, hi = 0x1p+60;
@@ -634,7 +739,7 @@ __device__ __forceinline__ void row_finish_body(Ctrl* ctrl, const Sched* sched, 
         const double2* g = gtab2 + (t & 1) * kc.m;
         sigA = exact_sigma(kc, xc + i * D, yc, D, g, 0, cA);
         sigB = exact_sigma(kc, xc + i * D, yc, D, g, 1, cB);
-        atomicAdd(&ctrl->fallbacks, 1);
+        atomicAdd(&ctrl->fallbacks_row, 1);
     }
     const double hnew = -sigB / cB;
     const double rho = cA / cB;
@@ -673,15 +778,6 @@ __device__ __forceinline__ void row_finish_body(Ctrl* ctrl, const Sched* sched, 
     }
     if (log_za) log_za[i] = LN2 * (-sc.lamA * LOG2E * kc.s * xn2[i] + sigA);
     if (log_zb) log_zb[i] = LN2 * (-sc.lamB * LOG2E * kc.s * xn2[i] + sigB);
-}
-
-__global__ void row_finish(Ctrl* ctrl, const Sched* sched, Consts kc, int D,
-                           const double* __restrict__ xc, const double* __restrict__ yc,
-                           const double2* __restrict__ gtab2, const double* __restrict__ r,
-                           const double* __restrict__ xn2, const double2* __restrict__ part, int P,
-                           double* __restrict__ H, RowVar* __restrict__ rowvar, double2* __restrict__ rowck,
-                           double* __restrict__ log_za, double* __restrict__ log_zb, RowVarF32 rf) {
-    row_finish_body(ctrl, sched, kc, D, xc, yc, gtab2, r, xn2, part, P, H, rowvar, rowck, log_za, log_zb, rf, (int64_t)blockIdx.x, (int64_t)blockIdx.y, (int64_t)gridDim.x);
 }
 
 // ---------------------------------------------------------------------------
@@ -775,6 +871,63 @@ __global__ __launch_bounds__(BLOCK) void col_sweep(const Ctrl* ctrl, const Sched
                                                    double2* __restrict__ cpart, int64_t split) {
     const SweepBlock sb = sweep_block(kc.n, split);
     col_sweep_body<M, D>(ctrl, sched, kc, xc, yc, gtab2, rowvar, rowck, cpart, split, sb.bx, sb.p, 0);
+}
+
+// Column sweep for grids that leave the chip short of waves, as row_sweep_par.
+template <int M, int D>
+__global__ __launch_bounds__(1024) void col_sweep_par(const Ctrl* ctrl, const Sched* sched, Consts kc,
+                                                      const double* __restrict__ xc, const double* __restrict__ yc,
+                                                      const double2* __restrict__ gtab2,
+                                                      const double2* __restrict__ rowck,
+                                                      double2* __restrict__ cpart, int64_t split) {
+    if (halted(ctrl)) return;
+    const int64_t t = ctrl->t;
+    const Sched sc = sched[t - ctrl->t_base];
+    const double cA = 2.0 * kc.s * sc.lamA * LOG2E;
+    const double cB = 2.0 * kc.s * sc.lamB * LOG2E;
+    const SweepBlock sb = sweep_block(kc.n, split);
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int waves = blockDim.x >> 6;
+    const int64_t j = sb.bx * 64 + lane;
+    const int64_t i0 = sb.p * split;
+    const int len = (int)(min(kc.n, i0 + split) - i0);
+    const int groups = (len + UNROLL - 1) / UNROLL;
+    const int64_t jj = j < kc.m ? j : kc.m - 1;
+    double y[D];
+#pragma unroll
+    for (int k = 0; k < D; ++k) y[k] = yc[jj * D + k];
+    const double2 g = gtab2[(t & 1) * kc.m + jj];
+    const double G = g.y / cB;
+    const double Dj = g.x - cA * G;
+    float* sums = group_sums();
+    auto run = [&](auto factor) {
+        constexpr bool FACTOR = decltype(factor)::value;
+        const int c1 = (wave + 1) * groups / waves;
+        for (int c = wave * groups / waves; c < c1; ++c) {
+            const double* __restrict__ xp = xc + (i0 + c * UNROLL) * D;
+            const double2* __restrict__ kp = rowck + i0 + c * UNROLL;
+            float accA = 0.f, accB = 0.f;
+            if ((c + 1) * UNROLL <= len) {
+#pragma unroll
+                for (int u = 0; u < UNROLL; ++u) col_terms<M, D, FACTOR>(y, xp + u * D, kp[u], G, Dj, cA, cB, accA, accB);
+            } else {
+                for (int u = 0; u < len - c * UNROLL; ++u)
+                    col_terms<M, D, FACTOR>(y, xp + u * D, kp[u], G, Dj, cA, cB, accA, accB);
+            }
+            sums[c * 64 + lane] = accA;
+            sums[(groups + c) * 64 + lane] = accB;
+        }
+    };
+    if (kc.factor_cols) run(std::true_type{});
+    else run(std::false_type{});
+    __syncthreads();
+    if (wave < 2 && j < kc.m) {
+        const double inv_n = 1.0 / (double)kc.n;   // the row weights r_i enter as n r_i (rowck)
+        double s = sum_groups(sums + wave * groups * 64, groups, lane);
+        s *= wave == 0 && kc.factor_cols ? exp2(Dj) * inv_n : inv_n;
+        reinterpret_cast<double*>(cpart)[2 * (sb.p * kc.m + j) + wave] = s;
+    }
 }
 
 __device__ __forceinline__ void col_sweep_dyn_body(const Ctrl* ctrl, const Sched* sched, Consts kc, int D,
@@ -1024,6 +1177,27 @@ struct TraceCols {
     double *col_a, *col_b, *theta_bar, *theta_hat;
 };
 
+// The sums of a and b over the block (up to BLOCK threads, whole waves), valid in thread 0.
+__device__ __forceinline__ double2 block_sums(double a, double b) {
+    __shared__ double2 sh[BLOCK / 64];
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) {
+        a += __shfl_xor(a, o, 64);
+        b += __shfl_xor(b, o, 64);
+    }
+    if (blockDim.x > 64) {
+        __syncthreads();   // an earlier call's sums are read
+        if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = make_double2(a, b);
+        __syncthreads();
+        a = b = 0.0;
+        for (int w = 0; w < (int)(blockDim.x >> 6); ++w) {
+            a += sh[w].x;
+            b += sh[w].y;
+        }
+    }
+    return make_double2(a, b);
+}
+
 __device__ __forceinline__ void dual_update_body(Ctrl* ctrl, const Sched* sched, Consts kc,
                                                      const double2* __restrict__ cpart, int P,
                                                      const double* __restrict__ c,
@@ -1032,20 +1206,22 @@ __device__ __forceinline__ void dual_update_body(Ctrl* ctrl, const Sched* sched,
                                                      float2* __restrict__ gtabf, int64_t m_pad,
                                                      double* __restrict__ respart, TraceCols tr,
                                                      double* __restrict__ dtpart, int64_t bx_) {
+    const bool first = bx_ == 0 && threadIdx.x == 0;
+    if (first) ctrl->done_seen = ctrl->done;
     if (halted(ctrl)) return;
     const int64_t t = ctrl->t;
+    if (first) {
+        ctrl->t_row = t + 1;   // the next row sweep; this iteration is complete with complete_iteration
+        ctrl->fallbacks += ctrl->fallbacks_row;
+        ctrl->fallbacks_row = 0;
+    }
     const Sched sc = sched[t - ctrl->t_base];
-    const int64_t j = (int64_t)bx_ * BLOCK + threadIdx.x;
+    const int64_t j = (int64_t)bx_ * blockDim.x + threadIdx.x;
     double res = 0.0, dtj = 0.0;
     int bad = 0;
     if (j < kc.m) {
-        double colA = 0.0, colB = 0.0;
-#pragma unroll 8   // independent loads in flight; the sum order is unchanged
-        for (int p = 0; p < P; ++p) {
-            double2 v = cpart[(int64_t)p * kc.m + j];
-            colA += v.x;
-            colB += v.y;
-        }
+        const double2 col = merge_splits(cpart, P, kc.m, j);
+        const double colA = col.x, colB = col.y;
         const double* nu_r = buf.nu[t & 1];
         const double* th_r = buf.theta[t & 1];
         double* nu_w = buf.nu[(t + 1) & 1];
@@ -1084,58 +1260,33 @@ __device__ __forceinline__ void dual_update_body(Ctrl* ctrl, const Sched* sched,
         if (tr.theta_hat) tr.theta_hat[j] = that;
     }
     // block reduction of the residual (and D_t summand; fixed order: deterministic)
-    __shared__ double sh[BLOCK];
-    __shared__ double shd[BLOCK];
-    __shared__ int shbad;
-    if (threadIdx.x == 0) shbad = 0;
-    __syncthreads();
-    if (bad) atomicOr(&shbad, 1);
-    sh[threadIdx.x] = res;
-    shd[threadIdx.x] = dtj;
-    __syncthreads();
-    for (int o = BLOCK / 2; o > 0; o >>= 1) {
-        if ((int)threadIdx.x < o) {
-            sh[threadIdx.x] += sh[threadIdx.x + o];
-            shd[threadIdx.x] += shd[threadIdx.x + o];
-        }
-        __syncthreads();
-    }
+    const double2 tot = block_sums(res, dtj);
     if (threadIdx.x == 0) {
-        respart[bx_] = sh[0];
-        if (dtpart) dtpart[bx_] = shd[0];
-        if (shbad) atomicOr(&ctrl->err, 1);
+        respart[bx_] = tot.x;
+        if (dtpart) dtpart[bx_] = tot.y;
     }
+    if (__any(bad) && (threadIdx.x & 63) == 0) atomicOr(&ctrl->err, 1);
 }
 
-// Completes iteration t after the dual update (a kernel of its own: the block partials are
-// visible at the kernel boundary, so the dual update needs no device-scope fence and no
-// last-block counter -- on a chip whose XCDs keep separate L2 caches every such fence writes
-// back the L2).  One block: the residual ||col(X^t) - c||_1 as a fixed-order tree over the
-// block partials, the stop decision (iterates t >= 1 only; t = 0 is the product coupling of
-// eta_0 = infinity), and otherwise the D_t summand of the step and t + 1.
-__device__ __forceinline__ void dual_finish_body(Ctrl* ctrl, const Sched* sched, const double* __restrict__ respart,
-                                                 const double* __restrict__ dtpart, int64_t nb) {
-    if (halted(ctrl)) return;   // the same control block for every thread: uniform
-    const int64_t t = ctrl->t;
-    __shared__ double sh[BLOCK];
-    __shared__ double shd[BLOCK];
+// Completes iteration t after its dual update (t_row = t + 1: a kernel boundary later, so that the
+// block partials are visible; the dual update needs no device-scope fence and no last-block
+// counter, which on a chip whose XCDs keep separate L2 caches write back the L2).  One block: the
+// residual ||col(X^t) - c||_1 as a fixed-order sum over the block partials, the stop decision
+// (iterates t >= 1 only; t = 0 is the product coupling of eta_0 = infinity), and otherwise the D_t
+// summand of the step and t + 1.
+__device__ __forceinline__ void complete_iteration(Ctrl* ctrl, const Sched* sched, const double* __restrict__ respart,
+                                                   const double* __restrict__ dtpart, int64_t nb) {
+    const int64_t t = ctrl->t;   // the same control block for every thread: uniform
+    if (ctrl->done != 0 || ctrl->t_row != t + 1) return;
     double a = 0.0, b = 0.0;
-    for (int64_t k = threadIdx.x; k < nb; k += BLOCK) {
+    for (int64_t k = threadIdx.x; k < nb; k += blockDim.x) {
         a += respart[k];
         if (dtpart) b += dtpart[k];
     }
-    sh[threadIdx.x] = a;
-    shd[threadIdx.x] = b;
-    __syncthreads();
-    for (int o = BLOCK / 2; o > 0; o >>= 1) {
-        if ((int)threadIdx.x < o) {
-            sh[threadIdx.x] += sh[threadIdx.x + o];
-            shd[threadIdx.x] += shd[threadIdx.x + o];
-        }
-        __syncthreads();
-    }
+    const double2 sums = block_sums(a, b);
+    __syncthreads();   // every thread has read t and done
     if (threadIdx.x != 0) return;
-    const double tot = sh[0];
+    const double tot = sums.x;
     ctrl->res_last = tot;
     if (ctrl->err) {
         ctrl->done = 1;
@@ -1147,15 +1298,34 @@ __device__ __forceinline__ void dual_finish_body(Ctrl* ctrl, const Sched* sched,
         if (dtpart) {
             // the step is taken: its D_t summand joins the sum
             const Sched sc = sched[t - ctrl->t_base];
-            ctrl->dt_acc += (sc.lamB - sc.lamA) * ctrl->dt_cost + shd[0];
+            ctrl->dt_acc += (sc.lamB - sc.lamA) * ctrl->dt_cost + sums.y;
         }
         ctrl->t = t + 1;
     }
 }
 
+// With nb > 0 the launch has one block more than the rows take, which completes the previous
+// iteration (complete_iteration) while the rows' blocks merge this one's sums: the residual is
+// looked at one row pass late, and a kernel per iteration is saved (4.5 us of 43 at 4096 x 4096).
+// The rows' blocks go by done_seen, which no block of this launch writes.
+__global__ void row_finish(Ctrl* ctrl, const Sched* sched, Consts kc, int D,
+                           const double* __restrict__ xc, const double* __restrict__ yc,
+                           const double2* __restrict__ gtab2, const double* __restrict__ r,
+                           const double* __restrict__ xn2, const double2* __restrict__ part, int P,
+                           double* __restrict__ H, RowVar* __restrict__ rowvar, double2* __restrict__ rowck,
+                           double* __restrict__ log_za, double* __restrict__ log_zb, RowVarF32 rf,
+                           const double* __restrict__ respart, int64_t nb) {
+    if (nb > 0 && blockIdx.x == gridDim.x - 1) {
+        complete_iteration(ctrl, sched, respart, nullptr, nb);
+        return;
+    }
+    row_finish_body(ctrl, sched, kc, D, xc, yc, gtab2, r, xn2, part, P, H, rowvar, rowck, log_za, log_zb, rf,
+                    ctrl->done_seen, (int64_t)blockIdx.x);
+}
+
 __global__ __launch_bounds__(BLOCK) void dual_finish(Ctrl* ctrl, const Sched* sched, const double* __restrict__ respart,
                                                      const double* __restrict__ dtpart, int64_t nb) {
-    dual_finish_body(ctrl, sched, respart, dtpart, nb);
+    complete_iteration(ctrl, sched, respart, dtpart, nb);
 }
 
 __global__ __launch_bounds__(BLOCK) void dual_update(Ctrl* ctrl, const Sched* sched, Consts kc,

@@ -449,8 +449,8 @@ __global__ __launch_bounds__(BLOCK, (row_sweep_min_waves<T, KP>())) void row_swe
     constexpr int NS = KP / Op::KSTEP;
     constexpr bool INTERLEAVE = sizeof(T) == 2 && NS >= 12;   // measured: +1.5% at NS = 12, -8% at NS = 4
     __shared__ __align__(16) char lds[2][L::BUF];
-    if (halted(ctrl)) return;
-    const int64_t t = ctrl->t;
+    if (halted_row(ctrl)) return;
+    const int64_t t = ctrl->t_row;
     const Sched sc = sched[t - ctrl->t_base];
     // the products come scaled by 1 / dscale (a power of two): the factors of the products
     // take dscale, the offsets entering the accumulator 1 / dscale (exact scalings)
@@ -880,8 +880,8 @@ __device__ __forceinline__ void row_sweep_mfma64_body(const Ctrl* ctrl, const Sc
     using L = LdsTile64<KP>;
     constexpr int NS = KP / 4;
     __shared__ __align__(16) char lds[2][L::BUF];
-    if (halted(ctrl)) return;
-    const int64_t t = ctrl->t;
+    if (halted_row(ctrl)) return;
+    const int64_t t = ctrl->t_row;
     const Sched sc = sched[t - ctrl->t_base];
     const double cA = 2.0 * kc.s * sc.lamA * LOG2E;
     const double cB = 2.0 * kc.s * sc.lamB * LOG2E;

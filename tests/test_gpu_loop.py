@@ -2,10 +2,12 @@
 enqueue exactly the iterations that were asked for."""
 from __future__ import annotations
 
+import numpy as np
 import pytest
 import torch
 
 import paper_2511_11359_amd as P
+from oracle import lamp as OL
 from paper_2511_11359_amd import workloads as W
 
 pytestmark = pytest.mark.gpu
@@ -36,3 +38,39 @@ def test_batch_stops_and_counts_with_the_rest_running():
         for s, r, o in zip(states, reps, one):
             assert r["converged"] and r["iters"] == s.t == o["iters"]
             assert r["final_res"] <= tol
+
+
+@pytest.mark.parametrize("n,m,d,metric", [(1, 1, 1, "sqeuclid"), (63, 65, 2, "sqeuclid"), (64, 129, 3, "l1"), (65, 1031, 7, "sqeuclid"),
+                                          (2049, 130, 16, "sqeuclid"), (500, 517, 12, "sqeuclid"), (300, 9, 8, "linf")])
+def test_small_sweeps_match_oracle(n, m, d, metric):
+    """Small grids run the group-parallel sweeps (64-row blocks, split groups over the waves): ends of
+    blocks and groups, fewer groups than waves.  Tolerances as in test_gpu_dims.py."""
+    wl = W.random_small(n, m, d, seed=900 + n, eta=1e-2)
+    x, y = wl.x.astype(np.float64), wl.y.astype(np.float64)
+    s = 1.0 / OL.max_cost(x, y, metric)
+    C, prm = OL.ground_cost(x, y, s, metric), OL.Params(eta=wl.eta)
+    at, _ = OL.lamp_dense(C, wl.r, wl.c, prm, 3, 1.0, trace=False)
+    _, tr_or = OL.lamp_dense(C, wl.r, wl.c, prm, 1, 1.0, state=at)
+    dev = lambda v: torch.tensor(v, dtype=torch.float64, device="cuda")  # noqa: E731
+    st = P.State(dev(at.nu), dev(at.theta), at.t, at.lam)
+    prob = P.Problem(wl.x, wl.y, wl.r, wl.c, cost_scale=s, cost_norm=1.0, metric=metric)
+    _, tr = P.step(prob, P.make_params(eta=wl.eta), st, trace=True)
+    for col, ref in (("col_a", tr_or.colA[0]), ("col_b", tr_or.colB[0])):
+        assert np.all(np.abs(tr[col].cpu().numpy() - ref) <= 4e-6 * ref + 1e-30)
+    assert np.max(np.abs(tr["log_za"].cpu().numpy() - tr_or.logZA[0])) <= 2e-6
+    assert np.max(np.abs(tr["log_zb"].cpu().numpy() - tr_or.logZB[0])) <= 2e-6
+
+
+def test_fused_completion_matches_single_steps():
+    """A solve completes each iteration in the next one's row pass; steps complete theirs at once.
+    From one state, k single iterations resumed by solve(max_iter=1) take the same decisions, and a
+    stop keeps the iterate that met the tolerance."""
+    wl = W.random_small(130, 210, 2, seed=8, eta=1e-2)
+    prob = P.Problem(wl.x, wl.y, wl.r, wl.c)
+    full, rep, _ = P.solve(prob, P.make_params(eta=wl.eta, tol=3e-2, max_iter=4000))
+    assert rep["converged"] and rep["final_res"] <= 3e-2
+    again, rep2, _ = P.solve(prob, P.make_params(eta=wl.eta, max_iter=rep["iters"]))
+    assert rep2["iters"] == rep["iters"] == full.t
+    assert torch.equal(again.nu, full.nu) and torch.equal(again.theta, full.theta)
+    _, rep3, _ = P.solve(prob, P.make_params(eta=wl.eta, tol=3e-2, max_iter=rep["iters"]))
+    assert rep3["iters"] == rep["iters"] and not rep3["converged"]   # its iterate is tested one iteration later
