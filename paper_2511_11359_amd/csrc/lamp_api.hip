@@ -517,26 +517,6 @@ bool sweep_dispatch(int d, F&& launch) {
     return false;
 }
 
-// The certificate's pair passes: the compiled dimensions of the vector-ALU sweeps and, for the
-// squared Euclidean cost, 32 and 64 (the thread's own point in registers and the streamed
-// point through scalar loads; the run-time form loads both points' coordinates per pair,
-// 6.6 s for a certificate at n = m = 2^16, d = 64).
-template <int M, typename F>
-bool cert_dispatch(int d, F&& launch) {
-    if (sweep_dispatch<M>(d, launch)) return true;
-    if constexpr (M == METRIC_SQEUCLID) {
-        if (d == 32) {
-            launch(IC<32>{});
-            return true;
-        }
-        if (d == 64) {
-            launch(IC<64>{});
-            return true;
-        }
-    }
-    return false;
-}
-
 // f(IC<M>) for the run-time metric.
 template <typename F>
 bool by_metric(int metric, F&& f) {
@@ -1979,6 +1959,10 @@ lamp_status lamp_certificate(const lamp_problem* prob, const lamp_params* params
     double* vals = sc + 13 * nm;     // 4n
     double* mu = sc + 17 * nm;       // 2n: the row minima of C_ij + K theta_j, C_ij + K nu_j
     double* S = sc + 19 * nm;        // d + 2
+    // column and row data of single passes, in arrays that a later pass fills
+    float* wf = reinterpret_cast<float*>(dr);             // n, until round_rows_merge
+    float2* yff = reinterpret_cast<float2*>(tr1);         // m, until round_rank_one
+    double2* soft_cols = reinterpret_cast<double2*>(dr);  // m, after the sums of cpp, tr1, absdr
     const dim3 split_grid(sweep_grid(kc.n, L.P_r));
     hipLaunchKernelGGL(col_residual, grid1(kc.m), dim3(BLOCK), 0, st, kc, at<double2>(ws, L.cpart), col_parts(LV),
                        prob->c, colres);
@@ -1986,12 +1970,23 @@ lamp_status lamp_certificate(const lamp_problem* prob, const lamp_params* params
                        at<double2>(ws, L.gtab), gA);
     // pair passes: the kernel of the problem's metric and dimension, coordinates of the
     // thread's own point in registers where compiled (run-time form otherwise)
+    OwnPts xs{at<double>(ws, L.xc), prob->d, 1}, ys{at<double>(ws, L.yc), prob->d, 1};
     auto by_md = [&](auto&& launch) {
         const bool done = by_metric(kc.metric, [&](auto m) {
-            return cert_dispatch<decltype(m)::value>(prob->d, [&](auto dd) { launch(m, dd); });
+            return sweep_dispatch<decltype(m)::value>(prob->d, [&](auto dd) { launch(m, dd); });
         });
         if (!done) launch(IC<-1>{}, IC<0>{});
     };
+    if (L.use64) {
+        // d > 16: the run-time form reads the own points coordinate by coordinate; the matrix-core
+        // operand copies (n d and m d doubles or more) are not needed any more
+        xs = OwnPts{at<double>(ws, L.xop64), 1, kc.n};
+        ys = OwnPts{at<double>(ws, L.yop64), 1, kc.m};
+        hipLaunchKernelGGL(transpose_points, grid1(kc.n * prob->d), dim3(BLOCK), 0, st, (const double*)at<double>(ws, L.xc),
+                           kc.n, prob->d, at<double>(ws, L.xop64));
+        hipLaunchKernelGGL(transpose_points, grid1(kc.m * prob->d), dim3(BLOCK), 0, st, (const double*)at<double>(ws, L.yc),
+                           kc.m, prob->d, at<double>(ws, L.yop64));
+    }
     // explicit cost: the row-wise passes in the row sweep's layout (coalesced reads of C)
     const dim3 cost_rows_grid((unsigned)cdiv(kc.n, 4 * COST_ROWS));
     if (L.cost) {
@@ -2003,7 +1998,7 @@ lamp_status lamp_certificate(const lamp_problem* prob, const lamp_params* params
     } else {
         by_md([&](auto m, auto dd) {
             hipLaunchKernelGGL((cert_rows<decltype(m)::value, decltype(dd)::value>), split_grid, dim3(BLOCK), 0,
-                               st, kc, prob->d, cA, at<double>(ws, L.xc), at<double>(ws, L.yc),
+                               st, kc, prob->d, cA, xs, at<double>(ws, L.yc),
                                at<double>(ws, L.xn2), at<double>(ws, L.yn2), gA, at<double>(ws, L.H), state->nu,
                                state->theta, part, L.split_r);
         });
@@ -2015,7 +2010,7 @@ lamp_status lamp_certificate(const lamp_problem* prob, const lamp_params* params
     hipLaunchKernelGGL(reduce_sums, dim3(1), dim3(1024), 0, st, colres, kc.m, kc.m, 1, small + 4);
     hipLaunchKernelGGL(reduce_sums, dim3(1), dim3(1024), 0, st, prods, kc.m, kc.m, 2, small + 5);
     // Round (Algorithm 3) of the same X and its cost
-    hipLaunchKernelGGL(round_row_factors, grid1(kc.n), dim3(BLOCK), 0, st, kc, psum, xr);
+    hipLaunchKernelGGL(round_row_factors, grid1(kc.n), dim3(BLOCK), 0, st, kc, psum, prob->r, xr, wf);
     // Round step 2 over row splits; the split partials reuse the (consumed) column partials
     double* rpart = at<double>(ws, L.cpart);
     if (L.cost) {
@@ -2028,13 +2023,12 @@ lamp_status lamp_certificate(const lamp_problem* prob, const lamp_params* params
         by_md([&](auto m, auto dd) {
             hipLaunchKernelGGL((round_cols<decltype(m)::value, decltype(dd)::value>),
                                dim3(sweep_grid(kc.m, L.P_c)), dim3(BLOCK), 0, st, kc, prob->d, cA,
-                               at<double>(ws, L.xc), at<double>(ws, L.yc), gA, at<double>(ws, L.H), prob->r, xr,
-                               rpart, L.split_c);
+                               at<double>(ws, L.xc), ys, gA, at<double>(ws, L.H), (const float*)wf, rpart, L.split_c);
         });
     }
     hipLaunchKernelGGL(round_cols_merge, grid1(kc.m), dim3(BLOCK), 0, st, kc, (const double*)rpart,
                        (int)(L.cost ? L.P_cx : L.P_c), colp);
-    hipLaunchKernelGGL(round_col_factors, grid1(kc.m), dim3(BLOCK), 0, st, kc, prob->c, colp, yf, dc);
+    hipLaunchKernelGGL(round_col_factors, grid1(kc.m), dim3(BLOCK), 0, st, kc, prob->c, colp, yf, dc, yff);
     if (L.cost) {
         by_cost_type(kc.cost_type, [&](auto tag) {
             using T = std::remove_pointer_t<decltype(tag)>;
@@ -2044,9 +2038,9 @@ lamp_status lamp_certificate(const lamp_problem* prob, const lamp_params* params
     } else {
         by_md([&](auto m, auto dd) {
             hipLaunchKernelGGL((round_rows<decltype(m)::value, decltype(dd)::value>), split_grid, dim3(BLOCK), 0,
-                               st, kc, prob->d, cA, at<double>(ws, L.xc), at<double>(ws, L.yc),
-                               at<double>(ws, L.xn2), at<double>(ws, L.yn2), gA, at<double>(ws, L.H), yf, part,
-                               L.split_r);
+                               st, kc, prob->d, cA, xs, at<double>(ws, L.yc),
+                               at<double>(ws, L.xn2), at<double>(ws, L.yn2), gA, at<double>(ws, L.H),
+                               (const float2*)yff, part, L.split_r);
         });
         hipLaunchKernelGGL(round_rows_merge, grid1(kc.n), dim3(BLOCK), 0, st, kc, (int)L.P_r, prob->r, xr,
                            (const double*)part, dr, cpp);
@@ -2079,11 +2073,12 @@ lamp_status lamp_certificate(const lamp_problem* prob, const lamp_params* params
         double* sv = vals;   // 2n (the row values above are reduced)
         // the minima: from the certificate row pass (recovered from r_i min for the explicit cost)
         if (L.cost) hipLaunchKernelGGL(row_minima_of_vals, grid1(kc.n), dim3(BLOCK), 0, st, kc, prob->r, vals, mu);
+        hipLaunchKernelGGL(cert_soft_cols, grid1(kc.m), dim3(BLOCK), 0, st, kc, 1.0 / params->eta,
+                           at<double>(ws, L.yn2), state->nu, state->theta, soft_cols);
         by_md([&](auto m, auto dd) {
             hipLaunchKernelGGL((cert_soft_rows<decltype(m)::value, decltype(dd)::value>), split_grid, dim3(BLOCK),
-                               0, st, kc, prob->d, 1.0 / params->eta, at<double>(ws, L.xc), at<double>(ws, L.yc),
-                               at<double>(ws, L.xn2), at<double>(ws, L.yn2), state->nu, state->theta,
-                               (const double*)mu, part, L.split_r);
+                               0, st, kc, prob->d, 1.0 / params->eta, xs, at<double>(ws, L.yc), at<double>(ws, L.xn2),
+                               (const double2*)soft_cols, (const double*)mu, part, L.split_r);
         });
         hipLaunchKernelGGL(cert_soft_merge, grid1(kc.n), dim3(BLOCK), 0, st, kc, (int)L.P_r, 1.0 / params->eta,
                            prob->r, (const double*)mu, (const double*)part, sv);

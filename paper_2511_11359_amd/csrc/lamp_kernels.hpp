@@ -1405,30 +1405,100 @@ __global__ void marginal_stats(const double* __restrict__ a, int64_t len, double
 }
 
 // ---------------------------------------------------------------------------
-// The pair term of the thread's own point against streamed points: coordinates in
-// registers for a compile-time dimension (M, D), read from memory for the run-time
-// metric and dimension (M = -1, D = 0).  The pair term is symmetric in its points.
+// The pair terms of the thread's own point against UNROLL streamed points (or one): coordinates
+// in registers for a compile-time dimension (M, D); for the run-time metric and dimension
+// (M = -1, D = 0) four coordinates at a time, each used for all UNROLL streamed points (one load
+// of an own coordinate per 8 pairs; coordinate k of the point at src[k stride]).  The sum of a
+// pair runs over k in order either way.  The pair term is symmetric in its points.
 // ---------------------------------------------------------------------------
 template <int M, int D>
 struct OwnPoint {
     double x[D];
-    __device__ __forceinline__ OwnPoint(const double* __restrict__ src, int, const Consts&) {
+    __device__ __forceinline__ OwnPoint(const double* __restrict__ src, int64_t, int, const Consts&) {
 #pragma unroll
         for (int k = 0; k < D; ++k) x[k] = src[k];
     }
     __device__ __forceinline__ double pair(const double* __restrict__ y) const { return pair_term<M, D>(x, y, 0.0); }
+    __device__ __forceinline__ void pairs(const double* __restrict__ y, double (&out)[UNROLL]) const {
+#pragma unroll
+        for (int u = 0; u < UNROLL; ++u) out[u] = pair(y + u * D);
+    }
 };
 
 template <>
 struct OwnPoint<-1, 0> {
     const double* x;
+    int64_t stride;
     int d;
-    Consts kc;
-    __device__ __forceinline__ OwnPoint(const double* __restrict__ src, int d_, const Consts& kc_)
-        : x(src), d(d_), kc(kc_) {}
+    const Consts& kc;
+    __device__ __forceinline__ OwnPoint(const double* __restrict__ src, int64_t stride_, int d_, const Consts& kc_)
+        : x(src), stride(stride_), d(d_), kc(kc_) {}
     __device__ __forceinline__ double pair(const double* __restrict__ y) const {
-        return pair_term_dyn(kc, d, x, y, 0.0);
+        if (kc.metric == METRIC_EXPLICIT) return pair_term_cost(kc, x[0], y[0], 0.0);
+        double a = 0.0;
+        for (int k = 0; k < d; ++k) a = accumulate(a, x[k * stride], y[k]);
+        return kc.metric == METRIC_SQEUCLID ? a : fma(-0.5, a, 0.0);
     }
+    __device__ __forceinline__ void pairs(const double* __restrict__ y, double (&out)[UNROLL]) const {
+        if (kc.metric == METRIC_EXPLICIT) {
+#pragma unroll
+            for (int u = 0; u < UNROLL; ++u) out[u] = pair_term_cost(kc, x[0], y[u], 0.0);
+        } else if (kc.metric == METRIC_SQEUCLID) {
+            run<METRIC_SQEUCLID>(y, out);
+        } else if (kc.metric == METRIC_L1) {
+            run<METRIC_L1>(y, out);
+        } else {
+            run<METRIC_LINF>(y, out);
+        }
+    }
+
+private:
+    template <int M>
+    __device__ __forceinline__ static double add(double a, double u, double v) {
+        if constexpr (M == METRIC_SQEUCLID) return fma(u, v, a);
+        const double t = fabs(u - v);
+        return M == METRIC_L1 ? a + t : fmax(a, t);
+    }
+    __device__ __forceinline__ double accumulate(double a, double u, double v) const {
+        if (kc.metric == METRIC_SQEUCLID) return add<METRIC_SQEUCLID>(a, u, v);
+        return kc.metric == METRIC_L1 ? add<METRIC_L1>(a, u, v) : add<METRIC_LINF>(a, u, v);
+    }
+    template <int M>
+    __device__ __forceinline__ void run(const double* __restrict__ y, double (&out)[UNROLL]) const {
+#pragma unroll
+        for (int u = 0; u < UNROLL; ++u) out[u] = 0.0;
+        int k = 0;
+        for (; k + 4 <= d; k += 4) {
+            double v[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) v[q] = x[(k + q) * stride];
+#pragma unroll
+            for (int u = 0; u < UNROLL; ++u)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) out[u] = add<M>(out[u], v[q], y[u * d + k + q]);
+        }
+        for (; k < d; ++k) {
+            const double v = x[k * stride];
+#pragma unroll
+            for (int u = 0; u < UNROLL; ++u) out[u] = add<M>(out[u], v, y[u * d + k]);
+        }
+        if constexpr (M != METRIC_SQEUCLID) {
+#pragma unroll
+            for (int u = 0; u < UNROLL; ++u) out[u] = fma(-0.5, out[u], 0.0);
+        }
+    }
+};
+
+// out[k len + i] = src[i d + k]: the own points' coordinates side by side for the run-time form.
+__global__ void transpose_points(const double* __restrict__ src, int64_t len, int d, double* __restrict__ out) {
+    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (e < len * d) out[e] = src[(e % len) * d + e / len];
+}
+
+// Coordinates of the own points of a pass: point i, coordinate k at p[i point + k coord].
+struct OwnPts {
+    const double* p;
+    int64_t point, coord;
 };
 
 // ---------------------------------------------------------------------------
@@ -1444,9 +1514,11 @@ struct OwnPoint<-1, 0> {
 // column splits (sweep_block): part[p][i] = (sum_j p_ij, sum_j C_ij p_ij, the two minima) of
 // split p, combined in order by cert_rows_merge.
 // ---------------------------------------------------------------------------
+// Groups of UNROLL streamed columns run with a compile-time count (their data are wave-uniform
+// scalar loads issued together), and what depends on the column alone comes precomputed: 18
+// vector slots a pair at d = 3, 4.5 -> 2.2 ms at 65536 x 65536.
 template <int M, int D>
-__global__ __launch_bounds__(BLOCK) void cert_rows(Consts kc, int Dm, double cA,
-                                                   const double* __restrict__ xc,
+__global__ __launch_bounds__(BLOCK) void cert_rows(Consts kc, int Dm, double cA, OwnPts xs,
                                                    const double* __restrict__ yc,
                                                    const double* __restrict__ xn2,
                                                    const double* __restrict__ yn2,
@@ -1460,24 +1532,35 @@ __global__ __launch_bounds__(BLOCK) void cert_rows(Consts kc, int Dm, double cA,
     if (i >= kc.n) return;
     const int64_t j0 = sb.p * split;
     const int64_t j1 = min(kc.m, j0 + split);
-    const OwnPoint<M, D> own(xc + i * Dm, Dm, kc);
-    const double h = H[i];
+    const OwnPoint<M, D> own(xs.p + i * xs.point, xs.coord, Dm, kc);
+    const double h = H[i], xi2 = xn2[i];
     double psum = 0.0, csum = 0.0, mth = __builtin_inf(), mnu = __builtin_inf();
-    for (int64_t jb = j0; jb < j1; jb += UNROLL) {
-        const int64_t je = min(j1, jb + UNROLL);
-        float ap = 0.f, ac = 0.f;
-        for (int64_t j = jb; j < je; ++j) {
-            const double dot = own.pair(yc + j * Dm);
-            const float p = fexp2(fma(cA, h + dot, gA[j]));
-            const double cij = kc.s * (xn2[i] + yn2[j] - 2.0 * dot);
-            ap += p;
-            ac = fmaf((float)cij, p, ac);
-            mth = fmin(mth, cij + kc.K * theta[j]);
-            mnu = fmin(mnu, cij + kc.K * nu[j]);
-        }
+    float ap = 0.f, ac = 0.f;
+    double K = kc.K;
+    asm("" : "+v"(K));   // one scalar operand an instruction: the column's
+    auto term = [&](double dot, int64_t j) {
+        const float p = fexp2(fma_su(h + dot, cA, gA[j]));
+        const double cij = kc.s * (xi2 + yn2[j] - 2.0 * dot);
+        ap += p;
+        ac = fmaf((float)cij, p, ac);
+        mth = fmin(mth, fma(K, theta[j], cij));
+        mnu = fmin(mnu, fma(K, nu[j], cij));
+    };
+    auto carry = [&] {
         psum += (double)ap;
         csum += (double)ac;
+        ap = ac = 0.f;
+    };
+    int64_t j = j0;
+    for (; j + UNROLL <= j1; j += UNROLL) {
+        double dot[UNROLL];
+        own.pairs(yc + j * Dm, dot);
+#pragma unroll
+        for (int u = 0; u < UNROLL; ++u) term(dot[u], j + u);
+        carry();
     }
+    for (; j < j1; ++j) term(own.pair(yc + j * Dm), j);
+    carry();
     double* o = part + (sb.p * kc.n + i) * 4;
     o[0] = psum;
     o[1] = csum;
@@ -1518,14 +1601,23 @@ __global__ void cert_rows_merge(Consts kc, int P, const double* __restrict__ r, 
 // FP64 across them and across the splits (in order).
 //   part[p][i] = (split p's sum for theta, for nu);  vals[0][i] = r_i softmin_i(theta), vals[1][i] likewise.
 // ---------------------------------------------------------------------------
+// With f = -lam LOG2E the base-2 exponent is (2 s lam LOG2E P_ij + b_j) + (f s |x~_i|^2 - f mu_i),
+// b_j = f (s |y~_j|^2 + K v_j) per column from cert_soft_cols: 15 vector slots a pair at d = 3
+// instead of 20, 4.1 -> 1.8 ms at 65536 x 65536.
+__global__ void cert_soft_cols(Consts kc, double lam, const double* __restrict__ yn2,
+                               const double* __restrict__ nu, const double* __restrict__ theta,
+                               double2* __restrict__ out) {
+    const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (j >= kc.m) return;
+    const double f = -lam * LOG2E, b = kc.s * yn2[j];
+    out[j] = make_double2(f * (b + kc.K * theta[j]), f * (b + kc.K * nu[j]));
+}
+
 template <int M, int D>
-__global__ __launch_bounds__(BLOCK) void cert_soft_rows(Consts kc, int Dm, double lam,
-                                                        const double* __restrict__ xc,
+__global__ __launch_bounds__(BLOCK) void cert_soft_rows(Consts kc, int Dm, double lam, OwnPts xs,
                                                         const double* __restrict__ yc,
                                                         const double* __restrict__ xn2,
-                                                        const double* __restrict__ yn2,
-                                                        const double* __restrict__ nu,
-                                                        const double* __restrict__ theta,
+                                                        const double2* __restrict__ cols,
                                                         const double* __restrict__ mu,
                                                         double* __restrict__ part, int64_t split) {
     const SweepBlock sb = sweep_block(kc.m, split);
@@ -1533,21 +1625,31 @@ __global__ __launch_bounds__(BLOCK) void cert_soft_rows(Consts kc, int Dm, doubl
     if (i >= kc.n) return;
     const int64_t j0 = sb.p * split;
     const int64_t j1 = min(kc.m, j0 + split);
-    const OwnPoint<M, D> own(xc + i * Dm, Dm, kc);
-    const double mth = mu[i], mnu = mu[kc.n + i];
-    const double f = -lam * LOG2E;
+    const OwnPoint<M, D> own(xs.p + i * xs.point, xs.coord, Dm, kc);
+    const double f = -lam * LOG2E, c = -2.0 * f * kc.s;
+    const double rth = f * (kc.s * xn2[i] - mu[i]), rnu = f * (kc.s * xn2[i] - mu[kc.n + i]);
     double sth = 0.0, snu = 0.0;
-    for (int64_t jb = j0; jb < j1; jb += UNROLL) {
-        const int64_t je = min(j1, jb + UNROLL);
-        float at = 0.f, an = 0.f;
-        for (int64_t j = jb; j < je; ++j) {
-            const double cij = kc.s * (xn2[i] + yn2[j] - 2.0 * own.pair(yc + j * Dm));
-            at += fexp2(f * (cij + kc.K * theta[j] - mth));
-            an += fexp2(f * (cij + kc.K * nu[j] - mnu));
-        }
+    float at = 0.f, an = 0.f;
+    auto term = [&](double dot, int64_t j) {
+        const double2 b = cols[j];
+        at += fexp2(fma_su(dot, c, b.x) + rth);
+        an += fexp2(fma_su(dot, c, b.y) + rnu);
+    };
+    auto carry = [&] {
         sth += (double)at;
         snu += (double)an;
+        at = an = 0.f;
+    };
+    int64_t j = j0;
+    for (; j + UNROLL <= j1; j += UNROLL) {
+        double dot[UNROLL];
+        own.pairs(yc + j * Dm, dot);
+#pragma unroll
+        for (int u = 0; u < UNROLL; ++u) term(dot[u], j + u);
+        carry();
     }
+    for (; j < j1; ++j) term(own.pair(yc + j * Dm), j);
+    carry();
     double* o = part + (sb.p * kc.n + i) * 2;
     o[0] = sth;
     o[1] = snu;
@@ -1581,37 +1683,50 @@ __global__ void cert_soft_merge(Consts kc, int P, double lam, const double* __re
 // is O(d) per row once the column sums are known.  The pair passes use the terms of
 // the certificate row sweep (FP32 exponentials, FP64 sums), the O(n + m) steps FP64.
 // ---------------------------------------------------------------------------
-__global__ void round_row_factors(Consts kc, const double* __restrict__ psum, double* __restrict__ xr) {
+// w_i = xr_i r_i rounded to FP32 (the weight of the pair terms).
+__global__ void round_row_factors(Consts kc, const double* __restrict__ psum, const double* __restrict__ r,
+                                  double* __restrict__ xr, float* __restrict__ w) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < kc.n) xr[i] = fmin(1.0 / psum[i], 1.0);
+    if (i >= kc.n) return;
+    const double x = fmin(1.0 / psum[i], 1.0);
+    xr[i] = x;
+    w[i] = (float)(x * r[i]);
 }
 
 // part[p][j] = sum over the rows i of split p of xr_i r_i p_ij (one thread per
 // column, rows in order); round_cols_merge adds the splits in order: colp_j.
+// 9 vector slots a pair at d = 3 (the weights were multiplied and rounded per pair before: 3.4 ->
+// 1.2 ms at 65536 x 65536).
 template <int M, int D>
 __global__ __launch_bounds__(BLOCK) void round_cols(Consts kc, int Dm, double cA, const double* __restrict__ xc,
-                                                    const double* __restrict__ yc, const double* __restrict__ gA,
-                                                    const double* __restrict__ H, const double* __restrict__ r,
-                                                    const double* __restrict__ xr, double* __restrict__ part,
-                                                    int64_t split) {
+                                                    OwnPts ys, const double* __restrict__ gA,
+                                                    const double* __restrict__ H, const float* __restrict__ w,
+                                                    double* __restrict__ part, int64_t split) {
     const SweepBlock sb = sweep_block(kc.n, split);
     const int64_t j = sb.bx * BLOCK + threadIdx.x;
     if (j >= kc.m) return;
     const int64_t p = sb.p;
     const int64_t i0 = p * split;
     const int64_t i1 = min(kc.n, i0 + split);
-    const OwnPoint<M, D> own(yc + j * Dm, Dm, kc);
+    const OwnPoint<M, D> own(ys.p + j * ys.point, ys.coord, Dm, kc);
     const double g = gA[j];
     double acc = 0.0;
-    for (int64_t ib = i0; ib < i1; ib += UNROLL) {
-        const int64_t ie = min(i1, ib + UNROLL);
-        float a = 0.f;
-        for (int64_t i = ib; i < ie; ++i) {
-            const double dot = own.pair(xc + i * Dm);
-            a = fmaf((float)(xr[i] * r[i]), fexp2(fma(cA, H[i] + dot, g)), a);
-        }
+    float a = 0.f;
+    auto term = [&](double dot, int64_t i) { a = fmaf(w[i], fexp2(fma(cA, H[i] + dot, g)), a); };
+    auto carry = [&] {
         acc += (double)a;
+        a = 0.f;
+    };
+    int64_t i = i0;
+    for (; i + UNROLL <= i1; i += UNROLL) {
+        double dot[UNROLL];
+        own.pairs(xc + i * Dm, dot);
+#pragma unroll
+        for (int u = 0; u < UNROLL; ++u) term(dot[u], i + u);
+        carry();
     }
+    for (; i < i1; ++i) term(own.pair(xc + i * Dm), i);
+    carry();
     part[p * kc.m + j] = acc;
 }
 
@@ -1623,14 +1738,15 @@ __global__ void round_cols_merge(Consts kc, const double* __restrict__ part, int
     colp[j] = a;
 }
 
-// y_j = min(c_j / colp_j, 1) and dc_j = c_j - y_j colp_j.
+// y_j = min(c_j / colp_j, 1), dc_j = c_j - y_j colp_j, and (y_j, 1 - y_j) in FP32 for the pair terms.
 __global__ void round_col_factors(Consts kc, const double* __restrict__ c, const double* __restrict__ colp,
-                                  double* __restrict__ y, double* __restrict__ dc) {
+                                  double* __restrict__ y, double* __restrict__ dc, float2* __restrict__ yf) {
     const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (j >= kc.m) return;
     const double yj = colp[j] > 0.0 ? fmin(c[j] / colp[j], 1.0) : 1.0;
     y[j] = yj;
     dc[j] = c[j] - yj * colp[j];
+    yf[j] = make_float2((float)yj, (float)(1.0 - yj));
 }
 
 // Rows of X'': dr_i = r_i - xr_i r_i sum_j p_ij y_j and cpp_i = xr_i r_i sum_j C_ij p_ij y_j.
@@ -1638,35 +1754,44 @@ __global__ void round_col_factors(Consts kc, const double* __restrict__ c, const
 // with psum_i recomputed in this pass: no difference of two nearly equal sums.  Over XCD-aware
 // column splits: part[p][i] = split p's three sums, combined in order by round_rows_merge.
 template <int M, int D>
-__global__ __launch_bounds__(BLOCK) void round_rows(Consts kc, int Dm, double cA, const double* __restrict__ xc,
+__global__ __launch_bounds__(BLOCK) void round_rows(Consts kc, int Dm, double cA, OwnPts xs,
                                                     const double* __restrict__ yc, const double* __restrict__ xn2,
                                                     const double* __restrict__ yn2, const double* __restrict__ gA,
-                                                    const double* __restrict__ H, const double* __restrict__ y,
+                                                    const double* __restrict__ H, const float2* __restrict__ yf,
                                                     double* __restrict__ part, int64_t split) {
     const SweepBlock sb = sweep_block(kc.m, split);
     const int64_t i = sb.bx * BLOCK + threadIdx.x;
     if (i >= kc.n) return;
     const int64_t j0 = sb.p * split;
     const int64_t j1 = min(kc.m, j0 + split);
-    const OwnPoint<M, D> own(xc + i * Dm, Dm, kc);
-    const double h = H[i];
+    const OwnPoint<M, D> own(xs.p + i * xs.point, xs.coord, Dm, kc);
+    const double h = H[i], xi2 = xn2[i];
     double ps = 0.0, pq = 0.0, cs = 0.0;
-    for (int64_t jb = j0; jb < j1; jb += UNROLL) {
-        const int64_t je = min(j1, jb + UNROLL);
-        float a = 0.f, b = 0.f, e = 0.f;
-        for (int64_t j = jb; j < je; ++j) {
-            const double dot = own.pair(yc + j * Dm);
-            const float p = fexp2(fma(cA, h + dot, gA[j]));
-            const double yj = y[j];
-            const float py = p * (float)yj;
-            a += p;
-            b = fmaf(p, (float)(1.0 - yj), b);
-            e = fmaf((float)(kc.s * (xn2[i] + yn2[j] - 2.0 * dot)), py, e);
-        }
+    float a = 0.f, b = 0.f, e = 0.f;
+    auto term = [&](double dot, int64_t j) {
+        const float p = fexp2(fma_su(h + dot, cA, gA[j]));
+        const float2 y = yf[j];
+        const float py = p * y.x;
+        a += p;
+        b = fmaf(p, y.y, b);
+        e = fmaf((float)(kc.s * (xi2 + yn2[j] - 2.0 * dot)), py, e);
+    };
+    auto carry = [&] {
         ps += (double)a;
         pq += (double)b;
         cs += (double)e;
+        a = b = e = 0.f;
+    };
+    int64_t j = j0;
+    for (; j + UNROLL <= j1; j += UNROLL) {
+        double dot[UNROLL];
+        own.pairs(yc + j * Dm, dot);
+#pragma unroll
+        for (int u = 0; u < UNROLL; ++u) term(dot[u], j + u);
+        carry();
     }
+    for (; j < j1; ++j) term(own.pair(yc + j * Dm), j);
+    carry();
     double* o = part + (sb.p * kc.n + i) * 3;
     o[0] = ps;
     o[1] = pq;
