@@ -291,11 +291,12 @@ struct Resolved {
     double dscale = 1.0;   // 1 / (range scale)^2 of the split FP16 operands, else 1
 };
 
-// Slot of the small-scalar area holding the range scale of the split FP16 operands (prep ->
-// resolve) and of the digit planes; the next slot holds the running maximum its reduction folds into.
-constexpr int SPLIT_SCALE_SLOT = 40;
-// The refined cost maximum (8 bytes), its number of candidate tiles and the flag of the digit planes.
+// Slots (doubles) of the small-scalar area behind the certificate's sums; see Scalars.
+constexpr int SCALARS_SLOT = 40;
+constexpr int SPLIT_SCALE_SLOT = SCALARS_SLOT;   // split FP16 operands and digit planes
 constexpr int REFINE_SLOT = 42;
+constexpr int TOP_SLOT = 44;
+constexpr int MARGINALS_SLOT = 45;
 
 lamp_status check_problem(const lamp_problem* p) {
     if (!p) return fail(LAMP_EINVAL, "problem is NULL");
@@ -357,14 +358,12 @@ lamp_status check_ws(const lamp_problem* p, void* ws, size_t ws_bytes, int prec 
 
 // Marginals must be strictly positive and sum to 1 (r in Delta^n, c in Delta^m with full support).
 // Checked on the device, ordered on the call's stream (the marginals may have been written by
-// earlier work on it); `dev6` is 6 doubles of device scratch for the two results.
-lamp_status check_marginals(const lamp_problem* p, double* dev6, hipStream_t st) {
-    hipLaunchKernelGGL(marginal_stats, dim3(1), dim3(1024), 0, st, p->r, p->n, dev6);
-    hipLaunchKernelGGL(marginal_stats, dim3(1), dim3(1024), 0, st, p->c, p->m, dev6 + 3);
-    HIPCHK(hipGetLastError());
-    double h[6];
-    HIPCHK(hipMemcpyAsync(h, dev6, sizeof(h), hipMemcpyDeviceToHost, st));
-    HIPCHK(hipStreamSynchronize(st));
+// earlier work on it); `dev6` receives the two results, `h` is a host copy of them.
+void launch_marginals(const lamp_problem* p, double* dev6, hipStream_t st) {
+    hipLaunchKernelGGL(marginal_stats, dim3(2), dim3(1024), 0, st, p->r, p->n, p->c, p->m, dev6);
+}
+
+lamp_status judge_marginals(const double* h) {
     const char* names[2] = {"r", "c"};
     for (int q = 0; q < 2; ++q) {
         const double* v = h + 3 * q;
@@ -374,6 +373,23 @@ lamp_status check_marginals(const lamp_problem* p, double* dev6, hipStream_t st)
     }
     return LAMP_OK;
 }
+
+// Small scalars of a call that the host reads back, all at once (SCALARS_SLOT).
+struct Scalars {
+    double range, range_bits;   // the range scale and its running maximum (SPLIT_SCALE_SLOT)
+    double refined;             // the refined cost maximum, its number of candidate tiles and the
+    int tiles, bad;             // flag of the digit planes (REFINE_SLOT)
+    double top;                 // the cost maximum (TOP_SLOT)
+    double marginals[6];        // marginal_stats
+};
+
+lamp_status read_scalars(const Layout& L, void* ws, hipStream_t st, Scalars* out) {
+    HIPCHK(hipMemcpyAsync(out, at<double>(ws, L.small) + SCALARS_SLOT, sizeof(Scalars), hipMemcpyDeviceToHost, st));
+    HIPCHK(hipStreamSynchronize(st));
+    return LAMP_OK;
+}
+
+double* marginals_ptr(const Layout& L, void* ws) { return at<double>(ws, L.small) + MARGINALS_SLOT; }
 
 dim3 grid1(int64_t cnt) { return dim3((unsigned)cdiv(cnt, BLOCK)); }
 
@@ -397,20 +413,28 @@ void launch_range_scale(const Layout& L, int64_t n, int64_t m, int d, void* ws, 
     hipLaunchKernelGGL(split_scale_final, dim3(1), dim3(1), 0, st, (const unsigned long long*)mbits, scale);
 }
 
-lamp_status prep_L(const lamp_problem* p, const Layout& L, void* ws, hipStream_t st) {
+// Whether a call computes the cost maximum (the scale or ||C||_inf is not given).
+bool needs_max(const lamp_problem* p) { return !(p->cost_scale > 0.0) || !(p->cost_norm > 0.0); }
+
+unsigned long long* top_ptr(const Layout& L, void* ws) {
+    return reinterpret_cast<unsigned long long*>(at<double>(ws, L.small) + TOP_SLOT);
+}
+
+// with_max: the cost maximum follows; its result goes to *top (its own slot if null).
+lamp_status prep_L(const lamp_problem* p, const Layout& L, void* ws, hipStream_t st, bool with_max,
+                   unsigned long long* top = nullptr) {
     const int prec = L.prec;
+    MaxStart mx{nullptr, nullptr};
+    if (with_max) mx = MaxStart{at<double>(ws, L.scratch), top ? top : top_ptr(L, ws)};
     if (L.cost) {
-        hipLaunchKernelGGL(prep_cost_codes, grid1(p->n), dim3(BLOCK), 0, st, p->n, 0, at<double>(ws, L.xc),
-                           at<double>(ws, L.xn2));
-        hipLaunchKernelGGL(prep_cost_codes, grid1(p->m), dim3(BLOCK), 0, st, p->m, 1, at<double>(ws, L.yc),
-                           at<double>(ws, L.yn2));
+        hipLaunchKernelGGL(prep_cost_codes, grid1(p->n + p->m), dim3(BLOCK), 0, st, p->n, p->m, at<double>(ws, L.xc),
+                           at<double>(ws, L.xn2), at<double>(ws, L.yc), at<double>(ws, L.yn2), mx);
         HIPCHK(hipGetLastError());
         return LAMP_OK;
     }
-    hipLaunchKernelGGL(prep_points, grid1(p->n), dim3(BLOCK), 0, st, p->x, p->n, p->d, p->x, p->y,
-                       at<double>(ws, L.xc), at<double>(ws, L.xn2), at<float>(ws, L.xcf), p->metric);
-    hipLaunchKernelGGL(prep_points, grid1(p->m), dim3(BLOCK), 0, st, p->y, p->m, p->d, p->x, p->y,
-                       at<double>(ws, L.yc), at<double>(ws, L.yn2), at<float>(ws, L.ycf), p->metric);
+    hipLaunchKernelGGL(prep_points, grid1(p->n + p->m), dim3(BLOCK), 0, st, p->x, p->n, p->y, p->m, p->d,
+                       at<double>(ws, L.xc), at<double>(ws, L.xn2), at<float>(ws, L.xcf), at<double>(ws, L.yc),
+                       at<double>(ws, L.yn2), at<float>(ws, L.ycf), p->metric, mx);
     if (L.use64) {
         hipLaunchKernelGGL(prep_operands64, grid1(L.n_pad64 * L.KP64), dim3(BLOCK), 0, st, at<double>(ws, L.xc),
                            p->n, p->d, L.KP64, L.n_pad64, at<double>(ws, L.xop64));
@@ -443,10 +467,6 @@ lamp_status prep_L(const lamp_problem* p, const Layout& L, void* ws, hipStream_t
     }
     HIPCHK(hipGetLastError());
     return LAMP_OK;
-}
-
-lamp_status prep(const lamp_problem* p, void* ws, hipStream_t st, int prec = LAMP_FP32) {
-    return prep_L(p, layout(p->n, p->m, p->d, prec, TARGET_BLOCKS, p->metric), ws, st);
 }
 
 // f(tag) with tag a null pointer to the element type of an explicit cost matrix.
@@ -535,7 +555,7 @@ void row_extreme64(const Layout& L, Consts kc, void* ws, const double* a, double
                        L.m_pad64 / 16, n_waves);
 }
 
-// Bits of the refined maximum, candidate count, digit flag (REFINE_SLOT).
+// The part of Scalars at REFINE_SLOT.
 struct Refined {
     double max;
     int tiles, bad;
@@ -856,76 +876,76 @@ void launch_cost(const Layout& L, Consts kc, int d, void* ws, double cA, const d
     hipLaunchKernelGGL(reduce_sums, dim3(1), dim3(1024), 0, st, (const double*)rows, kc.n, kc.n, 1, out);
 }
 
-__global__ void fill_scaled(int64_t cnt, double f, const double* __restrict__ in, double* __restrict__ out) {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < cnt) out[i] = f * in[i];
-}
-
-lamp_status max_sqdist_L(const lamp_problem* p, const Layout& L, void* ws, hipStream_t st, double* out_host) {
+Consts max_consts(const lamp_problem* p) {
     Consts kc{};
     kc.n = p->n;
     kc.m = p->m;
     kc.metric = p->metric;
     kc.cost = p->metric == LAMP_EXPLICIT ? p->cost : nullptr;
     kc.cost_type = p->metric == LAMP_EXPLICIT ? p->cost_type : COST_F32;
+    return kc;
+}
+
+// The cost maximum over every pair into *top (prepared by prep_L with_max).
+void launch_max(const lamp_problem* p, const Layout& L, void* ws, unsigned long long* top, hipStream_t st) {
+    const Consts kc = max_consts(p);
+    launch_row_extreme(L, kc, p->d, ws, at<double>(ws, L.scratch), +1.0, st);
+    hipLaunchKernelGGL(row_extreme_max, grid1(p->n), dim3(BLOCK), 0, st, kc, (const double*)at<double>(ws, L.rpart),
+                       extreme_parts(L), (const double*)at<double>(ws, L.xn2), (double*)nullptr, top);
+}
+
+// The same with the coarse products first: the few row tiles near the coarse maximum are evaluated
+// in FP64 into Scalars::refined; with many of them (points on a sphere, one-hot features) or a
+// coordinate that is not finite, the host runs launch_max.
+void launch_max_coarse(const lamp_problem* p, const Layout& L, void* ws, hipStream_t st) {
+    const Consts kc = max_consts(p);
     double* a = at<double>(ws, L.scratch);
     double* rowmax = a + std::max(p->n, p->m);
-    double* top = at<double>(ws, L.small);
+    int* list = reinterpret_cast<int*>(rowmax + std::max(p->n, p->m));
+    double* small = at<double>(ws, L.small);
     const double* xn2 = at<double>(ws, L.xn2);
-    hipLaunchKernelGGL(fill_scaled, grid1(p->m), dim3(BLOCK), 0, st, p->m, -0.5, at<double>(ws, L.yn2), a);
-    auto merge = [&] {
-        hipLaunchKernelGGL(row_extreme_merge, grid1(p->n), dim3(BLOCK), 0, st, kc, at<double>(ws, L.rpart),
-                           extreme_parts(L), xn2, 1, rowmax);
-        hipLaunchKernelGGL(reduce_max, dim3(1), dim3(1024), 0, st, rowmax, p->n, top);
+    auto* ref = reinterpret_cast<Refined*>(small + REFINE_SLOT);
+    launch_digits(L, kc, p->d, ws, st);
+    launch_row_extreme_coarse<false>(L, kc, p->d, ws, a, +1.0, nullptr, st);
+    hipLaunchKernelGGL(row_extreme_max, grid1(p->n), dim3(BLOCK), 0, st, kc, (const double*)at<double>(ws, L.rpart),
+                       extreme_parts(L), xn2, rowmax, top_ptr(L, ws));
+    hipLaunchKernelGGL(select_max_tiles, grid1(p->n), dim3(BLOCK), 0, st, p->n, p->d, (const double*)rowmax,
+                       (const double*)(small + TOP_SLOT), (const double*)(small + SPLIT_SCALE_SLOT), list, &ref->tiles);
+    auto refine = [&](auto kp) {
+        hipLaunchKernelGGL((refine_max<decltype(kp)::value>), dim3(COARSE_MAX_TILES * COARSE_MAX_SPLITS), dim3(BLOCK), 0,
+                           st, kc, (const double*)at<double>(ws, L.xop64), (const double*)at<double>(ws, L.yop64), xn2,
+                           (const double*)a, (const int*)list, (const int*)&ref->tiles, L.m_pad64 / 16,
+                           reinterpret_cast<unsigned long long*>(ref));
     };
+    if (L.KP64 == 32) refine(IC<32>{});
+    else if (L.KP64 == 64) refine(IC<64>{});
+    else refine(IC<128>{});
+}
+
+// Runs the cost maximum and reads the call's scalars back; sc->top is the maximum.
+lamp_status max_cost(const lamp_problem* p, const Layout& L, void* ws, hipStream_t st, Scalars* sc) {
+    lamp_status e;
     if (L.coarse) {
-        // the few row tiles near the coarse maximum are evaluated in FP64; with many of them
-        // (points on a sphere, one-hot features) or a coordinate that is not finite, every pair is
-        auto* ref = reinterpret_cast<Refined*>(top + REFINE_SLOT);
-        int* list = reinterpret_cast<int*>(rowmax + std::max(p->n, p->m));
-        const double* range = top + SPLIT_SCALE_SLOT;
-        launch_digits(L, kc, p->d, ws, st);
-        launch_row_extreme_coarse<false>(L, kc, p->d, ws, a, +1.0, nullptr, st);
-        merge();
-        hipLaunchKernelGGL(select_max_tiles, grid1(p->n), dim3(BLOCK), 0, st, p->n, p->d, (const double*)rowmax,
-                           (const double*)top, range, list, &ref->tiles);
-        auto refine = [&](auto kp) {
-            hipLaunchKernelGGL((refine_max<decltype(kp)::value>), dim3(COARSE_MAX_TILES * COARSE_MAX_SPLITS),
-                               dim3(BLOCK), 0, st, kc, (const double*)at<double>(ws, L.xop64),
-                               (const double*)at<double>(ws, L.yop64), xn2, (const double*)a, (const int*)list,
-                               (const int*)&ref->tiles, L.m_pad64 / 16, reinterpret_cast<unsigned long long*>(ref));
-        };
-        if (L.KP64 == 32) refine(IC<32>{});
-        else if (L.KP64 == 64) refine(IC<64>{});
-        else refine(IC<128>{});
+        launch_max_coarse(p, L, ws, st);
         HIPCHK(hipGetLastError());
-        Refined got;
-        HIPCHK(hipMemcpyAsync(&got, ref, sizeof(got), hipMemcpyDeviceToHost, st));
-        HIPCHK(hipStreamSynchronize(st));
-        if (!got.bad && got.tiles <= COARSE_MAX_TILES) {
-            *out_host = got.max;
+        if ((e = read_scalars(L, ws, st, sc)) != LAMP_OK) return e;
+        if (!sc->bad && sc->tiles <= COARSE_MAX_TILES) {
+            sc->top = sc->refined;
             return LAMP_OK;
         }
+        hipLaunchKernelGGL(split_scale_clear, dim3(1), dim3(1), 0, st, top_ptr(L, ws));
     }
-    launch_row_extreme(L, kc, p->d, ws, a, +1.0, st);
-    merge();
+    launch_max(p, L, ws, top_ptr(L, ws), st);
     HIPCHK(hipGetLastError());
-    HIPCHK(hipMemcpyAsync(out_host, top, sizeof(double), hipMemcpyDeviceToHost, st));
-    HIPCHK(hipStreamSynchronize(st));
-    return LAMP_OK;
+    return read_scalars(L, ws, st, sc);
 }
 
-lamp_status max_sqdist(const lamp_problem* p, void* ws, hipStream_t st, double* out_host, int prec) {
-    return max_sqdist_L(p, layout(p->n, p->m, p->d, prec, TARGET_BLOCKS, p->metric), ws, st, out_host);
-}
-
-lamp_status resolve_L(const lamp_problem* p, const lamp_params* q, const Layout& L, void* ws, hipStream_t st,
-                      Resolved* R) {
+// The call's constants from the problem, the parameters and, where they are needed, the cost maximum
+// (md) and the range scale of the split FP16 operands.
+lamp_status resolve(const lamp_problem* p, const lamp_params* q, const Layout& L, double md, double range,
+                    Resolved* R) {
     double s = p->cost_scale, cn = p->cost_norm;
-    if (!(s > 0.0) || !(cn > 0.0)) {
-        double md = 0.0;
-        lamp_status e = max_sqdist_L(p, L, ws, st, &md);
-        if (e != LAMP_OK) return e;
+    if (needs_max(p)) {
         if (!(md > 0.0)) return fail(LAMP_EDOMAIN, "all pairwise distances are zero");
         if (!(s > 0.0)) {
             s = 1.0 / md;
@@ -944,19 +964,8 @@ lamp_status resolve_L(const lamp_problem* p, const lamp_params* q, const Layout&
     R->kappa = 2.0 * R->tau2 * cn;
     R->clipb = std::tanh(R->beta / 2.0);
     if (R->tau1 * q->eta > 1.0) return fail(LAMP_EINVAL, "tau1 * eta = %g > 1", R->tau1 * q->eta);
-    R->dscale = 1.0;
-    if (L.prec == LAMP_FP16X3_MFMA) {
-        double sc = 0.0;
-        HIPCHK(hipMemcpyAsync(&sc, at<double>(ws, L.small) + SPLIT_SCALE_SLOT, sizeof(double), hipMemcpyDeviceToHost,
-                              st));
-        HIPCHK(hipStreamSynchronize(st));
-        R->dscale = 1.0 / (sc * sc);
-    }
+    R->dscale = L.prec == LAMP_FP16X3_MFMA ? 1.0 / (range * range) : 1.0;
     return LAMP_OK;
-}
-
-lamp_status resolve(const lamp_problem* p, const lamp_params* q, void* ws, hipStream_t st, Resolved* R) {
-    return resolve_L(p, q, layout(p->n, p->m, p->d, q->precision, TARGET_BLOCKS, p->metric), ws, st, R);
 }
 
 Consts make_consts(const lamp_problem* p, const Resolved& R) {
@@ -1038,21 +1047,20 @@ void launch_extreme_mfma(const Layout& L, Consts kc, void* ws, const Ctrl* ctrl,
 // Offsets for the first row sweep of a call: h_i = min_j(-g^B_j/cfac^B - x~.y~), exact in
 // FP64 for the FP64-argument form; for the matrix-core forms from their own operand copies
 // and FP32 arithmetic (an offset only has to keep the sums in range).
+// The FP64-argument form's a_j = -g^B_j / cfac^B come from col_table_init (in the scratch area).
 void launch_offsets(const Layout& L, Consts kc, int d, void* ws, hipStream_t st, const Ctrl* ctrl = nullptr,
                     const Sched* sched = nullptr) {
     if (is_mfma(L.prec)) {
         launch_extreme_mfma(L, kc, ws, ctrl ? ctrl : at<Ctrl>(ws, L.ctrl), sched ? sched : at<Sched>(ws, L.sched),
                             st);
         hipLaunchKernelGGL(row_extreme_merge, grid1(kc.n), dim3(BLOCK), 0, st, kc, at<double>(ws, L.rpart),
-                           (int)L.P_rm, (const double*)nullptr, 0, at<double>(ws, L.H));
+                           (int)L.P_rm, at<double>(ws, L.H));
         return;
     }
     double* a = at<double>(ws, L.scratch);
-    hipLaunchKernelGGL(offset_coeffs, grid1(kc.m), dim3(BLOCK), 0, st, ctrl ? ctrl : at<Ctrl>(ws, L.ctrl),
-                       sched ? sched : at<Sched>(ws, L.sched), kc, at<double2>(ws, L.gtab), a);
     auto merge = [&](double* out) {
         hipLaunchKernelGGL(row_extreme_merge, grid1(kc.n), dim3(BLOCK), 0, st, kc, at<double>(ws, L.rpart),
-                           extreme_parts(L), (const double*)nullptr, 0, out);
+                           extreme_parts(L), out);
     };
     if (L.coarse) {
         double* coarse = a + std::max(kc.n, kc.m);
@@ -1066,14 +1074,14 @@ void launch_offsets(const Layout& L, Consts kc, int d, void* ws, hipStream_t st,
     merge(at<double>(ws, L.H));
 }
 
-// The iteration loop of a solve call on its stream.  GRAPH_ITERS iterations are captured once
-// into a graph that is replayed (every kernel reads t, the schedule and the stop flag from
-// device memory); queue() enqueues exactly `count` iterations: whole replays, the remainder
-// launched directly.  Capturing costs the host 8 us per iteration (0.49 ms for 64) before the
-// first one can start, and an iteration queued past the end still costs its launches, so the
-// graph is short and nothing is queued past the call's last iteration: 4096 x 4096 points,
-// 16 iterations: 3.4 -> 0.98 ms.  Fewer than 2 GRAPH_ITERS iterations are launched directly.
-// The graph is destroyed on every return path.
+// The iteration loop of a solve call on its stream.  queue() enqueues exactly `count` iterations.
+// GRAPH_ITERS iterations are captured once into a graph that is replayed (every kernel reads t, the
+// schedule and the stop flag from device memory); the remainder is launched directly.  Capturing
+// costs the host about 100 us, and an iteration queued past the end still costs its launches, so
+// the graph is short, nothing is queued past the call's last iteration, and the first GRAPH_ITERS
+// iterations are launched directly: the GPU runs them while the host captures.  Fewer than
+// 3 GRAPH_ITERS iterations are all launched directly (12 us of host time each, below the GPU's 17 and
+// more).  The graph is destroyed on every return path.
 constexpr int GRAPH_ITERS = 8;
 
 struct IterLoop {
@@ -1082,7 +1090,9 @@ struct IterLoop {
 
     template <typename F>
     lamp_status queue(int64_t count, hipStream_t st, F&& iteration) {
-        if (!exec && count >= 2 * GRAPH_ITERS) {
+        if (!exec && count >= 3 * GRAPH_ITERS) {
+            for (int k = 0; k < GRAPH_ITERS; ++k) iteration();
+            count -= GRAPH_ITERS;
             HIPCHK(hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal));
             for (int k = 0; k < GRAPH_ITERS; ++k) iteration();
             const hipError_t ce = hipStreamEndCapture(st, &graph);
@@ -1100,6 +1110,59 @@ struct IterLoop {
         if (exec) (void)hipGraphExecDestroy(exec);
         if (graph) (void)hipGraphDestroy(graph);
     }
+};
+
+// The stream of a solve call.  Capture needs one that is not the default stream: a caller that
+// passes none gets a private one, from a small pool per device (creating and destroying a stream
+// costs 80 us a call).  A stream is in one call's hands at a time and idle when it goes back.
+class CallStream {
+public:
+    hipStream_t st = nullptr;
+
+    lamp_status open(hipStream_t caller) {
+        st = caller;
+        if (caller) return LAMP_OK;
+        HIPCHK(hipStreamSynchronize(nullptr));
+        HIPCHK(hipGetDevice(&dev_));
+        {
+            std::lock_guard<std::mutex> lk(mu());
+            auto& idle = pool()[dev_];
+            if (!idle.empty()) {
+                own_ = idle.back();
+                idle.pop_back();
+            }
+        }
+        if (!own_) HIPCHK(hipStreamCreateWithFlags(&own_, hipStreamNonBlocking));
+        st = own_;
+        return LAMP_OK;
+    }
+
+    ~CallStream() {
+        if (!own_) return;
+        if (hipStreamSynchronize(own_) == hipSuccess) {
+            std::lock_guard<std::mutex> lk(mu());
+            auto& idle = pool()[dev_];
+            if (idle.size() < MAX_IDLE) {
+                idle.push_back(own_);
+                return;
+            }
+        }
+        (void)hipStreamDestroy(own_);
+    }
+
+private:
+    static constexpr size_t MAX_IDLE = 4;
+    static std::mutex& mu() {
+        static std::mutex m;
+        return m;
+    }
+    // never destroyed: the runtime may be gone before static objects are
+    static std::map<int, std::vector<hipStream_t>>& pool() {
+        static auto* p = new std::map<int, std::vector<hipStream_t>>;
+        return *p;
+    }
+    hipStream_t own_ = nullptr;
+    int dev_ = 0;
 };
 
 struct IterArgs {
@@ -1225,37 +1288,60 @@ void launch_iteration(const lamp_problem* p, const Layout& L, Consts kc, void* w
     if (!ia.fused) launch_finish(L, kc, ws, ia, st);
 }
 
-lamp_status upload_ctrl(void* ws, const Layout& L, int64_t t, int64_t t_end, int64_t t_base, double tol,
-                        hipStream_t st, Ctrl* host, double dt_acc = 0.0) {
-    host->dt_acc = dt_acc;
-    host->dt_cost = 0.0;
-    host->t = t;
-    host->t_row = t;
-    host->done_seen = 0;
-    host->fallbacks_row = 0;
-    host->t_end = t_end;
-    host->t_base = t_base;
-    host->t_done = -1;
-    host->done = 0;
-    host->err = 0;
-    host->fallbacks = 0;
-    host->tol = tol;
-    host->res_last = -1.0;
-    HIPCHK(hipMemcpyAsync(at<Ctrl>(ws, L.ctrl), host, sizeof(Ctrl), hipMemcpyHostToDevice, st));
-    return LAMP_OK;
+Ctrl start_ctrl(int64_t t, int64_t t_end, double tol, double dt_acc) {
+    Ctrl c{};
+    c.t = c.t_row = c.t_base = t;
+    c.t_end = t_end;
+    c.t_done = -1;
+    c.tol = tol;
+    c.res_last = -1.0;
+    c.dt_acc = dt_acc;
+    return c;
 }
 
+// Opens a call of one iteration's schedule: the control block and the entry travel by value.
+// marginals: checked on the device before the first iteration (nullable: checked already).
+void launch_open(const Layout& L, Consts kc, void* ws, const double* nu, const double* theta,
+                 const Ctrl& ctrl, const Sched& sched, const double* marginals, hipStream_t st) {
+    CallInit init{};
+    init.ctrl = ctrl;
+    init.sched = sched;
+    init.marginals = marginals;
+    init.write = 1;
+    hipLaunchKernelGGL(col_table_init, grid1(kc.m), dim3(BLOCK), 0, st, at<Ctrl>(ws, L.ctrl), at<Sched>(ws, L.sched), kc,
+                       at<double>(ws, L.yn2), nu, theta, at<double2>(ws, L.gtab), gtabf_ptr(L, ws), L.m_pad,
+                       is_mfma(L.prec) ? (double*)nullptr : at<double>(ws, L.scratch), init);
+}
+
+// Checks the arguments, prepares the points and resolves the constants.  The marginals are judged
+// here if the host has to wait for the device anyway or `defer` is null; else *defer points to their
+// statistics, which the call's first kernel judges on the device (a wait less).
 lamp_status common_setup(const lamp_problem* p, const lamp_params* q, void* ws, size_t ws_bytes,
-                         hipStream_t st, Resolved* R) {
+                         hipStream_t st, Resolved* R, const double** defer = nullptr) {
     lamp_status e;
     if ((e = check_problem(p)) != LAMP_OK) return e;
     if ((e = check_params(q)) != LAMP_OK) return e;
     if ((e = check_ws(p, ws, ws_bytes, q->precision)) != LAMP_OK) return e;
-    if ((e = check_marginals(p, at<double>(ws, layout(p->n, p->m, p->d, q->precision, TARGET_BLOCKS, p->metric).small),
-                             st)) != LAMP_OK)
-        return e;
-    if ((e = prep(p, ws, st, q->precision)) != LAMP_OK) return e;
-    return resolve(p, q, ws, st, R);
+    const Layout L = layout(p->n, p->m, p->d, q->precision, TARGET_BLOCKS, p->metric);
+    if (defer) *defer = nullptr;
+    launch_marginals(p, marginals_ptr(L, ws), st);
+    const bool mx = needs_max(p);
+    if ((e = prep_L(p, L, ws, st, mx)) != LAMP_OK) return e;
+    Scalars sc{};
+    if (mx || !defer || L.prec == LAMP_FP16X3_MFMA) {
+        if ((e = mx ? max_cost(p, L, ws, st, &sc) : read_scalars(L, ws, st, &sc)) != LAMP_OK) return e;
+        if ((e = judge_marginals(sc.marginals)) != LAMP_OK) return e;
+    } else {
+        *defer = marginals_ptr(L, ws);
+    }
+    return resolve(p, q, L, sc.top, sc.range, R);
+}
+
+// A call stopped by its marginals (err bit 1): their statistics, judged.
+lamp_status stopped_by_marginals(const Layout& L, void* ws, hipStream_t st) {
+    Scalars sc;
+    lamp_status e = read_scalars(L, ws, st, &sc);
+    return e != LAMP_OK ? e : judge_marginals(sc.marginals);
 }
 
 lamp_status check_state(const lamp_state* s) {
@@ -1272,16 +1358,10 @@ lamp_status state_normalisers(const lamp_problem* p, const lamp_params* q, const
     Layout L = layout(p->n, p->m, p->d, q->precision, TARGET_BLOCKS, p->metric);
     L.prec = LAMP_FP32;
     const Consts kc = make_consts(p, R);
-    Ctrl hc;
-    lamp_status e = upload_ctrl(ws, L, s->t, s->t + 1, s->t, 0.0, st, &hc);
-    if (e != LAMP_OK) return e;
     Sched sc{};
     sc.lamA = sc.lamB = sc.lamC = s->inv_eta;
     sc.w = sc.w2 = 0.0;   // nubar = nu: both halves evaluate p^{eta_t}(nu^t)
-    HIPCHK(hipMemcpyAsync(at<Sched>(ws, L.sched), &sc, sizeof(Sched), hipMemcpyHostToDevice, st));
-    HIPCHK(hipStreamSynchronize(st));   // the uploads read host locals of this frame
-    hipLaunchKernelGGL(col_table_init, grid1(p->m), dim3(BLOCK), 0, st, at<Ctrl>(ws, L.ctrl),
-                       at<Sched>(ws, L.sched), kc, at<double>(ws, L.yn2), s->nu, s->theta, at<double2>(ws, L.gtab), (float2*)nullptr, L.m_pad);
+    launch_open(L, kc, ws, s->nu, s->theta, start_ctrl(s->t, s->t + 1, 0.0, 0.0), sc, nullptr, st);
     launch_offsets(L, kc, p->d, ws, st);
     launch_row_sweep(L, kc, p->d, ws, st);
     hipLaunchKernelGGL(row_finish, grid1(kc.n), dim3(BLOCK), 0, st, at<Ctrl>(ws, L.ctrl), at<Sched>(ws, L.sched),
@@ -1530,10 +1610,35 @@ lamp_status batch_setup(const lamp_problem* probs, int count, const lamp_params*
     run->nu1.resize(count);
     run->th1.resize(count);
     lamp_status e;
+    // every problem's cost maximum before one wait (the schedule table's room holds the results)
+    const int batch_max = (int)std::min<int64_t>(count, TAB * (int64_t)(sizeof(Sched) / sizeof(double)));
+    std::vector<double> top(count, 0.0);
+    auto* tops = at<unsigned long long>(ws, B.sched);
+    for (int p0 = 0; p0 < count; p0 += batch_max) {
+        const int p1 = std::min(count, p0 + batch_max);
+        for (int p = p0; p < p1; ++p) {
+            void* w = sub_ws(ws, B, p);
+            const bool mx = needs_max(&probs[p]);
+            const bool alone = B.L[p].coarse;   // may need a second pass: waits for itself
+            if ((e = prep_L(&probs[p], B.L[p], w, st, mx, alone ? nullptr : tops + (p - p0))) != LAMP_OK) return e;
+            if (!mx) continue;
+            if (alone) {
+                Scalars sc;
+                if ((e = max_cost(&probs[p], B.L[p], w, st, &sc)) != LAMP_OK) return e;
+                top[p] = sc.top;
+            } else {
+                launch_max(&probs[p], B.L[p], w, tops + (p - p0), st);
+            }
+        }
+        HIPCHK(hipGetLastError());
+        std::vector<double> got(p1 - p0);
+        HIPCHK(hipMemcpyAsync(got.data(), tops, sizeof(double) * (p1 - p0), hipMemcpyDeviceToHost, st));
+        HIPCHK(hipStreamSynchronize(st));
+        for (int p = p0; p < p1; ++p)
+            if (!B.L[p].coarse) top[p] = got[p - p0];
+    }
     for (int p = 0; p < count; ++p) {
-        void* w = sub_ws(ws, B, p);
-        if ((e = prep_L(&probs[p], B.L[p], w, st)) != LAMP_OK) return e;
-        if ((e = resolve_L(&probs[p], q, B.L[p], w, st, &run->R[p])) != LAMP_OK) return e;
+        if ((e = resolve(&probs[p], q, B.L[p], top[p], 0.0, &run->R[p])) != LAMP_OK) return e;
         if (run->R[p].tau1 != run->R[0].tau1)
             return fail(LAMP_EINVAL, "batched problems need a common ||C||_inf (problem %d differs)", p);
     }
@@ -1599,7 +1704,8 @@ lamp_status batch_setup(const lamp_problem* probs, int count, const lamp_params*
         const ProbDesc& D = run->desc[p];
         // the per-problem set-up kernels read the batch control block and schedule
         hipLaunchKernelGGL(col_table_init, grid1(D.kc.m), dim3(BLOCK), 0, st, D.ctrl, at<Sched>(ws, B.sched), D.kc,
-                           D.yn2, states[p].nu, states[p].theta, D.gtab, (float2*)nullptr, (int64_t)0);
+                           D.yn2, states[p].nu, states[p].theta, D.gtab, (float2*)nullptr, (int64_t)0,
+                           at<double>(w, L.scratch), CallInit{});
         launch_offsets(L, D.kc, probs[p].d, w, st, D.ctrl, at<Sched>(ws, B.sched));
     }
     HIPCHK(hipGetLastError());
@@ -1683,15 +1789,13 @@ lamp_status step_impl(const lamp_problem* prob, const lamp_params* params, lamp_
     lamp_status e;
     if ((e = check_state(state)) != LAMP_OK) return e;
     Resolved R;
-    if ((e = common_setup(prob, params, ws, ws_bytes, st, &R)) != LAMP_OK) return e;
+    const double* marginals = nullptr;
+    if ((e = common_setup(prob, params, ws, ws_bytes, st, &R, &marginals)) != LAMP_OK) return e;
     const Layout L = layout(prob->n, prob->m, prob->d, params->precision, TARGET_BLOCKS, prob->metric);
     const Consts kc = make_consts(prob, R);
     const int64_t t = state->t;
     Sched tab[1];
     fill_sched(tab, 1, state->inv_eta, R.tau1, params->eta);
-    HIPCHK(hipMemcpyAsync(at<Sched>(ws, L.sched), tab, sizeof(Sched), hipMemcpyHostToDevice, st));
-    Ctrl hc;
-    if ((e = upload_ctrl(ws, L, t, t + 1, t, 0.0, st, &hc, state->dt_partial)) != LAMP_OK) return e;
     IterArgs ia{};
     ia.track_dt = params->track_dt != 0;
     ia.buf.nu[t & 1] = state->nu;
@@ -1703,15 +1807,18 @@ lamp_status step_impl(const lamp_problem* prob, const lamp_params* params, lamp_
         ia.log_za = trace->log_za;
         ia.log_zb = trace->log_zb;
     }
-    hipLaunchKernelGGL(col_table_init, grid1(kc.m), dim3(BLOCK), 0, st, at<Ctrl>(ws, L.ctrl), at<Sched>(ws, L.sched),
-                       kc, at<double>(ws, L.yn2), state->nu, state->theta, at<double2>(ws, L.gtab), gtabf_ptr(L, ws), L.m_pad);
+    launch_open(L, kc, ws, state->nu, state->theta, start_ctrl(t, t + 1, 0.0, state->dt_partial), tab[0], marginals,
+                st);
     launch_offsets(L, kc, prob->d, ws, st);
     launch_iteration(prob, L, kc, ws, ia, st);
+    hipLaunchKernelGGL(commit_state, grid1(kc.m), dim3(BLOCK), 0, st, (const Ctrl*)at<Ctrl>(ws, L.ctrl), kc.m,
+                       (const double*)at<double>(ws, L.nu1), (const double*)at<double>(ws, L.th1), state->nu,
+                       state->theta);
     HIPCHK(hipGetLastError());
-    HIPCHK(hipMemcpyAsync(state->nu, at<double>(ws, L.nu1), sizeof(double) * kc.m, hipMemcpyDeviceToDevice, st));
-    HIPCHK(hipMemcpyAsync(state->theta, at<double>(ws, L.th1), sizeof(double) * kc.m, hipMemcpyDeviceToDevice, st));
+    Ctrl hc;
     HIPCHK(hipMemcpyAsync(&hc, at<Ctrl>(ws, L.ctrl), sizeof(Ctrl), hipMemcpyDeviceToHost, st));
     HIPCHK(hipStreamSynchronize(st));
+    if (hc.err & 2) return stopped_by_marginals(L, ws, st);
     if (hc.err) return fail(LAMP_ENUMERIC, "non-finite value in the dual update at t = %lld", (long long)t);
     if (res_out) *res_out = hc.res_last;
     state->t = t + 1;
@@ -1768,9 +1875,11 @@ lamp_status lamp_cost_scale(const lamp_problem* prob, void* ws, size_t ws_bytes,
     lamp_status e;
     if ((e = check_problem(prob)) != LAMP_OK) return e;
     if ((e = check_ws(prob, ws, ws_bytes)) != LAMP_OK) return e;
-    if ((e = prep(prob, ws, st)) != LAMP_OK) return e;
-    double md = 0.0;
-    if ((e = max_sqdist(prob, ws, st, &md, LAMP_FP32)) != LAMP_OK) return e;
+    const Layout L = layout(prob->n, prob->m, prob->d, LAMP_FP32, TARGET_BLOCKS, prob->metric);
+    Scalars sc;
+    if ((e = prep_L(prob, L, ws, st, true)) != LAMP_OK) return e;
+    if ((e = max_cost(prob, L, ws, st, &sc)) != LAMP_OK) return e;
+    const double md = sc.top;
     if (!(md > 0.0)) return fail(LAMP_EDOMAIN, "all pairwise distances are zero");
     if (s_out) *s_out = 1.0 / md;
     if (max_sqdist_out) *max_sqdist_out = md;
@@ -1808,24 +1917,12 @@ lamp_status lamp_solve(const lamp_problem* prob, const lamp_params* params, lamp
     lamp_status e;
     if ((e = check_state(state)) != LAMP_OK) return e;
     // graph capture needs a non-default stream: use a private one when given NULL
-    hipStream_t st = (hipStream_t)stream;
-    hipStream_t own = nullptr;
-    if (!st) {
-        HIPCHK(hipStreamSynchronize(nullptr));
-        HIPCHK(hipStreamCreateWithFlags(&own, hipStreamNonBlocking));
-        st = own;
-    }
-    struct StreamGuard {
-        hipStream_t s;
-        ~StreamGuard() {
-            if (s) {
-                (void)hipStreamSynchronize(s);
-                (void)hipStreamDestroy(s);
-            }
-        }
-    } guard{own};
+    CallStream call;
+    if ((e = call.open((hipStream_t)stream)) != LAMP_OK) return e;
+    hipStream_t st = call.st;
     Resolved R;
-    if ((e = common_setup(prob, params, ws, ws_bytes, st, &R)) != LAMP_OK) return e;
+    const double* marginals = nullptr;
+    if ((e = common_setup(prob, params, ws, ws_bytes, st, &R, &marginals)) != LAMP_OK) return e;
     const Layout L = layout(prob->n, prob->m, prob->d, params->precision, TARGET_BLOCKS, prob->metric);
     const Consts kc = make_consts(prob, R);
     const int64_t t0 = state->t;
@@ -1842,17 +1939,23 @@ lamp_status lamp_solve(const lamp_problem* prob, const lamp_params* params, lamp
     ia.buf.nu[(t0 + 1) & 1] = at<double>(ws, L.nu1);
     ia.buf.theta[(t0 + 1) & 1] = at<double>(ws, L.th1);
 
-    std::vector<Sched> tab(TAB);
+    // the control block and the schedule entries this call can use, which lie side by side
     double lam_epoch = state->inv_eta;   // lam at t_base of the current epoch
     int64_t t_base = t0;
-    double lam_next_epoch = fill_sched(tab.data(), TAB, lam_epoch, R.tau1, params->eta);
-    HIPCHK(hipMemcpyAsync(at<Sched>(ws, L.sched), tab.data(), sizeof(Sched) * TAB, hipMemcpyHostToDevice, st));
-    Ctrl hc;
     int64_t t_end = std::min(t_stop, t_base + TAB);
-    if ((e = upload_ctrl(ws, L, t0, t_end, t_base, params->tol, st, &hc, state->dt_partial)) != LAMP_OK) return e;
-
-    hipLaunchKernelGGL(col_table_init, grid1(kc.m), dim3(BLOCK), 0, st, at<Ctrl>(ws, L.ctrl), at<Sched>(ws, L.sched),
-                       kc, at<double>(ws, L.yn2), state->nu, state->theta, at<double2>(ws, L.gtab), gtabf_ptr(L, ws), L.m_pad);
+    static_assert(sizeof(Ctrl) <= 256, "the control block takes one 256-byte slot");
+    std::vector<char> open(256 + sizeof(Sched) * TAB);
+    Sched* tab = reinterpret_cast<Sched*>(open.data() + 256);
+    Ctrl hc = start_ctrl(t0, t_end, params->tol, state->dt_partial);
+    std::memcpy(open.data(), &hc, sizeof(Ctrl));
+    const int entries = (int)std::max<int64_t>(1, t_end - t_base);
+    double lam_next_epoch = fill_sched(tab, entries, lam_epoch, R.tau1, params->eta);
+    HIPCHK(hipMemcpyAsync(at<char>(ws, L.ctrl), open.data(), 256 + sizeof(Sched) * entries, hipMemcpyHostToDevice, st));
+    CallInit init{};
+    init.marginals = marginals;
+    hipLaunchKernelGGL(col_table_init, grid1(kc.m), dim3(BLOCK), 0, st, at<Ctrl>(ws, L.ctrl), at<Sched>(ws, L.sched), kc,
+                       at<double>(ws, L.yn2), state->nu, state->theta, at<double2>(ws, L.gtab), gtabf_ptr(L, ws), L.m_pad,
+                       is_mfma(L.prec) ? (double*)nullptr : at<double>(ws, L.scratch), init);
     launch_offsets(L, kc, prob->d, ws, st);
     HIPCHK(hipGetLastError());
 
@@ -1868,6 +1971,7 @@ lamp_status lamp_solve(const lamp_problem* prob, const lamp_params* params, lamp
         if (ia.fused) launch_finish(L, kc, ws, ia, st);
         HIPCHK(hipMemcpyAsync(&hc, at<Ctrl>(ws, L.ctrl), sizeof(Ctrl), hipMemcpyDeviceToHost, st));
         HIPCHK(hipStreamSynchronize(st));
+        if (hc.err & 2) return stopped_by_marginals(L, ws, st);
         if (hc.err) {
             result = fail(LAMP_ENUMERIC, "non-finite value in the dual update at t = %lld", (long long)hc.t_done);
             t_cur = hc.t_done;
@@ -1887,20 +1991,27 @@ lamp_status lamp_solve(const lamp_problem* prob, const lamp_params* params, lamp
             // new schedule epoch
             t_base = t_cur;
             lam_epoch = lam_next_epoch;
-            lam_next_epoch = fill_sched(tab.data(), TAB, lam_epoch, R.tau1, params->eta);
-            HIPCHK(hipMemcpyAsync(at<Sched>(ws, L.sched), tab.data(), sizeof(Sched) * TAB, hipMemcpyHostToDevice, st));
+            lam_next_epoch = fill_sched(tab, TAB, lam_epoch, R.tau1, params->eta);
+            HIPCHK(hipMemcpyAsync(at<Sched>(ws, L.sched), tab, sizeof(Sched) * TAB, hipMemcpyHostToDevice, st));
             t_end = std::min(t_stop, t_base + TAB);
             hc.t_end = t_end;
             hc.t_base = t_base;
             HIPCHK(hipMemcpyAsync(at<Ctrl>(ws, L.ctrl), &hc, sizeof(Ctrl), hipMemcpyHostToDevice, st));
         }
     }
+    if (t_stop <= t0) {   // no iteration has waited for the device: the marginals are still to be judged
+        HIPCHK(hipMemcpyAsync(&hc, at<Ctrl>(ws, L.ctrl), sizeof(Ctrl), hipMemcpyDeviceToHost, st));
+        HIPCHK(hipStreamSynchronize(st));
+        if (hc.err & 2) return stopped_by_marginals(L, ws, st);
+    }
     // the iterate of t_cur lives in buffer t_cur & 1
     if (t_cur != t0 && (t_cur & 1) != (t0 & 1)) {
-        HIPCHK(hipMemcpyAsync(state->nu, at<double>(ws, L.nu1), sizeof(double) * kc.m, hipMemcpyDeviceToDevice, st));
-        HIPCHK(hipMemcpyAsync(state->theta, at<double>(ws, L.th1), sizeof(double) * kc.m, hipMemcpyDeviceToDevice, st));
+        hipLaunchKernelGGL(commit_state, grid1(kc.m), dim3(BLOCK), 0, st, (const Ctrl*)at<Ctrl>(ws, L.ctrl), kc.m,
+                           (const double*)at<double>(ws, L.nu1), (const double*)at<double>(ws, L.th1), state->nu,
+                           state->theta);
+        HIPCHK(hipGetLastError());
+        HIPCHK(hipStreamSynchronize(st));
     }
-    HIPCHK(hipStreamSynchronize(st));
     // lam at t_cur (continue the recursion from the epoch base)
     double lam = lam_epoch;
     for (int64_t k = t_base; k < t_cur; ++k) lam = next_lam(lam, R.tau1, params->eta);
@@ -2246,11 +2357,7 @@ lamp_status lamp_sweep_times(const lamp_problem* prob, const lamp_params* params
     const Consts kc = make_consts(prob, R);
     Sched tab[1];
     fill_sched(tab, 1, state->inv_eta, R.tau1, params->eta);
-    HIPCHK(hipMemcpyAsync(at<Sched>(ws, L.sched), tab, sizeof(Sched), hipMemcpyHostToDevice, st));
-    Ctrl hc;
-    if ((e = upload_ctrl(ws, L, state->t, state->t + 1, state->t, 0.0, st, &hc)) != LAMP_OK) return e;
-    hipLaunchKernelGGL(col_table_init, grid1(kc.m), dim3(BLOCK), 0, st, at<Ctrl>(ws, L.ctrl), at<Sched>(ws, L.sched),
-                       kc, at<double>(ws, L.yn2), state->nu, state->theta, at<double2>(ws, L.gtab), gtabf_ptr(L, ws), L.m_pad);
+    launch_open(L, kc, ws, state->nu, state->theta, start_ctrl(state->t, state->t + 1, 0.0, 0.0), tab[0], nullptr, st);
     launch_offsets(L, kc, prob->d, ws, st);
     launch_row_sweep(L, kc, prob->d, ws, st);
     hipLaunchKernelGGL(row_finish, grid1(kc.n), dim3(BLOCK), 0, st, at<Ctrl>(ws, L.ctrl), at<Sched>(ws, L.sched), kc,
@@ -2333,29 +2440,24 @@ lamp_status lamp_solve_batched(const lamp_problem* probs, int32_t count, const l
     if (reinterpret_cast<uintptr_t>(ws) % 256 != 0) return fail(LAMP_EINVAL, "workspace must be 256-byte aligned");
     const size_t need = lamp_batch_workspace_bytes(probs, count, params) - 256;
     if (ws_bytes < need) return fail(LAMP_ENOMEM, "workspace has %zu bytes, needs %zu", ws_bytes, need);
-    hipStream_t st = (hipStream_t)stream;
-    hipStream_t own = nullptr;
-    if (!st) {
-        HIPCHK(hipStreamSynchronize(nullptr));
-        HIPCHK(hipStreamCreateWithFlags(&own, hipStreamNonBlocking));
-        st = own;
-    }
-    struct StreamGuard {
-        hipStream_t s;
-        ~StreamGuard() {
-            if (s) {
-                (void)hipStreamSynchronize(s);
-                (void)hipStreamDestroy(s);
-            }
-        }
-    } guard{own};
-    // the first problem's sub-workspace is laid out at offset 0 of a batch plan's problem region;
-    // its small-scalar area is scratch here (every problem's preparation rewrites it later)
+    CallStream call;
+    if ((e = call.open((hipStream_t)stream)) != LAMP_OK) return e;
+    hipStream_t st = call.st;
+    // every marginal before one wait (the schedule table's room holds the statistics)
     {
         const BatchPlan B0 = batch_plan(probs, count);
-        double* dev6 = at<double>(static_cast<char*>(ws) + B0.sub[0], B0.L[0].small);
-        for (int p = 0; p < count; ++p)
-            if ((e = check_marginals(&probs[p], dev6, st)) != LAMP_OK) return e;
+        double* stats = at<double>(ws, B0.sched);
+        const int at_once = TAB;
+        for (int p0 = 0; p0 < count; p0 += at_once) {
+            const int p1 = std::min(count, p0 + at_once);
+            for (int p = p0; p < p1; ++p) launch_marginals(&probs[p], stats + 6 * (p - p0), st);
+            HIPCHK(hipGetLastError());
+            std::vector<double> h(6 * (p1 - p0));
+            HIPCHK(hipMemcpyAsync(h.data(), stats, sizeof(double) * h.size(), hipMemcpyDeviceToHost, st));
+            HIPCHK(hipStreamSynchronize(st));
+            for (int p = p0; p < p1; ++p)
+                if ((e = judge_marginals(h.data() + 6 * (p - p0))) != LAMP_OK) return e;
+        }
     }
 
     int cand = 0;

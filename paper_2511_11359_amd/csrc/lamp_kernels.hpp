@@ -219,12 +219,10 @@ __device__ __forceinline__ float fexp2(double e) {
 // ---------------------------------------------------------------------------
 // Preparation: centred FP64 copies, squared norms.
 // ---------------------------------------------------------------------------
-__global__ void prep_points(const float* __restrict__ pts, int64_t cnt, int d,
-                            const float* __restrict__ mu_src_a, const float* __restrict__ mu_src_b,
-                            double* __restrict__ out, double* __restrict__ nrm2,
-                            float* __restrict__ outf, int metric) {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= cnt) return;
+__device__ __forceinline__ void prep_point(const float* __restrict__ pts, int64_t i, int d,
+                                           const float* __restrict__ mu_src_a, const float* __restrict__ mu_src_b,
+                                           double* __restrict__ out, double* __restrict__ nrm2,
+                                           float* __restrict__ outf, int metric) {
     double acc = 0.0;
     for (int k = 0; k < d; ++k) {
         // centre mu = (x_0 + y_0) / 2: any fixed point works, this one keeps
@@ -238,13 +236,43 @@ __global__ void prep_points(const float* __restrict__ pts, int64_t cnt, int d,
     nrm2[i] = metric == METRIC_SQEUCLID ? acc : 0.0;   // the l1 / l_inf pair term carries the cost
 }
 
+// What the cost maximum starts from: a_j = -|y~_j|^2 / 2 and a cleared result (nullable).
+struct MaxStart {
+    double* a;
+    unsigned long long* bits;
+};
+
+// Both clouds in one launch: the n source points, then the m targets.
+__global__ void prep_points(const float* __restrict__ x, int64_t n, const float* __restrict__ y, int64_t m, int d,
+                            double* __restrict__ xc, double* __restrict__ xn2, float* __restrict__ xcf,
+                            double* __restrict__ yc, double* __restrict__ yn2, float* __restrict__ ycf, int metric,
+                            MaxStart mx) {
+    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (e == 0 && mx.bits) *mx.bits = 0ull;
+    if (e < n) {
+        prep_point(x, e, d, x, y, xc, xn2, xcf, metric);
+    } else if (e < n + m) {
+        const int64_t j = e - n;
+        prep_point(y, j, d, x, y, yc, yn2, ycf, metric);
+        if (mx.a) mx.a[j] = -0.5 * yn2[j];
+    }
+}
+
 // Index codes of the points of an explicit cost matrix: i for row i, -(i + 1) for
-// column i (cols = 1); zero norms.
-__global__ void prep_cost_codes(int64_t cnt, int cols, double* __restrict__ out, double* __restrict__ nrm2) {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= cnt) return;
-    out[i] = cols ? -(double)(i + 1) : (double)i;
-    nrm2[i] = 0.0;
+// column i; zero norms.
+__global__ void prep_cost_codes(int64_t n, int64_t m, double* __restrict__ xc, double* __restrict__ xn2,
+                                double* __restrict__ yc, double* __restrict__ yn2, MaxStart mx) {
+    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (e == 0 && mx.bits) *mx.bits = 0ull;
+    if (e < n) {
+        xc[e] = (double)e;
+        xn2[e] = 0.0;
+    } else if (e < n + m) {
+        const int64_t j = e - n;
+        yc[j] = -(double)(j + 1);
+        yn2[j] = 0.0;
+        if (mx.a) mx.a[j] = 0.0;
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -252,14 +280,40 @@ __global__ void prep_cost_codes(int64_t cnt, int cols, double* __restrict__ out,
 //   g^A_j = -lam_t LOG2E (s yn2_j + K nu_j),  g^B_j = -lam_{t+1} LOG2E (s yn2_j + K nubar_j),
 //   nubar = nu + w (theta - nu)  (step:lamp_mid_nu).
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ void col_table_init_body(const Ctrl* ctrl, const Sched* sched, Consts kc,
-                               const double* __restrict__ yn2, const double* __restrict__ nu,
-                               const double* __restrict__ theta, double2* __restrict__ gtab2,
-                               float2* __restrict__ gtabf, int64_t m_pad, int64_t bx_, int64_t by_, int64_t nb_) {
-    int64_t j = (int64_t)bx_ * blockDim.x + threadIdx.x;
+// with offsets != nullptr also a_j = -g^B_j / cfac^B for the exact offsets.  The kernel opens a
+// call: the first thread writes the control block if it comes by value (init.write; the schedule
+// entry then comes with it) and stops the call before its first iteration (done, err bit 1) if a
+// marginal is not a positive vector of sum 1 (init.marginals, from marginal_stats; nullable).
+struct CallInit {
+    Ctrl ctrl;
+    Sched sched;
+    const double* marginals;
+    int32_t write;
+};
+
+__device__ __forceinline__ bool marginals_bad(const double* v) {
+    return v[1] >= 0.0 || v[4] >= 0.0 || fabs(v[0] - 1.0) > 1e-9 || fabs(v[3] - 1.0) > 1e-9;
+}
+
+__global__ void col_table_init(Ctrl* ctrl, Sched* sched, Consts kc, const double* __restrict__ yn2,
+                               const double* __restrict__ nu, const double* __restrict__ theta,
+                               double2* __restrict__ gtab2, float2* __restrict__ gtabf, int64_t m_pad,
+                               double* __restrict__ offsets, CallInit init) {
+    const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t t = init.write ? init.ctrl.t : ctrl->t;
+    const Sched sc = init.write ? init.sched : sched[t - ctrl->t_base];
+    if (j == 0) {
+        if (init.write) {
+            *ctrl = init.ctrl;
+            sched[0] = init.sched;
+        }
+        if (init.marginals && marginals_bad(init.marginals)) {
+            ctrl->done = 1;
+            ctrl->done_seen = 1;
+            ctrl->err = 2;
+        }
+    }
     if (j >= kc.m) return;
-    const int64_t t = ctrl->t;
-    const Sched sc = sched[t - ctrl->t_base];
     double nb = nu[j] + sc.w * (theta[j] - nu[j]);
     double base = kc.s * yn2[j];
     double2 g;
@@ -267,29 +321,17 @@ __device__ __forceinline__ void col_table_init_body(const Ctrl* ctrl, const Sche
     g.y = -sc.lamB * LOG2E * (base + kc.K * nb);
     gtab2[(t & 1) * kc.m + j] = g;
     if (gtabf) gtabf[(t & 1) * m_pad + j] = make_float2((float)g.x, (float)g.y);
+    if (offsets) offsets[j] = -g.y / (2.0 * kc.s * sc.lamB * LOG2E);
 }
 
-__global__ void col_table_init(const Ctrl* ctrl, const Sched* sched, Consts kc,
-                               const double* __restrict__ yn2, const double* __restrict__ nu,
-                               const double* __restrict__ theta, double2* __restrict__ gtab2,
-                               float2* __restrict__ gtabf, int64_t m_pad) {
-    col_table_init_body(ctrl, sched, kc, yn2, nu, theta, gtab2, gtabf, m_pad, (int64_t)blockIdx.x, (int64_t)blockIdx.y, (int64_t)gridDim.x);
-}
-
-// a_j = -g^B_j / cfac^B for the exact offset initialisation.
-__device__ __forceinline__ void offset_coeffs_body(const Ctrl* ctrl, const Sched* sched, Consts kc,
-                              const double2* __restrict__ gtab2, double* __restrict__ a, int64_t bx_, int64_t by_, int64_t nb_) {
-    int64_t j = (int64_t)bx_ * blockDim.x + threadIdx.x;
-    if (j >= kc.m) return;
-    const int64_t t = ctrl->t;
-    const Sched sc = sched[t - ctrl->t_base];
-    const double cB = 2.0 * kc.s * sc.lamB * LOG2E;
-    a[j] = -gtab2[(t & 1) * kc.m + j].y / cB;
-}
-
-__global__ void offset_coeffs(const Ctrl* ctrl, const Sched* sched, Consts kc,
-                              const double2* __restrict__ gtab2, double* __restrict__ a) {
-    offset_coeffs_body(ctrl, sched, kc, gtab2, a, (int64_t)blockIdx.x, (int64_t)blockIdx.y, (int64_t)gridDim.x);
+// The iterate of the workspace's buffers into the caller's state, unless the call was stopped by
+// its marginals.
+__global__ void commit_state(const Ctrl* ctrl, int64_t m, const double* __restrict__ nu1,
+                             const double* __restrict__ th1, double* __restrict__ nu, double* __restrict__ theta) {
+    const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (j >= m || (ctrl->err & 2)) return;
+    nu[j] = nu1[j];
+    theta[j] = th1[j];
 }
 
 // ---------------------------------------------------------------------------
@@ -369,24 +411,34 @@ __global__ __launch_bounds__(BLOCK) void row_extreme_dyn(Consts kc, int D, const
     row_extreme_dyn_body(kc, D, xc, yc, a, sgn, part, split, sb.bx, sb.p, 0);
 }
 
-// Merge the partial minima (exact, order independent); optionally transform.
-//   mode 0: out_i = min            (offset init, writes H)
-//   mode 1: out_i = xn2_i - 2 min  (squared distance maximum of row i)
-__device__ __forceinline__ void row_extreme_merge_body(Consts kc, const double* __restrict__ part, int P,
-                                  const double* __restrict__ xn2, int mode,
-                                  double* __restrict__ out, int64_t bx_, int64_t by_, int64_t nb_) {
-    int64_t i = (int64_t)bx_ * blockDim.x + threadIdx.x;
+// Merge the partial minima (exact, order independent).
+__global__ void row_extreme_merge(Consts kc, const double* __restrict__ part, int P, double* __restrict__ out) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= kc.n) return;
     double best = part[i];
 #pragma unroll 8
     for (int p = 1; p < P; ++p) best = fmin(best, part[(int64_t)p * kc.n + i]);
-    out[i] = (mode == 0) ? best : xn2[i] - 2.0 * best;
+    out[i] = best;
 }
 
-__global__ void row_extreme_merge(Consts kc, const double* __restrict__ part, int P,
-                                  const double* __restrict__ xn2, int mode,
-                                  double* __restrict__ out) {
-    row_extreme_merge_body(kc, part, P, xn2, mode, out, (int64_t)blockIdx.x, (int64_t)blockIdx.y, (int64_t)gridDim.x);
+// The largest xn2_i - 2 min_i over the rows into *bits (cleared before), and each row's value if
+// rowmax is given.  Non-negative doubles order as their bits do; a NaN counts as 0, and so does a
+// negative rounding of 0.
+__global__ void row_extreme_max(Consts kc, const double* __restrict__ part, int P, const double* __restrict__ xn2,
+                                double* __restrict__ rowmax, unsigned long long* __restrict__ bits) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    double v = 0.0;
+    if (i < kc.n) {
+        double best = part[i];
+#pragma unroll 8
+        for (int p = 1; p < P; ++p) best = fmin(best, part[(int64_t)p * kc.n + i]);
+        const double row = xn2[i] - 2.0 * best;
+        if (rowmax) rowmax[i] = row;
+        v = fmax(row, 0.0);
+    }
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) v = fmax(v, __shfl_xor(v, o, 64));
+    if ((threadIdx.x & 63) == 0 && v > 0.0) atomicMax(bits, (unsigned long long)__double_as_longlong(v));
 }
 
 // ---------------------------------------------------------------------------
@@ -1342,26 +1394,13 @@ __global__ __launch_bounds__(BLOCK) void dual_update(Ctrl* ctrl, const Sched* sc
 // ---------------------------------------------------------------------------
 // Deterministic single-block reductions.
 // ---------------------------------------------------------------------------
-// out[k] = sum_i v_k(i) for the certificate: mode selects the terms.
-__global__ void reduce_max(const double* __restrict__ v, int64_t n, double* __restrict__ out) {
-    __shared__ double sh[1024];
-    double best = -__builtin_inf();
-    for (int64_t i = threadIdx.x; i < n; i += blockDim.x) best = fmax(best, v[i]);
-    sh[threadIdx.x] = best;
-    __syncthreads();
-    for (int o = blockDim.x / 2; o > 0; o >>= 1) {
-        if ((int)threadIdx.x < o) sh[threadIdx.x] = fmax(sh[threadIdx.x], sh[threadIdx.x + o]);
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) out[0] = sh[0];
-}
-
 // sums[q] = sum_i vals[q * stride + i] for q < Q (each a fixed-order tree).
 __global__ void reduce_sums(const double* __restrict__ vals, int64_t n, int64_t stride, int Q,
                             double* __restrict__ out) {
     __shared__ double sh[1024];
     for (int q = 0; q < Q; ++q) {
         double acc = 0.0;
+#pragma unroll 8   // independent loads in flight; the sum order is unchanged
         for (int64_t i = threadIdx.x; i < n; i += blockDim.x) acc += vals[q * stride + i];
         sh[threadIdx.x] = acc;
         __syncthreads();
@@ -1374,18 +1413,32 @@ __global__ void reduce_sums(const double* __restrict__ vals, int64_t n, int64_t 
     }
 }
 
-// Checks of a marginal a[0..len) in one block: out[0] = sum (fixed order), out[1] = the
-// first index whose entry is not a positive finite number (-1: none), out[2] = that entry.
-__global__ void marginal_stats(const double* __restrict__ a, int64_t len, double* __restrict__ out) {
+// Checks of the marginals, one block each (block 0: r, block 1: c), into out[3 block + ...]: the
+// sum (fixed order), the first index whose entry is not a positive finite number (-1: none), that
+// entry.  Eight loads in flight a thread.
+__global__ void marginal_stats(const double* __restrict__ r, int64_t n, const double* __restrict__ c, int64_t m,
+                               double* __restrict__ out) {
     __shared__ double sh[1024];
     __shared__ long long bad[1024];
+    const double* __restrict__ a = blockIdx.x == 0 ? r : c;
+    const int64_t len = blockIdx.x == 0 ? n : m;
+    out += 3 * blockIdx.x;
     double acc = 0.0;
     long long first = -1;
-    for (int64_t i = threadIdx.x; i < len; i += blockDim.x) {
-        const double v = a[i];
+    auto take = [&](double v, int64_t i) {
         acc += v;
         if (first < 0 && !(v > 0.0 && v <= 1.7976931348623157e308)) first = (long long)i;
+    };
+    int64_t i = threadIdx.x;
+    const int64_t step = blockDim.x;
+    for (; i + 7 * step < len; i += 8 * step) {
+        double v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = a[i + u * step];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) take(v[u], i + u * step);
     }
+    for (; i < len; i += step) take(a[i], i);
     sh[threadIdx.x] = acc;
     bad[threadIdx.x] = first;
     __syncthreads();

@@ -74,3 +74,47 @@ def test_fused_completion_matches_single_steps():
     assert torch.equal(again.nu, full.nu) and torch.equal(again.theta, full.theta)
     _, rep3, _ = P.solve(prob, P.make_params(eta=wl.eta, tol=3e-2, max_iter=rep["iters"]))
     assert rep3["iters"] == rep["iters"] and not rep3["converged"]   # its iterate is tested one iteration later
+
+
+@pytest.mark.parametrize("call", ["step", "solve0", "solve1", "solve40", "noalloc", "cert", "batch"])
+@pytest.mark.parametrize("fault", ["negative", "nan", "sum"])
+def test_bad_marginals_leave_the_state(call, fault):
+    """With the cost scale given, step and solve judge the marginals on the device: the call is refused
+    and the state is as it was."""
+    wl = W.random_small(90, 70, 2, seed=4, eta=1e-2)
+    c = wl.c.copy()
+    if fault == "sum":
+        c *= 1.0 + 1e-8
+    else:
+        c[33] = -1e-3 if fault == "negative" else float("nan")
+    prob = P.Problem(wl.x, wl.y, wl.r, c, cost_scale=0.3, cost_norm=1.0)
+    st = P.State(torch.full((70,), 0.01, dtype=torch.float64, device="cuda"),
+                 torch.full((70,), 0.02, dtype=torch.float64, device="cuda"), 3, 1.5)
+    par = lambda it: P.make_params(eta=1e-2, max_iter=it)  # noqa: E731
+    run = {"step": lambda: P.step(prob, par(1), st), "solve0": lambda: P.solve(prob, par(0), st),
+           "solve1": lambda: P.solve(prob, par(1), st), "solve40": lambda: P.solve(prob, par(40), st),
+           "noalloc": lambda: P.step_noalloc(prob, par(1), st), "cert": lambda: P.certificate(prob, par(1), st),
+           "batch": lambda: P.solve_batched([prob, prob], par(9), [st, st.clone()])}[call]
+    with pytest.raises(P.LampError) as err:
+        run()
+    assert err.value.status == -2
+    assert ("c[33]" in str(err.value)) == (fault != "sum")
+    assert st.t == 3 and torch.all(st.nu == 0.01) and torch.all(st.theta == 0.02)
+    good, _, _ = P.solve(P.Problem(wl.x, wl.y, wl.r, wl.c, cost_scale=0.3, cost_norm=1.0), par(3))
+    assert good.t == 3 and torch.isfinite(good.nu).all()
+
+
+def test_solves_on_the_default_stream_from_threads():
+    """Calls without a stream take one from the pool, each its own."""
+    import threading
+    wl = W.random_small(200, 150, 3, seed=6, eta=1e-2)
+    ref, _, _ = P.solve(P.Problem(wl.x, wl.y, wl.r, wl.c), P.make_params(eta=1e-2, max_iter=30))
+    got = [None] * 6
+
+    def work(k):
+        got[k] = P.solve(P.Problem(wl.x, wl.y, wl.r, wl.c), P.make_params(eta=1e-2, max_iter=30))[0]
+
+    ts = [threading.Thread(target=work, args=(k,)) for k in range(6)]
+    [t.start() for t in ts]
+    [t.join() for t in ts]
+    assert all(g is not None and torch.equal(g.nu, ref.nu) for g in got)
