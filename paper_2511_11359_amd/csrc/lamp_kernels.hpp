@@ -454,6 +454,19 @@ __device__ __forceinline__ double fma_su(double a, double b, double c_uniform) {
     return e;
 }
 
+// Streamed points whose scalar loads are in flight together: from D = 9 on two.  The coordinates of all
+// UNROLL points do not fit the scalar registers there, and the compiler, loading them all the same,
+// moved them through vector lanes (48 of 244 vector instructions a group at D = 16): 20011 x 20011
+// column sweep at D = 16 382 -> 310 us, 12 256 -> 248; 40 problems at D = 16 in a batch 39.4 -> 32.6 ms.
+// Up to D = 8 the fence costs 1 to 2% (D = 6 183 -> 186 us).
+template <int D>
+constexpr int loads_together() { return D <= 8 ? UNROLL : 2; }
+
+template <int D>
+__device__ __forceinline__ void loads_fence(int u) {
+    if (u % loads_together<D>() == 0 && u > 0) __builtin_amdgcn_sched_barrier(0);
+}
+
 // One column j of the row sweep for this lane's row: returns 2^eA, 2^eB.
 template <int M, int D>
 __device__ __forceinline__ void row_terms(const double (&x)[D], double h, const double* __restrict__ yj,
@@ -524,7 +537,10 @@ __device__ __forceinline__ void row_sweep_body(const Ctrl* ctrl, const Sched* sc
             np += UNROLL;
         } else {
 #pragma unroll
-            for (int u = 0; u < UNROLL; ++u) row_terms<M, D>(x, h, yp + u * D, gp[u], cA, cB, pA[u], pB[u]);
+            for (int u = 0; u < UNROLL; ++u) {
+                loads_fence<D>(u);
+                row_terms<M, D>(x, h, yp + u * D, gp[u], cA, cB, pA[u], pB[u]);
+            }
         }
         float accA = pA[0], accB = pB[0];
 #pragma unroll
@@ -630,7 +646,10 @@ __global__ __launch_bounds__(1024) void row_sweep_par(const Ctrl* ctrl, const Sc
         if ((c + 1) * UNROLL <= len) {
             float pA[UNROLL], pB[UNROLL];
 #pragma unroll
-            for (int u = 0; u < UNROLL; ++u) row_terms<M, D>(x, h, yp + u * D, gp[u], cA, cB, pA[u], pB[u]);
+            for (int u = 0; u < UNROLL; ++u) {
+                loads_fence<D>(u);
+                row_terms<M, D>(x, h, yp + u * D, gp[u], cA, cB, pA[u], pB[u]);
+            }
             accA = pA[0];
             accB = pB[0];
 #pragma unroll
@@ -864,7 +883,10 @@ __device__ __forceinline__ void col_sweep_run(double cA, double cB, const double
     for (int c = 0; c < nfull; ++c, xp += UNROLL * D, kp += UNROLL) {
         float accA = 0.f, accB = 0.f;
 #pragma unroll
-        for (int u = 0; u < UNROLL; ++u) col_terms<M, D, FACTOR>(y, xp + u * D, kp[u], G, Dj, cA, cB, accA, accB);
+        for (int u = 0; u < UNROLL; ++u) {
+            loads_fence<D>(u);
+            col_terms<M, D, FACTOR>(y, xp + u * D, kp[u], G, Dj, cA, cB, accA, accB);
+        }
         sumA += (double)accA;
         sumB += (double)accB;
     }
@@ -962,7 +984,10 @@ __global__ __launch_bounds__(1024) void col_sweep_par(const Ctrl* ctrl, const Sc
             float accA = 0.f, accB = 0.f;
             if ((c + 1) * UNROLL <= len) {
 #pragma unroll
-                for (int u = 0; u < UNROLL; ++u) col_terms<M, D, FACTOR>(y, xp + u * D, kp[u], G, Dj, cA, cB, accA, accB);
+                for (int u = 0; u < UNROLL; ++u) {
+                    loads_fence<D>(u);
+                    col_terms<M, D, FACTOR>(y, xp + u * D, kp[u], G, Dj, cA, cB, accA, accB);
+                }
             } else {
                 for (int u = 0; u < len - c * UNROLL; ++u)
                     col_terms<M, D, FACTOR>(y, xp + u * D, kp[u], G, Dj, cA, cB, accA, accB);
