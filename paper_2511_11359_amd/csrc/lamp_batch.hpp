@@ -51,16 +51,22 @@ __device__ __forceinline__ const T* as_const(const T* p) {
     return (const T*)(const __attribute__((address_space(4))) T*)(uintptr_t)p;
 }
 
-// Next work item of a persistent sweep kernel: one atomic increment per block on the
-// phase's counter (largest items come first in the list, so the tail is short).  The
-// counter is returned to zero by the next phase kernel of the iteration.
-__device__ __forceinline__ int next_item(unsigned* counter) {
-    __shared__ int k_sh;
-    if (threadIdx.x == 0) k_sh = (int)atomicAdd(counter, 1u);
-    __syncthreads();
-    const int k = __builtin_amdgcn_readfirstlane(k_sh);   // block-uniform
-    __syncthreads();
-    return k;
+// Work items of a persistent sweep: block b starts on item b of the list (largest first, so the
+// tail is short) and draws every further one from the phase's counter, one atomic increment a
+// block, asked for before the item in hand is swept, so that its latency is hidden.  The counter is
+// returned to zero by the next phase kernel of the iteration.
+template <typename F>
+__device__ __forceinline__ void for_items(unsigned* counter, int n_items, F&& sweep) {
+    __shared__ int next_sh[2];
+    int k = blockIdx.x;
+    for (int half = 0; k < n_items; half ^= 1) {
+        unsigned drawn = 0;
+        if (threadIdx.x == 0) drawn = atomicAdd(counter, 1u);
+        sweep(k);
+        if (threadIdx.x == 0) next_sh[half] = (int)(gridDim.x + drawn);
+        __syncthreads();
+        k = __builtin_amdgcn_readfirstlane(next_sh[half]);   // block-uniform; the halves alternate,
+    }                                                        // so one barrier an item is enough
 }
 
 __device__ __forceinline__ void reset_counter(unsigned* counter) {
@@ -76,36 +82,50 @@ __device__ __forceinline__ bool batch_idle(const ProbDesc* __restrict__ pd, int 
     return !__syncthreads_or(running);
 }
 
-// Row sweep items of every running problem; each item runs the body compiled for its
-// problem's dimension (the run-time form for any other dimension).
+// Row sweep items of every running problem.  What does not depend on the dimension stands outside
+// the switch, which holds the bare loops over the streamed points: with the whole body in each of
+// its 17 cases 311 scalar registers were spilled (662 in the column sweep, whose vector registers
+// for them left room for 5 of 8 waves).  A wave whose rows all lie past the end skips its item.
 __global__ __launch_bounds__(BLOCK) void batch_row_sweep(const ProbDesc* __restrict__ pd,
                                                          const Item* __restrict__ items,
                                                          const int* __restrict__ n_active,
                                                          const Sched* sched, unsigned* counter, int count) {
     const int n_items = *n_active;   // items of problems still running (rewritten by the host)
     if ((int)blockIdx.x >= n_items || batch_idle(pd, count)) return;   // surplus blocks leave at once
-    for (;;) {
-        const int k = next_item(counter);
-        if (k >= n_items) break;
+    for_items(counter, n_items, [&](int k) {
         const Item it = items[k];
         const ProbDesc& P = pd[it.prob];
         const Ctrl* ctrl = as_const(P.ctrl);
-        const double* xc = as_global(P.xc);
+        const int64_t n = P.kc.n;
+        const int64_t i = (int64_t)it.bx * BLOCK + threadIdx.x;
+        const int64_t wave_row = (int64_t)it.bx * BLOCK + __builtin_amdgcn_readfirstlane(threadIdx.x & ~63u);
+        if (halted_row(ctrl) || wave_row >= n) return;
+        const int64_t t = ctrl->t_row;
+        const Sched sc = sched[t - ctrl->t_base];
+        const double cA = 2.0 * P.kc.s * sc.lamA * LOG2E;
+        const double cB = 2.0 * P.kc.s * sc.lamB * LOG2E;
+        const int64_t j0 = it.by * P.split_r;
+        const int64_t j1 = min(P.kc.m, j0 + P.split_r);
+        const int64_t ii = i < n ? i : n - 1;
+        const double* xi = as_global(P.xc) + ii * P.d;
         const double* yc = as_const(P.yc);
-        const double2* gtab = as_const(P.gtab);
-        const double* H = as_global(P.H);
-        double2* rpart = as_global(P.rpart);
+        const double2* g = as_const(P.gtab) + (t & 1) * P.kc.m;
+        const double h = as_global(P.H)[ii];
+        double sumA = 0.0, sumB = 0.0;
         switch (P.d) {
-#define CASE(D)                                                                                                  \
-    case D:                                                                                                      \
-        row_sweep_body<METRIC_SQEUCLID, D>(ctrl, sched, P.kc, xc, yc, gtab, H, rpart, P.split_r, it.bx, it.by, 0); \
-        break;
+#define CASE(D)                                                                                  \
+    case D: {                                                                                    \
+        double x[D];                                                                             \
+        for (int q = 0; q < D; ++q) x[q] = xi[q];                                                \
+        row_sweep_run<METRIC_SQEUCLID, D, true>(cA, cB, x, h, yc, g, j0, j1, sumA, sumB);              \
+        break;                                                                                   \
+    }
             LAMP_BATCH_D(CASE)
 #undef CASE
-            default:
-                row_sweep_dyn_body(ctrl, sched, P.kc, P.d, xc, yc, gtab, H, rpart, P.split_r, it.bx, it.by, 0);
+            default: row_sweep_run_dyn(P.kc, P.d, cA, cB, xi, h, yc, g, j0, j1, sumA, sumB);
         }
-    }
+        if (i < n) as_global(P.rpart)[it.by * n + i] = make_double2(sumA, sumB);
+    });
 }
 
 __global__ __launch_bounds__(BLOCK) void batch_row_finish(const ProbDesc* __restrict__ pd,
@@ -127,31 +147,47 @@ __global__ __launch_bounds__(BLOCK) void batch_col_sweep(const ProbDesc* __restr
                                                          const Sched* sched, unsigned* counter, int count) {
     const int n_items = *n_active;   // items of problems still running (rewritten by the host)
     if ((int)blockIdx.x >= n_items || batch_idle(pd, count)) return;   // surplus blocks leave at once
-    for (;;) {
-        const int k = next_item(counter);
-        if (k >= n_items) break;
+    for_items(counter, n_items, [&](int k) {
         const Item it = items[k];
         const ProbDesc& P = pd[it.prob];
         const Ctrl* ctrl = as_const(P.ctrl);
+        const int64_t m = P.kc.m;
+        const int64_t j = (int64_t)it.bx * BLOCK + threadIdx.x;
+        const int64_t wave_col = (int64_t)it.bx * BLOCK + __builtin_amdgcn_readfirstlane(threadIdx.x & ~63u);
+        if (halted(ctrl) || wave_col >= m) return;
+        const int64_t t = ctrl->t;
+        const Sched sc = sched[t - ctrl->t_base];
+        const double cA = 2.0 * P.kc.s * sc.lamA * LOG2E;
+        const double cB = 2.0 * P.kc.s * sc.lamB * LOG2E;
+        const int64_t i0 = it.by * P.split_c;
+        const int64_t i1 = min(P.kc.n, i0 + P.split_c);
+        const int64_t jj = j < m ? j : m - 1;
+        const double* yj = as_global(P.yc) + jj * P.d;
         const double* xc = as_const(P.xc);
-        const double* yc = as_global(P.yc);
-        const double2* gtab = as_global(P.gtab);
-        const RowVar* rowvar = as_const(P.rowvar);
         const double2* rowck = as_const(P.rowck);
-        double2* cpart = as_global(P.cpart);
+        const double2 g = as_global(P.gtab)[(t & 1) * m + jj];
+        const double G = g.y / cB;
+        const double Dj = g.x - cA * G;
+        const bool factor = P.kc.factor_cols;
+        double sumA = 0.0, sumB = 0.0;
         switch (P.d) {
-#define CASE(D)                                                                                                 \
-    case D:                                                                                                     \
-        col_sweep_body<METRIC_SQEUCLID, D>(ctrl, sched, P.kc, xc, yc, gtab, rowvar, rowck, cpart, P.split_c, it.bx, \
-                                           it.by, 0);                                                           \
-        break;
+#define CASE(D)                                                                                      \
+    case D: {                                                                                        \
+        double y[D];                                                                                 \
+        for (int q = 0; q < D; ++q) y[q] = yj[q];                                                    \
+        if (factor) col_sweep_run<METRIC_SQEUCLID, D, true, true>(cA, cB, y, G, Dj, xc, rowck, i0, i1, sumA, sumB); \
+        else col_sweep_run<METRIC_SQEUCLID, D, false, true>(cA, cB, y, G, Dj, xc, rowck, i0, i1, sumA, sumB);       \
+        break;                                                                                       \
+    }
             LAMP_BATCH_D(CASE)
 #undef CASE
-            default:
-                col_sweep_dyn_body(ctrl, sched, P.kc, P.d, xc, yc, gtab, rowvar, rowck, cpart, P.split_c, it.bx, it.by,
-                                   0);
+            default: col_sweep_run_dyn(P.kc, P.d, cA, cB, yj, G, Dj, xc, rowck, i0, i1, sumA, sumB);
         }
-    }
+        const double inv_n = 1.0 / (double)P.kc.n;   // the row weights r_i enter as n r_i (rowck)
+        sumA *= factor ? exp2(Dj) * inv_n : inv_n;
+        sumB *= inv_n;
+        if (j < m) as_global(P.cpart)[it.by * m + j] = make_double2(sumA, sumB);
+    });
 }
 
 __global__ __launch_bounds__(BLOCK) void batch_dual_update(const ProbDesc* __restrict__ pd,

@@ -458,13 +458,17 @@ __device__ __forceinline__ double fma_su(double a, double b, double c_uniform) {
 // UNROLL points do not fit the scalar registers there, and the compiler, loading them all the same,
 // moved them through vector lanes (48 of 244 vector instructions a group at D = 16): 20011 x 20011
 // column sweep at D = 16 382 -> 310 us, 12 256 -> 248; 40 problems at D = 16 in a batch 39.4 -> 32.6 ms.
-// Up to D = 8 the fence costs 1 to 2% (D = 6 183 -> 186 us).
-template <int D>
-constexpr int loads_together() { return D <= 8 ? UNROLL : 2; }
+// Up to D = 8 the fence costs 1 to 2% (D = 6 183 -> 186 us).  TIGHT: for a kernel that holds more
+// scalars beside the loop, the most points whose coordinates and pair of exponent terms fit 64.
+template <int D, bool TIGHT>
+constexpr int loads_together() {
+    if (!TIGHT) return D <= 8 ? UNROLL : 2;
+    return D <= 2 ? UNROLL : D <= 6 ? 4 : 2;
+}
 
-template <int D>
+template <int D, bool TIGHT = false>
 __device__ __forceinline__ void loads_fence(int u) {
-    if (u % loads_together<D>() == 0 && u > 0) __builtin_amdgcn_sched_barrier(0);
+    if (u % loads_together<D, TIGHT>() == 0 && u > 0) __builtin_amdgcn_sched_barrier(0);
 }
 
 // One column j of the row sweep for this lane's row: returns 2^eA, 2^eB.
@@ -489,6 +493,42 @@ __device__ __forceinline__ void row_terms_dt(const double (&x)[D], double h, dou
     pB = fexp2(fma_su(dot, cB, g.y));
     const double cs = fma(-2.0, dot, M == METRIC_SQEUCLID ? xa + yn2j : xa);
     tB = pB * (float)cs;
+}
+
+// The row sums of one lane's row over the columns [j0, j1).
+template <int M, int D, bool TIGHT = false>
+__device__ __forceinline__ void row_sweep_run(double cA, double cB, const double (&x)[D], double h,
+                                              const double* __restrict__ yc, const double2* __restrict__ g,
+                                              int64_t j0, int64_t j1, double& sumA, double& sumB) {
+    const int nfull = (int)((j1 - j0) / UNROLL);
+    const double* __restrict__ yp = yc + j0 * D;
+    const double2* __restrict__ gp = g + j0;
+    for (int c = 0; c < nfull; ++c, yp += UNROLL * D, gp += UNROLL) {
+        float pA[UNROLL], pB[UNROLL];
+#pragma unroll
+        for (int u = 0; u < UNROLL; ++u) {
+            loads_fence<D, TIGHT>(u);
+            row_terms<M, D>(x, h, yp + u * D, gp[u], cA, cB, pA[u], pB[u]);
+        }
+        float accA = pA[0], accB = pB[0];
+#pragma unroll
+        for (int u = 1; u < UNROLL; ++u) {
+            accA += pA[u];
+            accB += pB[u];
+        }
+        sumA += (double)accA;
+        sumB += (double)accB;
+    }
+    const int rem = (int)((j1 - j0) - (int64_t)nfull * UNROLL);
+    float accA = 0.f, accB = 0.f;
+    for (int u = 0; u < rem; ++u) {
+        float a, b;
+        row_terms<M, D>(x, h, yp + u * D, gp[u], cA, cB, a, b);
+        accA += a;
+        accB += b;
+    }
+    sumA += (double)accA;
+    sumB += (double)accB;
 }
 
 // Row sweep body; with DT the sweep also sums the B coupling's cost terms for D_t tracking
@@ -521,61 +561,38 @@ __device__ __forceinline__ void row_sweep_body(const Ctrl* ctrl, const Sched* sc
     const double h = H[ii];
 
     double sumA = 0.0, sumB = 0.0, sumT = 0.0;
-    double xa = 0.0;
-    if constexpr (DT) xa = (M == METRIC_SQEUCLID ? xn2[ii] : 0.0) + 2.0 * h;
-    const int nfull = (int)((j1 - j0) / UNROLL);
-    const double* __restrict__ yp = yc + j0 * D;
-    const double2* __restrict__ gp = g + j0;
-    const double* __restrict__ np = DT ? yn2 + j0 : nullptr;
-    for (int c = 0; c < nfull; ++c, yp += UNROLL * D, gp += UNROLL) {
-        float pA[UNROLL], pB[UNROLL], tB[UNROLL];
-        if constexpr (DT) {
+    if constexpr (!DT) {
+        row_sweep_run<M, D>(cA, cB, x, h, yc, g, j0, j1, sumA, sumB);
+    } else {
+        const double xa = (M == METRIC_SQEUCLID ? xn2[ii] : 0.0) + 2.0 * h;
+        for (int64_t jb = j0; jb < j1; jb += UNROLL) {
+            float accA = 0.f, accB = 0.f, accT = 0.f;
+            auto terms = [&](int64_t j, float& a, float& b, float& tb) {
+                row_terms_dt<M, D>(x, h, xa, yc + j * D, M == METRIC_SQEUCLID ? yn2[j] : 0.0, g[j], cA, cB, a, b, tb);
+            };
+            if (jb + UNROLL <= j1) {
+                float pA[UNROLL], pB[UNROLL], tB[UNROLL];
 #pragma unroll
-            for (int u = 0; u < UNROLL; ++u)
-                row_terms_dt<M, D>(x, h, xa, yp + u * D, M == METRIC_SQEUCLID ? np[u] : 0.0, gp[u], cA, cB, pA[u],
-                                   pB[u], tB[u]);
-            np += UNROLL;
-        } else {
+                for (int u = 0; u < UNROLL; ++u) terms(jb + u, pA[u], pB[u], tB[u]);
 #pragma unroll
-            for (int u = 0; u < UNROLL; ++u) {
-                loads_fence<D>(u);
-                row_terms<M, D>(x, h, yp + u * D, gp[u], cA, cB, pA[u], pB[u]);
+                for (int u = 0; u < UNROLL; ++u) {
+                    accA += pA[u];
+                    accB += pB[u];
+                    accT += tB[u];
+                }
+            } else {
+                for (int64_t j = jb; j < j1; ++j) {
+                    float a, b, tb;
+                    terms(j, a, b, tb);
+                    accA += a;
+                    accB += b;
+                    accT += tb;
+                }
             }
-        }
-        float accA = pA[0], accB = pB[0];
-#pragma unroll
-        for (int u = 1; u < UNROLL; ++u) {
-            accA += pA[u];
-            accB += pB[u];
-        }
-        sumA += (double)accA;
-        sumB += (double)accB;
-        if constexpr (DT) {
-            float accT = tB[0];
-#pragma unroll
-            for (int u = 1; u < UNROLL; ++u) accT += tB[u];
+            sumA += (double)accA;
+            sumB += (double)accB;
             sumT += (double)accT;
         }
-    }
-    {
-        const int rem = (int)((j1 - j0) - (int64_t)nfull * UNROLL);
-        float accA = 0.f, accB = 0.f, accT = 0.f;
-        for (int u = 0; u < rem; ++u) {
-            float a, b;
-            if constexpr (DT) {
-                float tb;
-                row_terms_dt<M, D>(x, h, xa, yp + u * D, M == METRIC_SQEUCLID ? np[u] : 0.0, gp[u], cA, cB, a, b,
-                                   tb);
-                accT += tb;
-            } else {
-                row_terms<M, D>(x, h, yp + u * D, gp[u], cA, cB, a, b);
-            }
-            accA += a;
-            accB += b;
-        }
-        sumA += (double)accA;
-        sumB += (double)accB;
-        sumT += (double)accT;
     }
     if (i < kc.n) {
         part[p * kc.n + i] = make_double2(sumA, sumB);
@@ -689,37 +706,22 @@ __global__ __launch_bounds__(BLOCK) void row_sweep_dt(const Ctrl* ctrl, const Sc
     row_sweep_body<M, D, true>(ctrl, sched, kc, xc, yc, gtab2, H, part, split, sb.bx, sb.p, 0, xn2, yn2, tpart);
 }
 
-__device__ __forceinline__ void row_sweep_dyn_body(const Ctrl* ctrl, const Sched* sched, Consts kc, int D,
-                                                       const double* __restrict__ xc,
-                                                       const double* __restrict__ yc,
-                                                       const double2* __restrict__ gtab2,
-                                                       const double* __restrict__ H,
-                                                       double2* __restrict__ part, int64_t split, int64_t bx_, int64_t by_, int64_t nb_) {
-    if (halted_row(ctrl)) return;
-    const int64_t t = ctrl->t_row;
-    const Sched sc = sched[t - ctrl->t_base];
-    const double cA = 2.0 * kc.s * sc.lamA * LOG2E;
-    const double cB = 2.0 * kc.s * sc.lamB * LOG2E;
-    const double2* __restrict__ g = gtab2 + (t & 1) * kc.m;
-    const int64_t i = (int64_t)bx_ * BLOCK + threadIdx.x;
-    const int64_t p = by_;
-    const int64_t j0 = p * split;
-    const int64_t j1 = min(kc.m, j0 + split);
-    const int64_t ii = i < kc.n ? i : kc.n - 1;
-    const double h = H[ii];
-    double sumA = 0.0, sumB = 0.0;
+// The row sums of one lane's row, at xi, for a run-time dimension.
+__device__ __forceinline__ void row_sweep_run_dyn(const Consts& kc, int D, double cA, double cB,
+                                                  const double* __restrict__ xi, double h,
+                                                  const double* __restrict__ yc, const double2* __restrict__ g,
+                                                  int64_t j0, int64_t j1, double& sumA, double& sumB) {
     for (int64_t jb = j0; jb < j1; jb += UNROLL) {
         float accA = 0.f, accB = 0.f;
         const int64_t je = min(j1, jb + UNROLL);
         for (int64_t j = jb; j < je; ++j) {
-            const double dot = pair_term_dyn(kc, D, xc + ii * D, yc + j * D, h);
+            const double dot = pair_term_dyn(kc, D, xi, yc + j * D, h);
             accA += fexp2(fma(cA, dot, g[j].x));
             accB += fexp2(fma(cB, dot, g[j].y));
         }
         sumA += (double)accA;
         sumB += (double)accB;
     }
-    if (i < kc.n) part[p * kc.n + i] = make_double2(sumA, sumB);
 }
 
 __global__ __launch_bounds__(BLOCK) void row_sweep_dyn(const Ctrl* ctrl, const Sched* sched, Consts kc, int D,
@@ -728,8 +730,19 @@ __global__ __launch_bounds__(BLOCK) void row_sweep_dyn(const Ctrl* ctrl, const S
                                                        const double2* __restrict__ gtab2,
                                                        const double* __restrict__ H,
                                                        double2* __restrict__ part, int64_t split) {
+    if (halted_row(ctrl)) return;
     const SweepBlock sb = sweep_block(kc.m, split);
-    row_sweep_dyn_body(ctrl, sched, kc, D, xc, yc, gtab2, H, part, split, sb.bx, sb.p, 0);
+    const int64_t t = ctrl->t_row;
+    const Sched sc = sched[t - ctrl->t_base];
+    const double cA = 2.0 * kc.s * sc.lamA * LOG2E;
+    const double cB = 2.0 * kc.s * sc.lamB * LOG2E;
+    const int64_t i = sb.bx * BLOCK + threadIdx.x;
+    const int64_t j0 = sb.p * split;
+    const int64_t ii = i < kc.n ? i : kc.n - 1;
+    double sumA = 0.0, sumB = 0.0;
+    row_sweep_run_dyn(kc, D, cA, cB, xc + ii * D, H[ii], yc, gtab2 + (t & 1) * kc.m, j0, min(kc.m, j0 + split), sumA,
+                      sumB);
+    if (i < kc.n) part[sb.p * kc.n + i] = make_double2(sumA, sumB);
 }
 
 // Exact recomputation of sigma_i = log2 sum_j 2^(g_j + cfac x~_i.y~_j) (two passes, FP64 max).
@@ -873,7 +886,7 @@ __device__ __forceinline__ void col_terms(const double (&y)[D], const double* __
     accB += fexp2(fma_su(dot, cB, ck.y));
 }
 
-template <int M, int D, bool FACTOR>
+template <int M, int D, bool FACTOR, bool TIGHT = false>
 __device__ __forceinline__ void col_sweep_run(double cA, double cB, const double (&y)[D], double G, double Dj,
                                               const double* __restrict__ xc, const double2* __restrict__ rowck,
                                               int64_t i0, int64_t i1, double& sumA, double& sumB) {
@@ -884,7 +897,7 @@ __device__ __forceinline__ void col_sweep_run(double cA, double cB, const double
         float accA = 0.f, accB = 0.f;
 #pragma unroll
         for (int u = 0; u < UNROLL; ++u) {
-            loads_fence<D>(u);
+            loads_fence<D, TIGHT>(u);
             col_terms<M, D, FACTOR>(y, xp + u * D, kp[u], G, Dj, cA, cB, accA, accB);
         }
         sumA += (double)accA;
@@ -1007,33 +1020,17 @@ __global__ __launch_bounds__(1024) void col_sweep_par(const Ctrl* ctrl, const Sc
     }
 }
 
-__device__ __forceinline__ void col_sweep_dyn_body(const Ctrl* ctrl, const Sched* sched, Consts kc, int D,
-                                                       const double* __restrict__ xc,
-                                                       const double* __restrict__ yc,
-                                                       const double2* __restrict__ gtab2,
-                                                       const RowVar* __restrict__ rowvar,
-                                                       const double2* __restrict__ rowck,
-                                                       double2* __restrict__ cpart, int64_t split, int64_t bx_, int64_t by_, int64_t nb_) {
-    if (halted(ctrl)) return;
-    const int64_t t = ctrl->t;
-    const Sched sc = sched[t - ctrl->t_base];
-    const double cA = 2.0 * kc.s * sc.lamA * LOG2E;
-    const double cB = 2.0 * kc.s * sc.lamB * LOG2E;
-    const int64_t j = (int64_t)bx_ * BLOCK + threadIdx.x;
-    const int64_t p = by_;
-    const int64_t i0 = p * split;
-    const int64_t i1 = min(kc.n, i0 + split);
-    const int64_t jj = j < kc.m ? j : kc.m - 1;
-    const double2 g = gtab2[(t & 1) * kc.m + jj];
-    const double G = g.y / cB;   // the exponent assembly of col_terms
-    const double Dj = g.x - cA * G;
-    double sumA = 0.0, sumB = 0.0;
+// The column sums of one lane's column, at yj, for a run-time dimension (the exponent assembly of col_terms).
+__device__ __forceinline__ void col_sweep_run_dyn(const Consts& kc, int D, double cA, double cB,
+                                                  const double* __restrict__ yj, double G, double Dj,
+                                                  const double* __restrict__ xc, const double2* __restrict__ rowck,
+                                                  int64_t i0, int64_t i1, double& sumA, double& sumB) {
     for (int64_t ib = i0; ib < i1; ib += UNROLL) {
         float accA = 0.f, accB = 0.f;
         const int64_t ie = min(i1, ib + UNROLL);
         for (int64_t i = ib; i < ie; ++i) {
             const double2 ck = rowck[i];
-            const double dot = pair_term_dyn(kc, D, yc + jj * D, xc + i * D, G);
+            const double dot = pair_term_dyn(kc, D, yj, xc + i * D, G);
             double eA = fma(dot, cA, ck.x);
             if (!kc.factor_cols) eA += Dj;
             accA += fexp2(eA);
@@ -1042,10 +1039,6 @@ __device__ __forceinline__ void col_sweep_dyn_body(const Ctrl* ctrl, const Sched
         sumA += (double)accA;
         sumB += (double)accB;
     }
-    const double inv_n = 1.0 / (double)kc.n;
-    sumA *= (kc.factor_cols ? exp2(Dj) : 1.0) * inv_n;
-    sumB *= inv_n;
-    if (j < kc.m) cpart[p * kc.m + j] = make_double2(sumA, sumB);
 }
 
 __global__ __launch_bounds__(BLOCK) void col_sweep_dyn(const Ctrl* ctrl, const Sched* sched, Consts kc, int D,
@@ -1055,8 +1048,24 @@ __global__ __launch_bounds__(BLOCK) void col_sweep_dyn(const Ctrl* ctrl, const S
                                                        const RowVar* __restrict__ rowvar,
                                                        const double2* __restrict__ rowck,
                                                        double2* __restrict__ cpart, int64_t split) {
+    if (halted(ctrl)) return;
     const SweepBlock sb = sweep_block(kc.n, split);
-    col_sweep_dyn_body(ctrl, sched, kc, D, xc, yc, gtab2, rowvar, rowck, cpart, split, sb.bx, sb.p, 0);
+    const int64_t t = ctrl->t;
+    const Sched sc = sched[t - ctrl->t_base];
+    const double cA = 2.0 * kc.s * sc.lamA * LOG2E;
+    const double cB = 2.0 * kc.s * sc.lamB * LOG2E;
+    const int64_t j = sb.bx * BLOCK + threadIdx.x;
+    const int64_t i0 = sb.p * split;
+    const int64_t jj = j < kc.m ? j : kc.m - 1;
+    const double2 g = gtab2[(t & 1) * kc.m + jj];
+    const double G = g.y / cB;
+    const double Dj = g.x - cA * G;
+    double sumA = 0.0, sumB = 0.0;
+    col_sweep_run_dyn(kc, D, cA, cB, yc + jj * D, G, Dj, xc, rowck, i0, min(kc.n, i0 + split), sumA, sumB);
+    const double inv_n = 1.0 / (double)kc.n;
+    sumA *= (kc.factor_cols ? exp2(Dj) : 1.0) * inv_n;
+    sumB *= inv_n;
+    if (j < kc.m) cpart[sb.p * kc.m + j] = make_double2(sumA, sumB);
 }
 
 // ---------------------------------------------------------------------------
