@@ -1526,7 +1526,6 @@ struct BatchRun {
     std::vector<Item> lists[2];   // row / column sweep items of the running problems, largest first
     std::vector<ProbDesc> desc;
     std::vector<Resolved> R;
-    std::vector<double*> nu1, th1;
     int grid;
     int64_t target_total;
     double tau1;
@@ -1597,8 +1596,9 @@ lamp_status batch_upload(const BatchRun& run, void* ws, hipStream_t st) {
     return LAMP_OK;
 }
 
-// Everything up to the first iteration: per-problem preparation and cost scale, the
-// shared schedule, control blocks, column tables, exact offsets, descriptors and work lists.
+// Everything up to the first iteration: marginal checks, preparation and cost scales, the
+// shared schedule, control blocks, column tables, exact offsets, descriptors and work lists.  Each
+// step is one launch for all problems with d <= BATCH_MAX_D and one a problem for the others.
 lamp_status batch_setup(const lamp_problem* probs, int count, const lamp_params* q, const lamp_state* states,
                         void* ws, hipStream_t st, int cand, int64_t t_stop, BatchRun* run) {
     run->B = batch_plan(probs, count);
@@ -1607,64 +1607,18 @@ lamp_status batch_setup(const lamp_problem* probs, int count, const lamp_params*
     run->target_total = kBatchCands[cand].target_total;
     run->desc.resize(count);
     run->R.resize(count);
-    run->nu1.resize(count);
-    run->th1.resize(count);
-    lamp_status e;
-    // every problem's cost maximum before one wait (the schedule table's room holds the results)
-    const int batch_max = (int)std::min<int64_t>(count, TAB * (int64_t)(sizeof(Sched) / sizeof(double)));
-    std::vector<double> top(count, 0.0);
-    auto* tops = at<unsigned long long>(ws, B.sched);
-    for (int p0 = 0; p0 < count; p0 += batch_max) {
-        const int p1 = std::min(count, p0 + batch_max);
-        for (int p = p0; p < p1; ++p) {
-            void* w = sub_ws(ws, B, p);
-            const bool mx = needs_max(&probs[p]);
-            const bool alone = B.L[p].coarse;   // may need a second pass: waits for itself
-            if ((e = prep_L(&probs[p], B.L[p], w, st, mx, alone ? nullptr : tops + (p - p0))) != LAMP_OK) return e;
-            if (!mx) continue;
-            if (alone) {
-                Scalars sc;
-                if ((e = max_cost(&probs[p], B.L[p], w, st, &sc)) != LAMP_OK) return e;
-                top[p] = sc.top;
-            } else {
-                launch_max(&probs[p], B.L[p], w, tops + (p - p0), st);
-            }
-        }
-        HIPCHK(hipGetLastError());
-        std::vector<double> got(p1 - p0);
-        HIPCHK(hipMemcpyAsync(got.data(), tops, sizeof(double) * (p1 - p0), hipMemcpyDeviceToHost, st));
-        HIPCHK(hipStreamSynchronize(st));
-        for (int p = p0; p < p1; ++p)
-            if (!B.L[p].coarse) top[p] = got[p - p0];
-    }
-    for (int p = 0; p < count; ++p) {
-        if ((e = resolve(&probs[p], q, B.L[p], top[p], 0.0, &run->R[p])) != LAMP_OK) return e;
-        if (run->R[p].tau1 != run->R[0].tau1)
-            return fail(LAMP_EINVAL, "batched problems need a common ||C||_inf (problem %d differs)", p);
-    }
-    run->tau1 = run->R[0].tau1;
     const int64_t t0 = states[0].t;
-    std::vector<Sched> tab(TAB);
-    fill_sched(tab.data(), TAB, states[0].inv_eta, run->tau1, q->eta);
-    HIPCHK(hipMemcpyAsync(at<Sched>(ws, B.sched), tab.data(), sizeof(Sched) * TAB, hipMemcpyHostToDevice, st));
-    std::vector<Ctrl> hc(count);
+    // the control blocks' room holds the statistics until they are written
+    static_assert(sizeof(Ctrl) >= BATCH_STATS * sizeof(double));
+    double* stats = at<double>(ws, B.ctrlv);
     std::vector<Item> fin[2];   // row finish / dual update items: one per block of rows / columns
     for (int p = 0; p < count; ++p) {
         const Layout& L = B.L[p];
         void* w = sub_ws(ws, B, p);
-        Ctrl& c = hc[p];
-        c = Ctrl{};
-        c.t = t0;
-        c.t_row = t0;
-        c.t_end = std::min(t_stop, t0 + TAB);
-        c.t_base = t0;
-        c.t_done = -1;
-        c.tol = q->tol;
-        c.res_last = -1.0;
-        const Consts kc = make_consts(&probs[p], run->R[p]);
         ProbDesc& D = run->desc[p];
+        D = ProbDesc{};
         D.ctrl = at<Ctrl>(ws, B.ctrlv) + p;
-        D.kc = kc;
+        D.kc = max_consts(&probs[p]);
         D.d = probs[p].d;
         D.n_dual_blocks = (int)cdiv(probs[p].m, BLOCK);
         D.xc = at<double>(w, L.xc);
@@ -1679,35 +1633,89 @@ lamp_status batch_setup(const lamp_problem* probs, int count, const lamp_params*
         D.rowck = at<double2>(w, L.rowck);
         D.rpart = at<double2>(ws, B.rpartB[p]);
         D.cpart = at<double2>(ws, B.cpartB[p]);
-        run->nu1[p] = at<double>(w, L.nu1);
-        run->th1[p] = at<double>(w, L.th1);
         D.buf.nu[t0 & 1] = states[p].nu;
         D.buf.theta[t0 & 1] = states[p].theta;
-        D.buf.nu[(t0 + 1) & 1] = run->nu1[p];
-        D.buf.theta[(t0 + 1) & 1] = run->th1[p];
+        D.buf.nu[(t0 + 1) & 1] = at<double>(w, L.nu1);
+        D.buf.theta[(t0 + 1) & 1] = at<double>(w, L.th1);
         D.respart = at<double>(w, L.respart);
+        D.x = probs[p].x;
+        D.y = probs[p].y;
+        D.aux = at<double>(w, L.scratch);
+        D.stats = stats + BATCH_STATS * p;
+        D.needs_max = needs_max(&probs[p]);
         for (int64_t x = 0; x < cdiv(probs[p].n, BLOCK); ++x) fin[0].push_back(Item{p, (int)x, 0, 0});
         for (int64_t x = 0; x < cdiv(probs[p].m, BLOCK); ++x) fin[1].push_back(Item{p, (int)x, 0, 0});
     }
     batch_assign(run, probs, std::vector<char>(count, 1));
+    const Item* rows = at<Item>(ws, B.items[1]);
+    const Item* cols = at<Item>(ws, B.items[3]);
+    const Item* pairs = at<Item>(ws, B.items[0]);
+    const ProbDesc* pd = at<ProbDesc>(ws, B.descs);
+    const unsigned n_rows = (unsigned)fin[0].size(), n_cols = (unsigned)fin[1].size();
+    const unsigned n_pairs = (unsigned)run->lists[0].size();
+    HIPCHK(hipMemcpyAsync(at<Item>(ws, B.items[1]), fin[0].data(), sizeof(Item) * n_rows, hipMemcpyHostToDevice, st));
+    HIPCHK(hipMemcpyAsync(at<Item>(ws, B.items[3]), fin[1].data(), sizeof(Item) * n_cols, hipMemcpyHostToDevice, st));
+    lamp_status e;
+    if ((e = batch_upload(*run, ws, st)) != LAMP_OK) return e;   // synchronises: the vectors above are read
+    hipLaunchKernelGGL(batch_marginals, dim3((unsigned)(2 * count)), dim3(1024), 0, st, pd);
+    hipLaunchKernelGGL(batch_prep, dim3(n_rows + n_cols), dim3(BLOCK), 0, st, pd, rows, (int)n_rows, cols);
+    hipLaunchKernelGGL(batch_extreme, dim3(n_pairs), dim3(BLOCK), 0, st, pd, pairs, +1.0);
+    hipLaunchKernelGGL(batch_extreme_max, dim3(n_rows), dim3(BLOCK), 0, st, pd, rows);
+    for (int p = 0; p < count; ++p) {
+        if (probs[p].d <= BATCH_MAX_D) continue;
+        void* w = sub_ws(ws, B, p);
+        auto* top = reinterpret_cast<unsigned long long*>(stats + BATCH_STATS * p + BATCH_STATS - 1);
+        const bool alone = B.L[p].coarse;   // may need a second pass: waits for itself, below
+        if ((e = prep_L(&probs[p], B.L[p], w, st, needs_max(&probs[p]), alone ? nullptr : top)) != LAMP_OK) return e;
+        if (needs_max(&probs[p]) && !alone) launch_max(&probs[p], B.L[p], w, top, st);
+    }
+    HIPCHK(hipGetLastError());
+    std::vector<double> got((size_t)BATCH_STATS * count);
+    HIPCHK(hipMemcpyAsync(got.data(), stats, sizeof(double) * got.size(), hipMemcpyDeviceToHost, st));
+    HIPCHK(hipStreamSynchronize(st));
+    for (int p = 0; p < count; ++p)
+        if ((e = judge_marginals(got.data() + (size_t)BATCH_STATS * p)) != LAMP_OK) return e;
+    for (int p = 0; p < count; ++p) {
+        double top = needs_max(&probs[p]) ? got[(size_t)BATCH_STATS * p + BATCH_STATS - 1] : 0.0;
+        if (needs_max(&probs[p]) && B.L[p].coarse) {
+            Scalars sc;
+            if ((e = max_cost(&probs[p], B.L[p], sub_ws(ws, B, p), st, &sc)) != LAMP_OK) return e;
+            top = sc.top;
+        }
+        if ((e = resolve(&probs[p], q, B.L[p], top, 0.0, &run->R[p])) != LAMP_OK) return e;
+        if (run->R[p].tau1 != run->R[0].tau1)
+            return fail(LAMP_EINVAL, "batched problems need a common ||C||_inf (problem %d differs)", p);
+    }
+    run->tau1 = run->R[0].tau1;
+    std::vector<Sched> tab(TAB);
+    fill_sched(tab.data(), TAB, states[0].inv_eta, run->tau1, q->eta);
+    HIPCHK(hipMemcpyAsync(at<Sched>(ws, B.sched), tab.data(), sizeof(Sched) * TAB, hipMemcpyHostToDevice, st));
+    std::vector<Ctrl> hc(count);
+    for (int p = 0; p < count; ++p) {
+        Ctrl& c = hc[p];
+        c = Ctrl{};
+        c.t = t0;
+        c.t_row = t0;
+        c.t_end = std::min(t_stop, t0 + TAB);
+        c.t_base = t0;
+        c.t_done = -1;
+        c.tol = q->tol;
+        c.res_last = -1.0;
+        run->desc[p].kc = make_consts(&probs[p], run->R[p]);
+    }
     const unsigned zeros[2] = {0u, 0u};
     HIPCHK(hipMemcpyAsync(at<unsigned>(ws, B.counters), zeros, sizeof(zeros), hipMemcpyHostToDevice, st));
     HIPCHK(hipMemcpyAsync(at<Ctrl>(ws, B.ctrlv), hc.data(), sizeof(Ctrl) * count, hipMemcpyHostToDevice, st));
-    HIPCHK(hipMemcpyAsync(at<Item>(ws, B.items[1]), fin[0].data(), sizeof(Item) * fin[0].size(), hipMemcpyHostToDevice,
+    HIPCHK(hipMemcpyAsync(at<ProbDesc>(ws, B.descs), run->desc.data(), sizeof(ProbDesc) * count, hipMemcpyHostToDevice,
                           st));
-    HIPCHK(hipMemcpyAsync(at<Item>(ws, B.items[3]), fin[1].data(), sizeof(Item) * fin[1].size(), hipMemcpyHostToDevice,
-                          st));
-    if ((e = batch_upload(*run, ws, st)) != LAMP_OK) return e;   // synchronises: the vectors above are read
-    for (int p = 0; p < count; ++p) {
-        const Layout& L = B.L[p];
-        void* w = sub_ws(ws, B, p);
-        const ProbDesc& D = run->desc[p];
-        // the per-problem set-up kernels read the batch control block and schedule
-        hipLaunchKernelGGL(col_table_init, grid1(D.kc.m), dim3(BLOCK), 0, st, D.ctrl, at<Sched>(ws, B.sched), D.kc,
-                           D.yn2, states[p].nu, states[p].theta, D.gtab, (float2*)nullptr, (int64_t)0,
-                           at<double>(w, L.scratch), CallInit{});
-        launch_offsets(L, D.kc, probs[p].d, w, st, D.ctrl, at<Sched>(ws, B.sched));
-    }
+    HIPCHK(hipStreamSynchronize(st));   // the copies read this call's vectors
+    hipLaunchKernelGGL(batch_col_table, dim3(n_cols), dim3(BLOCK), 0, st, pd, cols, (const Sched*)at<Sched>(ws, B.sched));
+    hipLaunchKernelGGL(batch_extreme, dim3(n_pairs), dim3(BLOCK), 0, st, pd, pairs, -1.0);
+    hipLaunchKernelGGL(batch_offsets, dim3(n_rows), dim3(BLOCK), 0, st, pd, rows);
+    for (int p = 0; p < count; ++p)
+        if (probs[p].d > BATCH_MAX_D)
+            launch_offsets(B.L[p], run->desc[p].kc, probs[p].d, sub_ws(ws, B, p), st, run->desc[p].ctrl,
+                           at<Sched>(ws, B.sched));
     HIPCHK(hipGetLastError());
     return LAMP_OK;
 }
@@ -2443,23 +2451,6 @@ lamp_status lamp_solve_batched(const lamp_problem* probs, int32_t count, const l
     CallStream call;
     if ((e = call.open((hipStream_t)stream)) != LAMP_OK) return e;
     hipStream_t st = call.st;
-    // every marginal before one wait (the schedule table's room holds the statistics)
-    {
-        const BatchPlan B0 = batch_plan(probs, count);
-        double* stats = at<double>(ws, B0.sched);
-        const int at_once = TAB;
-        for (int p0 = 0; p0 < count; p0 += at_once) {
-            const int p1 = std::min(count, p0 + at_once);
-            for (int p = p0; p < p1; ++p) launch_marginals(&probs[p], stats + 6 * (p - p0), st);
-            HIPCHK(hipGetLastError());
-            std::vector<double> h(6 * (p1 - p0));
-            HIPCHK(hipMemcpyAsync(h.data(), stats, sizeof(double) * h.size(), hipMemcpyDeviceToHost, st));
-            HIPCHK(hipStreamSynchronize(st));
-            for (int p = p0; p < p1; ++p)
-                if ((e = judge_marginals(h.data() + 6 * (p - p0))) != LAMP_OK) return e;
-        }
-    }
-
     int cand = 0;
     if ((e = batch_tune(probs, count, params, states, ws, st, &cand)) != LAMP_OK) return e;
     const int64_t t0 = states[0].t;
@@ -2528,6 +2519,9 @@ lamp_status lamp_solve_batched(const lamp_problem* probs, int32_t count, const l
             HIPCHK(hipStreamSynchronize(st));
         }
     }
+    hipLaunchKernelGGL(batch_commit, dim3((unsigned)B.cap_items[3]), dim3(BLOCK), 0, st,
+                       (const ProbDesc*)at<ProbDesc>(ws, B.descs), (const Item*)at<Item>(ws, B.items[3]), t0);
+    HIPCHK(hipGetLastError());
     HIPCHK(hipMemcpyAsync(hc.data(), hc_dev, sizeof(Ctrl) * count, hipMemcpyDeviceToHost, st));
     HIPCHK(hipStreamSynchronize(st));
     const double secs = std::chrono::duration<double>(std::chrono::steady_clock::now() - t_start).count();
@@ -2535,11 +2529,6 @@ lamp_status lamp_solve_batched(const lamp_problem* probs, int32_t count, const l
     const double lam0 = states[0].inv_eta;   // every state starts at (t0, lam0); states[0] is rewritten below
     for (int p = 0; p < count; ++p) {
         const int64_t tp = hc[p].done ? hc[p].t_done : hc[p].t;
-        if ((tp & 1) != (t0 & 1)) {
-            HIPCHK(hipMemcpyAsync(states[p].nu, run.nu1[p], sizeof(double) * probs[p].m, hipMemcpyDeviceToDevice, st));
-            HIPCHK(hipMemcpyAsync(states[p].theta, run.th1[p], sizeof(double) * probs[p].m, hipMemcpyDeviceToDevice,
-                                  st));
-        }
         double lam = lam0;
         for (int64_t k = t0; k < tp; ++k) lam = next_lam(lam, run.tau1, params->eta);
         states[p].t = tp;
@@ -2558,7 +2547,6 @@ lamp_status lamp_solve_batched(const lamp_problem* probs, int32_t count, const l
             outs[p].row_fallbacks = hc[p].fallbacks;
         }
     }
-    HIPCHK(hipStreamSynchronize(st));
     if (result != LAMP_OK) return result;
     return (all_conv || params->tol == 0.0) ? LAMP_OK : LAMP_NOT_CONVERGED;
 }

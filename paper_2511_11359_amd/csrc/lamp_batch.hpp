@@ -26,7 +26,14 @@ struct ProbDesc {
     double2* cpart;
     DualBufs buf;
     double* respart;
+    // set-up
+    const float *x, *y;
+    double* aux;            // per-column terms of the cost maximum, then of the offsets
+    double* stats;          // marginal_stats of r and c, then the cost maximum
+    int32_t needs_max, pad;
 };
+
+constexpr int BATCH_STATS = 7;   // doubles a problem
 
 struct Item {
     int32_t prob, bx, by, pad;
@@ -35,6 +42,7 @@ struct Item {
 // Every dimension the single-problem sweeps compile for the squared Euclidean cost.
 #define LAMP_BATCH_D(X) \
     X(1) X(2) X(3) X(4) X(5) X(6) X(7) X(8) X(9) X(10) X(11) X(12) X(13) X(14) X(15) X(16)
+constexpr int BATCH_MAX_D = 16;
 
 // The descriptor's pointers are loaded from memory, so the compiler cannot tell their
 // address space (it would use flat loads) nor that the column data are read-only during
@@ -49,6 +57,96 @@ __device__ __forceinline__ T* as_global(T* p) {
 template <typename T>
 __device__ __forceinline__ const T* as_const(const T* p) {
     return (const T*)(const __attribute__((address_space(4))) T*)(uintptr_t)p;
+}
+
+// ---------------------------------------------------------------------------
+// Set-up of every problem with d <= BATCH_MAX_D, each step one launch for all of them (a launch per
+// problem and step ran 64 problems of 512 to 8192 points through 512 small kernels).  The point and
+// column steps take the items of the row finish and dual update, the passes over all pairs those of
+// the row sweep, whose partials' room holds their minima.
+// ---------------------------------------------------------------------------
+__global__ __launch_bounds__(1024) void batch_marginals(const ProbDesc* __restrict__ pd) {
+    const ProbDesc& P = pd[blockIdx.x / 2];
+    if (blockIdx.x % 2 == 0) marginal_stats_body(as_global(P.r), P.kc.n, P.stats);
+    else marginal_stats_body(as_global(P.c), P.kc.m, P.stats + 3);
+}
+
+__global__ __launch_bounds__(BLOCK) void batch_prep(const ProbDesc* __restrict__ pd, const Item* __restrict__ rows,
+                                                    int n_rows, const Item* __restrict__ cols) {
+    const bool row = (int)blockIdx.x < n_rows;
+    const Item it = row ? rows[blockIdx.x] : cols[blockIdx.x - n_rows];
+    const ProbDesc& P = pd[it.prob];
+    if (P.d > BATCH_MAX_D) return;
+    const int64_t i = (int64_t)it.bx * BLOCK + threadIdx.x;
+    if (row) {
+        if (i == 0) P.stats[BATCH_STATS - 1] = 0.0;
+        if (i < P.kc.n) prep_point(P.x, i, P.d, P.x, P.y, const_cast<double*>(P.xc), const_cast<double*>(P.xn2), nullptr, METRIC_SQEUCLID);
+    } else if (i < P.kc.m) {
+        prep_point(P.y, i, P.d, P.x, P.y, const_cast<double*>(P.yc), const_cast<double*>(P.yn2), nullptr, METRIC_SQEUCLID);
+        P.aux[i] = -0.5 * P.yn2[i];
+    }
+}
+
+// Partial minima of a_j + sgn x~_i . y~_j: sgn = 1 for the cost maximum, -1 for the offsets.
+__global__ __launch_bounds__(BLOCK) void batch_extreme(const ProbDesc* __restrict__ pd,
+                                                       const Item* __restrict__ items, double sgn) {
+    const Item it = items[blockIdx.x];
+    const ProbDesc& P = pd[it.prob];
+    const int64_t wave_row = (int64_t)it.bx * BLOCK + __builtin_amdgcn_readfirstlane(threadIdx.x & ~63u);
+    if (wave_row >= P.kc.n || (sgn > 0.0 && !P.needs_max)) return;
+    const double* xc = as_global(P.xc);
+    const double* yc = as_const(P.yc);
+    const double* a = as_const(static_cast<const double*>(P.aux));
+    double* part = as_global(reinterpret_cast<double*>(P.rpart));
+    switch (P.d) {
+#define CASE(D)                                                                                           \
+    case D: row_extreme_body<METRIC_SQEUCLID, D>(P.kc, xc, yc, a, sgn, part, P.split_r, it.bx, it.by, 0); break;
+        LAMP_BATCH_D(CASE)
+#undef CASE
+    }
+}
+
+__global__ __launch_bounds__(BLOCK) void batch_extreme_max(const ProbDesc* __restrict__ pd,
+                                                           const Item* __restrict__ rows) {
+    const Item it = rows[blockIdx.x];
+    const ProbDesc& P = pd[it.prob];
+    if (P.d > BATCH_MAX_D || !P.needs_max) return;
+    row_extreme_max_body(P.kc.n, as_global(reinterpret_cast<const double*>(P.rpart)), P.P_r, as_global(P.xn2), nullptr,
+                         reinterpret_cast<unsigned long long*>(P.stats + BATCH_STATS - 1),
+                         (int64_t)it.bx * BLOCK + threadIdx.x);
+}
+
+__global__ __launch_bounds__(BLOCK) void batch_col_table(const ProbDesc* __restrict__ pd,
+                                                         const Item* __restrict__ cols,
+                                                         const Sched* __restrict__ sched) {
+    const Item it = cols[blockIdx.x];
+    const ProbDesc& P = pd[it.prob];
+    const int64_t j = (int64_t)it.bx * BLOCK + threadIdx.x;
+    const int64_t t = P.ctrl->t;
+    if (j < P.kc.m)
+        col_table_entry(P.kc, sched[t - P.ctrl->t_base], t, j, as_global(P.yn2), as_global(P.buf.nu[t & 1]),
+                        as_global(P.buf.theta[t & 1]), as_global(P.gtab), nullptr, 0, as_global(P.aux));
+}
+
+__global__ __launch_bounds__(BLOCK) void batch_offsets(const ProbDesc* __restrict__ pd,
+                                                       const Item* __restrict__ rows) {
+    const Item it = rows[blockIdx.x];
+    const ProbDesc& P = pd[it.prob];
+    const int64_t i = (int64_t)it.bx * BLOCK + threadIdx.x;
+    if (P.d <= BATCH_MAX_D && i < P.kc.n)
+        P.H[i] = merge_minima(as_global(reinterpret_cast<const double*>(P.rpart)), P.P_r, P.kc.n, i);
+}
+
+// The iterate every problem ended on into the caller's state, where it lies in the other buffer.
+__global__ __launch_bounds__(BLOCK) void batch_commit(const ProbDesc* __restrict__ pd, const Item* __restrict__ cols,
+                                                      int64_t t0) {
+    const Item it = cols[blockIdx.x];
+    const ProbDesc& P = pd[it.prob];
+    const int64_t j = (int64_t)it.bx * BLOCK + threadIdx.x;
+    const int64_t t = P.ctrl->done ? P.ctrl->t_done : P.ctrl->t;
+    if (j >= P.kc.m || (t & 1) == (t0 & 1)) return;
+    P.buf.nu[t0 & 1][j] = P.buf.nu[t & 1][j];
+    P.buf.theta[t0 & 1][j] = P.buf.theta[t & 1][j];
 }
 
 // Work items of a persistent sweep: block b starts on item b of the list (largest first, so the

@@ -295,6 +295,21 @@ __device__ __forceinline__ bool marginals_bad(const double* v) {
     return v[1] >= 0.0 || v[4] >= 0.0 || fabs(v[0] - 1.0) > 1e-9 || fabs(v[3] - 1.0) > 1e-9;
 }
 
+__device__ __forceinline__ void col_table_entry(const Consts& kc, const Sched& sc, int64_t t, int64_t j,
+                                                const double* __restrict__ yn2, const double* __restrict__ nu,
+                                                const double* __restrict__ theta, double2* __restrict__ gtab2,
+                                                float2* __restrict__ gtabf, int64_t m_pad,
+                                                double* __restrict__ offsets) {
+    double nb = nu[j] + sc.w * (theta[j] - nu[j]);
+    double base = kc.s * yn2[j];
+    double2 g;
+    g.x = -sc.lamA * LOG2E * (base + kc.K * nu[j]);
+    g.y = -sc.lamB * LOG2E * (base + kc.K * nb);
+    gtab2[(t & 1) * kc.m + j] = g;
+    if (gtabf) gtabf[(t & 1) * m_pad + j] = make_float2((float)g.x, (float)g.y);
+    if (offsets) offsets[j] = -g.y / (2.0 * kc.s * sc.lamB * LOG2E);
+}
+
 __global__ void col_table_init(Ctrl* ctrl, Sched* sched, Consts kc, const double* __restrict__ yn2,
                                const double* __restrict__ nu, const double* __restrict__ theta,
                                double2* __restrict__ gtab2, float2* __restrict__ gtabf, int64_t m_pad,
@@ -313,15 +328,7 @@ __global__ void col_table_init(Ctrl* ctrl, Sched* sched, Consts kc, const double
             ctrl->err = 2;
         }
     }
-    if (j >= kc.m) return;
-    double nb = nu[j] + sc.w * (theta[j] - nu[j]);
-    double base = kc.s * yn2[j];
-    double2 g;
-    g.x = -sc.lamA * LOG2E * (base + kc.K * nu[j]);
-    g.y = -sc.lamB * LOG2E * (base + kc.K * nb);
-    gtab2[(t & 1) * kc.m + j] = g;
-    if (gtabf) gtabf[(t & 1) * m_pad + j] = make_float2((float)g.x, (float)g.y);
-    if (offsets) offsets[j] = -g.y / (2.0 * kc.s * sc.lamB * LOG2E);
+    if (j < kc.m) col_table_entry(kc, sc, t, j, yn2, nu, theta, gtab2, gtabf, m_pad, offsets);
 }
 
 // The iterate of the workspace's buffers into the caller's state, unless the call was stopped by
@@ -411,34 +418,39 @@ __global__ __launch_bounds__(BLOCK) void row_extreme_dyn(Consts kc, int D, const
     row_extreme_dyn_body(kc, D, xc, yc, a, sgn, part, split, sb.bx, sb.p, 0);
 }
 
-// Merge the partial minima (exact, order independent).
-__global__ void row_extreme_merge(Consts kc, const double* __restrict__ part, int P, double* __restrict__ out) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= kc.n) return;
+// The least of the partial minima of row i (exact, order independent).
+__device__ __forceinline__ double merge_minima(const double* __restrict__ part, int P, int64_t n, int64_t i) {
     double best = part[i];
 #pragma unroll 8
-    for (int p = 1; p < P; ++p) best = fmin(best, part[(int64_t)p * kc.n + i]);
-    out[i] = best;
+    for (int p = 1; p < P; ++p) best = fmin(best, part[(int64_t)p * n + i]);
+    return best;
+}
+
+__global__ void row_extreme_merge(Consts kc, const double* __restrict__ part, int P, double* __restrict__ out) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < kc.n) out[i] = merge_minima(part, P, kc.n, i);
 }
 
 // The largest xn2_i - 2 min_i over the rows into *bits (cleared before), and each row's value if
 // rowmax is given.  Non-negative doubles order as their bits do; a NaN counts as 0, and so does a
 // negative rounding of 0.
-__global__ void row_extreme_max(Consts kc, const double* __restrict__ part, int P, const double* __restrict__ xn2,
-                                double* __restrict__ rowmax, unsigned long long* __restrict__ bits) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+__device__ __forceinline__ void row_extreme_max_body(int64_t n, const double* __restrict__ part, int P,
+                                                     const double* __restrict__ xn2, double* __restrict__ rowmax,
+                                                     unsigned long long* __restrict__ bits, int64_t i) {
     double v = 0.0;
-    if (i < kc.n) {
-        double best = part[i];
-#pragma unroll 8
-        for (int p = 1; p < P; ++p) best = fmin(best, part[(int64_t)p * kc.n + i]);
-        const double row = xn2[i] - 2.0 * best;
+    if (i < n) {
+        const double row = xn2[i] - 2.0 * merge_minima(part, P, n, i);
         if (rowmax) rowmax[i] = row;
         v = fmax(row, 0.0);
     }
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) v = fmax(v, __shfl_xor(v, o, 64));
     if ((threadIdx.x & 63) == 0 && v > 0.0) atomicMax(bits, (unsigned long long)__double_as_longlong(v));
+}
+
+__global__ void row_extreme_max(Consts kc, const double* __restrict__ part, int P, const double* __restrict__ xn2,
+                                double* __restrict__ rowmax, unsigned long long* __restrict__ bits) {
+    row_extreme_max_body(kc.n, part, P, xn2, rowmax, bits, (int64_t)blockIdx.x * blockDim.x + threadIdx.x);
 }
 
 // ---------------------------------------------------------------------------
@@ -1447,16 +1459,13 @@ __global__ void reduce_sums(const double* __restrict__ vals, int64_t n, int64_t 
     }
 }
 
-// Checks of the marginals, one block each (block 0: r, block 1: c), into out[3 block + ...]: the
-// sum (fixed order), the first index whose entry is not a positive finite number (-1: none), that
-// entry.  Eight loads in flight a thread.
-__global__ void marginal_stats(const double* __restrict__ r, int64_t n, const double* __restrict__ c, int64_t m,
-                               double* __restrict__ out) {
+// Check of a marginal by one block of 1024 threads, into out[3]: the sum (fixed order), the first
+// index whose entry is not a positive finite number (-1: none), that entry.  Eight loads in flight a
+// thread.
+__device__ __forceinline__ void marginal_stats_body(const double* __restrict__ a, int64_t len,
+                                                    double* __restrict__ out) {
     __shared__ double sh[1024];
     __shared__ long long bad[1024];
-    const double* __restrict__ a = blockIdx.x == 0 ? r : c;
-    const int64_t len = blockIdx.x == 0 ? n : m;
-    out += 3 * blockIdx.x;
     double acc = 0.0;
     long long first = -1;
     auto take = [&](double v, int64_t i) {
@@ -1489,6 +1498,13 @@ __global__ void marginal_stats(const double* __restrict__ r, int64_t n, const do
         out[1] = (double)bad[0];
         out[2] = bad[0] >= 0 ? a[bad[0]] : 0.0;
     }
+}
+
+// Both marginals of a call: block 0 checks r, block 1 c.
+__global__ void marginal_stats(const double* __restrict__ r, int64_t n, const double* __restrict__ c, int64_t m,
+                               double* __restrict__ out) {
+    if (blockIdx.x == 0) marginal_stats_body(r, n, out);
+    else marginal_stats_body(c, m, out + 3);
 }
 
 // ---------------------------------------------------------------------------
