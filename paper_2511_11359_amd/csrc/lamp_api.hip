@@ -392,6 +392,7 @@ lamp_status read_scalars(const Layout& L, void* ws, hipStream_t st, Scalars* out
 double* marginals_ptr(const Layout& L, void* ws) { return at<double>(ws, L.small) + MARGINALS_SLOT; }
 
 dim3 grid1(int64_t cnt) { return dim3((unsigned)cdiv(cnt, BLOCK)); }
+dim3 wave_grid(int64_t cnt) { return dim3((unsigned)cdiv(cnt, 64)); }
 
 template <typename T>
 void prep_ops(const lamp_problem* p, const Layout& L, void* ws, hipStream_t st) {
@@ -872,8 +873,8 @@ void launch_cost(const Layout& L, Consts kc, int d, void* ws, double cA, const d
     });
     if (!done)
         hipLaunchKernelGGL(cost_sweep_dyn, g, dim3(BLOCK), 0, st, kc, d, cA, xc, yc, xn2, yn2, gA, part, L.split_r);
-    hipLaunchKernelGGL(cost_finish, grid1(kc.n), dim3(BLOCK), 0, st, kc, (int)L.P_r, r, (const double*)part, rows);
-    hipLaunchKernelGGL(reduce_sums, dim3(1), dim3(1024), 0, st, (const double*)rows, kc.n, kc.n, 1, out);
+    hipLaunchKernelGGL(cost_finish, wave_grid(kc.n), dim3(64), 0, st, kc, (int)L.P_r, r, (const double*)part, rows);
+    hipLaunchKernelGGL(reduce_sums, dim3(1), dim3(1024), 0, st, (const double*)rows, kc.n, kc.n, out);
 }
 
 Consts max_consts(const lamp_problem* p) {
@@ -2125,9 +2126,9 @@ lamp_status lamp_certificate(const lamp_problem* prob, const lamp_params* params
                            (const double*)part, vals, psum, mu);
     }
     hipLaunchKernelGGL(col_products, grid1(kc.m), dim3(BLOCK), 0, st, kc, prob->c, state->theta, state->nu, prods);
-    hipLaunchKernelGGL(reduce_sums, dim3(1), dim3(1024), 0, st, vals, kc.n, kc.n, 4, small);
-    hipLaunchKernelGGL(reduce_sums, dim3(1), dim3(1024), 0, st, colres, kc.m, kc.m, 1, small + 4);
-    hipLaunchKernelGGL(reduce_sums, dim3(1), dim3(1024), 0, st, prods, kc.m, kc.m, 2, small + 5);
+    hipLaunchKernelGGL(reduce_sums, dim3(4), dim3(1024), 0, st, vals, kc.n, kc.n, small);
+    hipLaunchKernelGGL(reduce_sums, dim3(1), dim3(1024), 0, st, colres, kc.m, kc.m, small + 4);
+    hipLaunchKernelGGL(reduce_sums, dim3(2), dim3(1024), 0, st, prods, kc.m, kc.m, small + 5);
     // Round (Algorithm 3) of the same X and its cost
     hipLaunchKernelGGL(round_row_factors, grid1(kc.n), dim3(BLOCK), 0, st, kc, psum, prob->r, xr, wf);
     // Round step 2 over row splits; the split partials reuse the (consumed) column partials
@@ -2175,17 +2176,21 @@ lamp_status lamp_certificate(const lamp_problem* prob, const lamp_params* params
         hipLaunchKernelGGL(round_rank_one, grid1(kc.n), dim3(BLOCK), 0, st, kc, prob->d, at<double>(ws, L.xc),
                            at<double>(ws, L.xn2), dr, S, tr1, absdr);
     } else {
-        hipLaunchKernelGGL(round_rank_one_pairs, grid1(kc.n), dim3(BLOCK), 0, st, kc, prob->d,
-                           at<double>(ws, L.xc), at<double>(ws, L.yc), dr, dc, tr1, absdr);
+        by_md([&](auto m, auto dd) {
+            if constexpr (decltype(m)::value != METRIC_SQEUCLID)
+                hipLaunchKernelGGL((round_rank_one_pairs<decltype(m)::value, decltype(dd)::value>), split_grid,
+                                   dim3(BLOCK), 0, st, kc, prob->d, xs, at<double>(ws, L.yc), dc, part, L.split_r);
+        });
+        hipLaunchKernelGGL(round_rank_one_merge, grid1(kc.n), dim3(BLOCK), 0, st, kc, (int)L.P_r, (const double*)dr,
+                           (const double*)part, tr1, absdr);
     }
-    hipLaunchKernelGGL(reduce_sums, dim3(1), dim3(1024), 0, st, cpp, kc.n, kc.n, 1, small + 7);
-    hipLaunchKernelGGL(reduce_sums, dim3(1), dim3(1024), 0, st, tr1, kc.n, kc.n, 1, small + 8);
-    hipLaunchKernelGGL(reduce_sums, dim3(1), dim3(1024), 0, st, absdr, kc.n, kc.n, 1, small + 9);
+    // cpp, tr1 and absdr lie nm apart
+    hipLaunchKernelGGL(reduce_sums, dim3(3), dim3(1024), 0, st, cpp, kc.n, nm, small + 7);
     // <r, log Z^t> for D_t (the telescoped normaliser term of Lemma kl_diff)
     double* rlz = at<double>(ws, L.dtrow);   // n
     hipLaunchKernelGGL(normaliser_terms, grid1(kc.n), dim3(BLOCK), 0, st, kc, cA, state->inv_eta, psum,
                        at<double>(ws, L.H), at<double>(ws, L.xn2), prob->r, rlz);
-    hipLaunchKernelGGL(reduce_sums, dim3(1), dim3(1024), 0, st, rlz, kc.n, kc.n, 1, small + 10);
+    hipLaunchKernelGGL(reduce_sums, dim3(1), dim3(1024), 0, st, rlz, kc.n, kc.n, small + 10);
     // D^eta(theta), D^eta(nu) at the problem's eta (def:dual_spp_e); NaN at eta = 0
     const bool soft = params->eta > 0.0;
     if (soft) {
@@ -2201,7 +2206,7 @@ lamp_status lamp_certificate(const lamp_problem* prob, const lamp_params* params
         });
         hipLaunchKernelGGL(cert_soft_merge, grid1(kc.n), dim3(BLOCK), 0, st, kc, (int)L.P_r, 1.0 / params->eta,
                            prob->r, (const double*)mu, (const double*)part, sv);
-        hipLaunchKernelGGL(reduce_sums, dim3(1), dim3(1024), 0, st, sv, kc.n, kc.n, 2, small + 11);
+        hipLaunchKernelGGL(reduce_sums, dim3(2), dim3(1024), 0, st, sv, kc.n, kc.n, small + 11);
     }
     HIPCHK(hipGetLastError());
     double h[13];
@@ -2252,7 +2257,7 @@ lamp_status lamp_backward(const lamp_problem* prob, const lamp_params* params, c
     hipLaunchKernelGGL(state_col_term, grid1(kc.m), dim3(BLOCK), 0, st, kc, state->inv_eta, at<double>(ws, L.yn2),
                        state->nu, gA);
     launch_adjoint(L, kc, prob->d, ws, cA, gA, st);
-    hipLaunchKernelGGL(adjoint_finish, grid1(kc.n), dim3(BLOCK), 0, st, kc, prob->d, (int)L.P_r,
+    hipLaunchKernelGGL(adjoint_finish, wave_grid(kc.n * prob->d), dim3(64), 0, st, kc, prob->d, (int)L.P_r,
                        grad_out * 2.0 * R.s, at<double>(ws, L.xc), prob->r, at<double>(ws, L.rpart), grad_x);
     HIPCHK(hipGetLastError());
     return LAMP_OK;
@@ -2315,7 +2320,7 @@ lamp_status lamp_backward_y(const lamp_problem* prob, const lamp_params* params,
             hipLaunchKernelGGL((norm_sweep<decltype(m)::value, D>), dim3(sweep_grid(kc.n, L.P_r)), dim3(BLOCK), 0,
                                st, kc, cA, at<double>(ws, L.xc), (const CostCol<D>*)cols, at<double>(ws, L.rpart),
                                L.split_r);
-            hipLaunchKernelGGL(norm_finish, grid1(kc.n), dim3(BLOCK), 0, st, kc, (int)L.P_r, cA, prob->r,
+            hipLaunchKernelGGL(norm_finish, wave_grid(kc.n), dim3(64), 0, st, kc, (int)L.P_r, cA, prob->r,
                                (const double*)at<double>(ws, L.rpart), at<RowVar>(ws, L.rowvar));
         });
     });
@@ -2344,7 +2349,7 @@ lamp_status lamp_backward_y(const lamp_problem* prob, const lamp_params* params,
     if (!done)
         hipLaunchKernelGGL(adjoint_y_sweep_dyn, g, dim3(BLOCK), 0, st, kc, d, cA, xc, xcf, yc, gA, rv, part,
                            L.split_c);
-    hipLaunchKernelGGL(adjoint_y_finish, grid1(kc.m), dim3(BLOCK), 0, st, kc, d, (int)L.P_c, grad_out * 2.0 * R.s,
+    hipLaunchKernelGGL(adjoint_y_finish, wave_grid(kc.m * d), dim3(64), 0, st, kc, d, (int)L.P_c, grad_out * 2.0 * R.s,
                        yc, part, grad_y);
     HIPCHK(hipGetLastError());
     return LAMP_OK;

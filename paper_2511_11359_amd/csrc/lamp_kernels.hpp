@@ -1440,23 +1440,20 @@ __global__ __launch_bounds__(BLOCK) void dual_update(Ctrl* ctrl, const Sched* sc
 // ---------------------------------------------------------------------------
 // Deterministic single-block reductions.
 // ---------------------------------------------------------------------------
-// sums[q] = sum_i vals[q * stride + i] for q < Q (each a fixed-order tree).
-__global__ void reduce_sums(const double* __restrict__ vals, int64_t n, int64_t stride, int Q,
-                            double* __restrict__ out) {
+// sums[q] = sum_i vals[q * stride + i], block q (each a fixed-order tree).
+__global__ void reduce_sums(const double* __restrict__ vals, int64_t n, int64_t stride, double* __restrict__ out) {
     __shared__ double sh[1024];
-    for (int q = 0; q < Q; ++q) {
-        double acc = 0.0;
+    vals += blockIdx.x * stride;
+    double acc = 0.0;
 #pragma unroll 8   // independent loads in flight; the sum order is unchanged
-        for (int64_t i = threadIdx.x; i < n; i += blockDim.x) acc += vals[q * stride + i];
-        sh[threadIdx.x] = acc;
-        __syncthreads();
-        for (int o = blockDim.x / 2; o > 0; o >>= 1) {
-            if ((int)threadIdx.x < o) sh[threadIdx.x] += sh[threadIdx.x + o];
-            __syncthreads();
-        }
-        if (threadIdx.x == 0) out[q] = sh[0];
+    for (int64_t i = threadIdx.x; i < n; i += blockDim.x) acc += vals[i];
+    sh[threadIdx.x] = acc;
+    __syncthreads();
+    for (int o = blockDim.x / 2; o > 0; o >>= 1) {
+        if ((int)threadIdx.x < o) sh[threadIdx.x] += sh[threadIdx.x + o];
         __syncthreads();
     }
+    if (threadIdx.x == 0) out[blockIdx.x] = sh[0];
 }
 
 // Check of a marginal by one block of 1024 threads, into out[3]: the sum (fixed order), the first
@@ -1938,19 +1935,41 @@ __global__ void round_col_sums(Consts kc, int D, const double* __restrict__ yc, 
     if (threadIdx.x == 0) S[b] = sh[0];
 }
 
-// t_i = dr_i (C dc)_i and |dr_i| by a pass over all pairs (the l1 / l_inf costs, whose
-// C dc has no closed form): C_ij = -2 s P(x~_i, y~_j).
-__global__ __launch_bounds__(BLOCK) void round_rank_one_pairs(Consts kc, int D, const double* __restrict__ xc,
+// (C dc)_i by a pass over all pairs (the l1 / l_inf costs, whose C dc has no closed form;
+// C_ij = -2 s P(x~_i, y~_j)): part[p][i] = sum of P(x~_i, y~_j) dc_j over column split p, FP64.  One
+// thread a row and a run-time dimension took 14.2 ms for 13378 x 38523 x 3, l1, against 0.3 ms of the
+// other pair passes; split and compiled like them 0.16 ms.
+template <int M, int D>
+__global__ __launch_bounds__(BLOCK) void round_rank_one_pairs(Consts kc, int Dm, OwnPts xs,
                                                               const double* __restrict__ yc,
-                                                              const double* __restrict__ dr,
-                                                              const double* __restrict__ dc, double* __restrict__ t,
-                                                              double* __restrict__ absdr) {
-    const int64_t i = (int64_t)blockIdx.x * BLOCK + threadIdx.x;
+                                                              const double* __restrict__ dc,
+                                                              double* __restrict__ part, int64_t split) {
+    const SweepBlock sb = sweep_block(kc.m, split);
+    const int64_t i = sb.bx * BLOCK + threadIdx.x;
+    if (i >= kc.n) return;
+    const int64_t j1 = min(kc.m, (sb.p + 1) * split);
+    const OwnPoint<M, D> own(xs.p + i * xs.point, xs.coord, Dm, kc);
+    double acc = 0.0;
+    int64_t j = sb.p * split;
+    for (; j + UNROLL <= j1; j += UNROLL) {
+        double dot[UNROLL];
+        own.pairs(yc + j * Dm, dot);
+#pragma unroll
+        for (int u = 0; u < UNROLL; ++u) acc = fma(dot[u], dc[j + u], acc);
+    }
+    for (; j < j1; ++j) acc = fma(own.pair(yc + j * Dm), dc[j], acc);
+    part[sb.p * kc.n + i] = acc;
+}
+
+// t_i = dr_i (C dc)_i and |dr_i| from the splits' sums, in split order.
+__global__ void round_rank_one_merge(Consts kc, int P, const double* __restrict__ dr, const double* __restrict__ part,
+                                     double* __restrict__ t, double* __restrict__ absdr) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= kc.n) return;
     double acc = 0.0;
-    for (int64_t j = 0; j < kc.m; ++j)
-        acc = fma(-2.0 * kc.s * pair_term_dyn(kc, D, xc + i * D, yc + j * D, 0.0), dc[j], acc);
-    t[i] = dr[i] * acc;
+#pragma unroll 8
+    for (int p = 0; p < P; ++p) acc += part[(int64_t)p * kc.n + i];
+    t[i] = dr[i] * (-2.0 * kc.s * acc);
     absdr[i] = fabs(dr[i]);
 }
 
@@ -2238,18 +2257,32 @@ __global__ __launch_bounds__(BLOCK) void norm_sweep(Consts kc, double cA, const 
 // X^t's row data for the column-side adjoint from the splits' (M, Z) at their common offset:
 // sigma_i = M + log2 Z (base 2), k_i = -sigma_i / cfac, so that
 // X_ij = r_i 2^(cfac (k_i + P_ij) + g_j); wA = wB = r_i.
-__global__ void norm_finish(Consts kc, int P, double cA, const double* __restrict__ r,
+// Split partials of a row under their own offsets (o[0] = M_p; -inf: no finite term) at the common
+// offset: 2^(M_p - off) v, exact.
+__device__ __forceinline__ double at_offset(double m, double v, double off) {
+    return m > -__builtin_inf() ? ldexp(v, (int)(m - off)) : 0.0;
+}
+
+// The largest offset of row i's partials (W doubles each).
+__device__ __forceinline__ double common_offset(const double* __restrict__ part, int P, int64_t n, int W, int64_t i) {
+    double off = -__builtin_inf();
+#pragma unroll 16
+    for (int p = 0; p < P; ++p) off = fmax(off, part[((int64_t)p * n + i) * W]);
+    return off;
+}
+
+// The merges run one wave a block, with 16 splits' loads in flight: they are bound by latency, and
+// blocks of 256 rows left most of the chip idle (941 rows of 107 splits: 29 us on 4 CUs).
+__global__ __launch_bounds__(64) void norm_finish(Consts kc, int P, double cA, const double* __restrict__ r,
                             const double* __restrict__ part, RowVar* __restrict__ rowvar) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= kc.n) return;
-    double off = -__builtin_inf();
-#pragma unroll 8
-    for (int p = 0; p < P; ++p) off = fmax(off, part[((int64_t)p * kc.n + i) * 2]);
+    const double off = common_offset(part, P, kc.n, 2, i);
     double z = 0.0;
-#pragma unroll 8
+#pragma unroll 16
     for (int p = 0; p < P; ++p) {
         const double* o = part + ((int64_t)p * kc.n + i) * 2;
-        if (o[0] > -__builtin_inf()) z += ldexp(o[1], (int)(o[0] - off));
+        z += at_offset(o[0], o[1], off);
     }
     RowVar rv;
     rv.k = -(off + log2(z)) / cA;
@@ -2295,21 +2328,17 @@ __global__ __launch_bounds__(BLOCK) void cost_sweep_dyn(Consts kc, int D, double
 
 // Row i's share of the transport cost, s r_i S_C / Z, from the splits' (M, Z, S_C) brought to
 // their common offset (exact powers of two).
-__global__ void cost_finish(Consts kc, int P, const double* __restrict__ r, const double* __restrict__ part,
+__global__ __launch_bounds__(64) void cost_finish(Consts kc, int P, const double* __restrict__ r, const double* __restrict__ part,
                             double* __restrict__ out) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= kc.n) return;
-    double off = -__builtin_inf();
-#pragma unroll 8
-    for (int p = 0; p < P; ++p) off = fmax(off, part[((int64_t)p * kc.n + i) * 3]);
+    const double off = common_offset(part, P, kc.n, 3, i);
     double z = 0.0, c = 0.0;
-#pragma unroll 8
+#pragma unroll 16
     for (int p = 0; p < P; ++p) {
         const double* o = part + ((int64_t)p * kc.n + i) * 3;
-        if (o[0] > -__builtin_inf()) {
-            z += ldexp(o[1], (int)(o[0] - off));
-            c += ldexp(o[2], (int)(o[0] - off));
-        }
+        z += at_offset(o[0], o[1], off);
+        c += at_offset(o[0], o[2], off);
     }
     out[i] = kc.s * r[i] * (c / z);
 }
@@ -2517,47 +2546,41 @@ __global__ __launch_bounds__(BLOCK) void adjoint_y_sweep_dyn(Consts kc, int D, d
     if (j < kc.m) o[0] = s0;
 }
 
-__global__ void adjoint_y_finish(Consts kc, int D, int P, double scale, const double* __restrict__ yc,
-                                 const double* __restrict__ part, float* __restrict__ grad) {
-    int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= kc.m) return;
-    double s0 = 0.0;
-#pragma unroll 8
-    for (int p = 0; p < P; ++p) s0 += part[((int64_t)p * kc.m + j) * (D + 1)];
-    for (int k = 0; k < D; ++k) {
-        double s1 = 0.0;
-#pragma unroll 8
-        for (int p = 0; p < P; ++p) s1 += part[((int64_t)p * kc.m + j) * (D + 1) + 1 + k];
-        grad[j * D + k] = (float)(scale * (s0 * yc[j * D + k] - s1));
+// One thread a coordinate (point e / D, coordinate e % D): neighbouring threads read neighbouring
+// doubles of a partial.
+__global__ __launch_bounds__(64) void adjoint_y_finish(Consts kc, int D, int P, double scale,
+                                                       const double* __restrict__ yc,
+                                                       const double* __restrict__ part, float* __restrict__ grad) {
+    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (e >= kc.m * D) return;
+    const int64_t j = e / D, k = e % D;
+    double s0 = 0.0, s1 = 0.0;
+#pragma unroll 16
+    for (int p = 0; p < P; ++p) {
+        const double* o = part + ((int64_t)p * kc.m + j) * (D + 1);
+        s0 += o[0];
+        s1 += o[1 + k];
     }
+    grad[e] = (float)(scale * (s0 * yc[e] - s1));
 }
 
-__global__ void adjoint_finish(Consts kc, int D, int P, double scale, const double* __restrict__ xc,
-                               const double* __restrict__ r, const double* __restrict__ part,
-                               float* __restrict__ grad) {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= kc.n) return;
+__global__ __launch_bounds__(64) void adjoint_finish(Consts kc, int D, int P, double scale,
+                                                     const double* __restrict__ xc, const double* __restrict__ r,
+                                                     const double* __restrict__ part, float* __restrict__ grad) {
+    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (e >= kc.n * D) return;
+    const int64_t i = e / D, k = e % D;
     const int W = D + 2;
-    double off = -__builtin_inf();
-#pragma unroll 8
-    for (int p = 0; p < P; ++p) off = fmax(off, part[((int64_t)p * kc.n + i) * W]);
-    // split p's sums are scaled by 2^-M_p: bring them to the common offset (exact)
-    double s0 = 0.0;
-#pragma unroll 8
+    const double off = common_offset(part, P, kc.n, W, i);
+    double s0 = 0.0, s1 = 0.0;
+#pragma unroll 16
     for (int p = 0; p < P; ++p) {
         const double* o = part + ((int64_t)p * kc.n + i) * W;
-        if (o[0] > -__builtin_inf()) s0 += ldexp(o[1], (int)(o[0] - off));
+        s0 += at_offset(o[0], o[1], off);
+        s1 += at_offset(o[0], o[2 + k], off);
     }
     const double cx = kc.metric == METRIC_SQEUCLID ? 1.0 : 0.0;
-    for (int k = 0; k < D; ++k) {
-        double s1 = 0.0;
-#pragma unroll 8
-        for (int p = 0; p < P; ++p) {
-            const double* o = part + ((int64_t)p * kc.n + i) * W;
-            if (o[0] > -__builtin_inf()) s1 += ldexp(o[2 + k], (int)(o[0] - off));
-        }
-        grad[i * D + k] = (float)(scale * r[i] * (cx * xc[i * D + k] - s1 / s0));
-    }
+    grad[e] = (float)(scale * r[i] * (cx * xc[e] - s1 / s0));
 }
 
 }  // namespace lampk

@@ -15,7 +15,7 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("n,m,d,kind", [(1, 9, 3, "sqeuclid"), (257, 7, 9, "sqeuclid"), (70, 263, 17, "sqeuclid"),
                                         (300, 129, 19, "sqeuclid"), (65, 90, 131, "sqeuclid"), (40, 77, 9, "l1"),
-                                        (90, 33, 11, "linf")])
+                                        (90, 33, 11, "linf"), (90, 1200, 3, "l1"), (300, 517, 8, "linf")])
 def test_certificate_passes(n, m, d, kind):
     wl = W.random_small(n, m, d, seed=60 + d, eta=1e-2)
     x, y = wl.x.astype(np.float64), wl.y.astype(np.float64)
