@@ -507,6 +507,8 @@ bool valu_dispatch(int d, F&& launch) {
     return false;
 }
 
+constexpr bool has_packed_form(int M, int D) { return D <= 4 || (M == METRIC_SQEUCLID && (D <= 8 || D == 16)); }
+
 // The iteration's sweeps and the offset pass: every dimension up to 16 for the squared Euclidean
 // cost (from 17 on the matrix cores take over), up to 8 for l1 / l_inf.  The compiled form keeps
 // the lane's point in registers and reads the streamed one through scalar loads; the run-time
@@ -830,6 +832,33 @@ void launch_col_sweep(const Layout& L, Consts kc, int d, void* ws, hipStream_t s
         hipLaunchKernelGGL(col_sweep_dyn, g, dim3(BLOCK), 0, st, ctrl, sch, kc, d, xc, yc, gt, rv, ck, part, L.split_c);
 }
 
+// Own points of a run-time pass over n (or m) points, coordinates side by side where the matrix-core
+// operand copies' room (n d doubles or more) is free for them: a wave's loads of a coordinate are one line
+// instead of 64.
+OwnPts own_points(const Layout& L, const double* src, double* room, int64_t len, int d, hipStream_t st) {
+    if (!L.use64) return OwnPts{src, d, 1};
+    hipLaunchKernelGGL(transpose_points, grid1(len * d), dim3(BLOCK), 0, st, src, len, d, room);
+    return OwnPts{room, 1, len};
+}
+
+// The gradient and cost passes of the dimensions without a packed form (valu_dispatch): compiled where
+// the sweeps are, else the run-time form in chunks of up to 32 coordinates, as even as multiples of four
+// allow.  launch(m, dd, kc, chunks, chunk).
+// 4000 x 5000 x 64, gradient in x 20.0 -> 0.81 ms, in y 20.7 -> 0.99, cost 5.3 -> 0.38 (the sums were kept
+// in memory, and every pair loaded both points); x 12 (compiled) 3.4 -> 0.15, 4.7 -> 0.19, 1.6 -> 0.12.
+template <typename F>
+void by_any_dim(int metric, int d, F&& launch) {
+    const bool done = by_metric(metric, [&](auto m) {
+        return sweep_dispatch<decltype(m)::value>(d, [&](auto dd) {
+            constexpr int M = decltype(m)::value, D = decltype(dd)::value;
+            if constexpr (!has_packed_form(M, D)) launch(m, dd, dd, 1, D);
+        });
+    });
+    if (done) return;
+    const int chunks = (int)cdiv(d, 32);
+    launch(IC<-1>{}, IC<0>{}, IC<32>{}, chunks, (int)cdiv(cdiv(d, chunks), 4) * 4);
+}
+
 void launch_adjoint(const Layout& L, Consts kc, int d, void* ws, double cA, const double* gA,
                     hipStream_t st) {
     const dim3 g(sweep_grid(kc.n, L.P_r));
@@ -847,8 +876,13 @@ void launch_adjoint(const Layout& L, Consts kc, int d, void* ws, double cA, cons
                                (const AdjCol<D>*)cols, part, L.split_r);
         });
     });
-    if (!done)
-        hipLaunchKernelGGL(adjoint_sweep_dyn, g, dim3(BLOCK), 0, st, kc, d, cA, xc, yc, ycf, gA, part, L.split_r);
+    if (done) return;
+    by_any_dim(kc.metric, d, [&](auto m, auto dd, auto k, int chunks, int chunk) {
+        constexpr int D = decltype(dd)::value;
+        const OwnPts xs = D > 0 ? OwnPts{xc, d, 1} : own_points(L, xc, at<double>(ws, L.xop64), kc.n, d, st);
+        hipLaunchKernelGGL((adjoint_sweep_any<decltype(m)::value, D, decltype(k)::value>), dim3(g.x, (unsigned)chunks),
+                           dim3(BLOCK), 0, st, kc, d, chunk, cA, xs, yc, gA, part, L.split_r);
+    });
 }
 
 // <C, X^t> in one pass over the pairs: per row the split sums (M, Z, S_C), then s r_i S_C / Z
@@ -872,7 +906,12 @@ void launch_cost(const Layout& L, Consts kc, int d, void* ws, double cA, const d
         });
     });
     if (!done)
-        hipLaunchKernelGGL(cost_sweep_dyn, g, dim3(BLOCK), 0, st, kc, d, cA, xc, yc, xn2, yn2, gA, part, L.split_r);
+        by_any_dim(kc.metric, d, [&](auto m, auto dd, auto, int, int) {
+            constexpr int D = decltype(dd)::value;
+            const OwnPts xs = D > 0 ? OwnPts{xc, d, 1} : own_points(L, xc, at<double>(ws, L.xop64), kc.n, d, st);
+            hipLaunchKernelGGL((cost_sweep_any<decltype(m)::value, D>), g, dim3(BLOCK), 0, st, kc, d, cA, xs, yc, xn2,
+                               yn2, gA, part, L.split_r);
+        });
     hipLaunchKernelGGL(cost_finish, wave_grid(kc.n), dim3(64), 0, st, kc, (int)L.P_r, r, (const double*)part, rows);
     hipLaunchKernelGGL(reduce_sums, dim3(1), dim3(1024), 0, st, (const double*)rows, kc.n, kc.n, out);
 }
@@ -2347,8 +2386,13 @@ lamp_status lamp_backward_y(const lamp_problem* prob, const lamp_params* params,
         });
     });
     if (!done)
-        hipLaunchKernelGGL(adjoint_y_sweep_dyn, g, dim3(BLOCK), 0, st, kc, d, cA, xc, xcf, yc, gA, rv, part,
-                           L.split_c);
+        by_any_dim(kc.metric, d, [&](auto mm, auto dd, auto k, int chunks, int chunk) {
+            constexpr int D = decltype(dd)::value;
+            const OwnPts ys = D > 0 ? OwnPts{yc, d, 1} : own_points(L, yc, at<double>(ws, L.yop64), kc.m, d, st);
+            hipLaunchKernelGGL((adjoint_y_sweep_any<decltype(mm)::value, D, decltype(k)::value>),
+                               dim3(g.x, (unsigned)chunks), dim3(BLOCK), 0, st, kc, d, chunk, cA, ys, xc,
+                               (const double*)gA, rv, part, L.split_c);
+        });
     hipLaunchKernelGGL(adjoint_y_finish, wave_grid(kc.m * d), dim3(64), 0, st, kc, d, (int)L.P_c, grad_out * 2.0 * R.s,
                        yc, part, grad_y);
     HIPCHK(hipGetLastError());

@@ -1518,6 +1518,7 @@ struct OwnPoint {
 #pragma unroll
         for (int k = 0; k < D; ++k) x[k] = src[k];
     }
+    __device__ __forceinline__ double at(int k) const { return x[k]; }
     __device__ __forceinline__ double pair(const double* __restrict__ y) const { return pair_term<M, D>(x, y, 0.0); }
     __device__ __forceinline__ void pairs(const double* __restrict__ y, double (&out)[UNROLL]) const {
 #pragma unroll
@@ -1533,6 +1534,7 @@ struct OwnPoint<-1, 0> {
     const Consts& kc;
     __device__ __forceinline__ OwnPoint(const double* __restrict__ src, int64_t stride_, int d_, const Consts& kc_)
         : x(src), stride(stride_), d(d_), kc(kc_) {}
+    __device__ __forceinline__ double at(int k) const { return x[k * stride]; }
     __device__ __forceinline__ double pair(const double* __restrict__ y) const {
         if (kc.metric == METRIC_EXPLICIT) return pair_term_cost(kc, x[0], y[0], 0.0);
         double a = 0.0;
@@ -2290,9 +2292,42 @@ __global__ __launch_bounds__(64) void norm_finish(Consts kc, int P, double cA, c
     rowvar[i] = rv;
 }
 
-// The transport cost for any dimension and metric at run time, FP64 sums.  part as above.
-__global__ __launch_bounds__(BLOCK) void cost_sweep_dyn(Consts kc, int D, double cA,
-                                                        const double* __restrict__ xc,
+// Rows' weighted sums for the dimensions without a packed form above: weights q_ij = 2^(e_ij - M) under
+// the lane's running integer offset M, every sum FP64.  term(q, dot, j) takes the weights and pair terms
+// of UNROLL streamed points from j (or one); rescale(sh) multiplies the sums by 2^sh (exact).
+template <typename Own, typename Rescale, typename Term>
+__device__ __forceinline__ double offset_weights(const Own& own, int Dm, double cA, const double* __restrict__ yc,
+                                                 const double* __restrict__ gA, int64_t j0, int64_t j1,
+                                                 Rescale&& rescale, Term&& term) {
+    double off = -__builtin_inf();
+    auto run = [&](auto cnt, int64_t j) {
+        constexpr int U = decltype(cnt)::value;
+        double dot[U], q[U], top = -__builtin_inf();
+        if constexpr (U == 1) dot[0] = own.pair(yc + j * Dm);
+        else own.pairs(yc + j * Dm, dot);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            q[u] = fma(cA, dot[u], gA[j + u]);
+            top = fmax(top, q[u]);
+        }
+        if (top > off) {   // raise the offset to the next integer
+            const double nm = ceil(top);
+            if (off > -__builtin_inf()) rescale((int)(off - nm));
+            off = nm;
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) q[u] = (double)fexp2(q[u] - off);
+        term(q, dot, j);
+    };
+    int64_t j = j0;
+    for (; j + UNROLL <= j1; j += UNROLL) run(std::integral_constant<int, UNROLL>{}, j);
+    for (; j < j1; ++j) run(std::integral_constant<int, 1>{}, j);
+    return off;
+}
+
+// The transport cost.  part as above.
+template <int M, int D>
+__global__ __launch_bounds__(BLOCK) void cost_sweep_any(Consts kc, int Dm, double cA, OwnPts xs,
                                                         const double* __restrict__ yc,
                                                         const double* __restrict__ xn2,
                                                         const double* __restrict__ yn2,
@@ -2300,27 +2335,26 @@ __global__ __launch_bounds__(BLOCK) void cost_sweep_dyn(Consts kc, int D, double
                                                         double* __restrict__ part, int64_t split) {
     const SweepBlock sb = sweep_block(kc.m, split);
     const int64_t i = sb.bx * BLOCK + threadIdx.x;
-    const int64_t p = sb.p;
-    const int64_t j0 = p * split;
-    const int64_t j1 = min(kc.m, j0 + split);
     if (i >= kc.n) return;
-    const double* xi = xc + i * D;
-    double off = -__builtin_inf(), s0 = 0.0, sc = 0.0;
-    for (int64_t j = j0; j < j1; ++j) {
-        const double pij = pair_term_dyn(kc, D, xi, yc + j * D, 0.0);
-        const double e = fma(cA, pij, gA[j]);
-        if (e > off) {   // raise the offset to ceil(e), rescaling the sums exactly
-            const double nm = ceil(e);
-            const int sh = j == j0 ? 0 : (int)(off - nm);
+    const int64_t j0 = sb.p * split;
+    const OwnPoint<M, D> own(xs.p + i * xs.point, xs.coord, Dm, kc);
+    const double x2 = xn2[i];
+    double s0 = 0.0, sc = 0.0;
+    const double off = offset_weights(
+        own, Dm, cA, yc, gA, j0, min(kc.m, j0 + split),
+        [&](int sh) {
             s0 = ldexp(s0, sh);
             sc = ldexp(sc, sh);
-            off = nm;
-        }
-        const double q = (double)fexp2(e - off);
-        s0 += q;
-        sc += q * fma(-2.0, pij, xn2[i] + yn2[j]);
-    }
-    double* o = part + (p * kc.n + i) * 3;
+        },
+        [&](const auto& q, const auto& dot, int64_t j) {
+            constexpr int U = sizeof(q) / sizeof(double);
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                s0 += q[u];
+                sc += q[u] * fma(-2.0, dot[u], x2 + yn2[j + u]);
+            }
+        });
+    double* o = part + (sb.p * kc.n + i) * 3;
     o[0] = off;
     o[1] = s0;
     o[2] = sc;
@@ -2343,53 +2377,110 @@ __global__ __launch_bounds__(64) void cost_finish(Consts kc, int P, const double
     out[i] = kc.s * r[i] * (c / z);
 }
 
-__global__ __launch_bounds__(BLOCK) void adjoint_sweep_dyn(Consts kc, int D, double cA,
-                                                           const double* __restrict__ xc,
+// Adds the derivatives of U streamed points from y in the coordinates c0 + k, k < nc <= KC, to s[k] with
+// their weights w_u >= 0: w_u y_k for the squared Euclidean cost, w_u / 2 sgn(y_k - x_k) for l1, the
+// same on the coordinate of the largest |x_k - y_k| (the first on ties) for l_inf; FP64.
+template <int D, int KC, int U, typename Own>
+__device__ __forceinline__ void add_derivatives(int metric, int Dm, int c0, int nc, const double (&w)[U],
+                                                const Own& own, const double* __restrict__ y, double (&s)[KC]) {
+    if (metric == METRIC_SQEUCLID) {
+#pragma unroll
+        for (int k = 0; k < KC; k += 4) {
+            if constexpr (D == 0) __builtin_amdgcn_sched_barrier(0);   // one block's scalar loads in flight
+            if (k + 4 <= nc) {                   // uniform
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+#pragma unroll
+                    for (int v = k; v < k + 4 && v < KC; ++v) s[v] = fma(w[u], y[u * Dm + c0 + v], s[v]);
+            } else {
+#pragma unroll
+                for (int v = k; v < k + 4 && v < KC; ++v)
+                    if (v < nc)
+#pragma unroll
+                        for (int u = 0; u < U; ++u) s[v] = fma(w[u], y[u * Dm + c0 + v], s[v]);
+            }
+        }
+        return;
+    }
+    int ks[U];
+    if (metric == METRIC_LINF) {
+        double best[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            ks[u] = 0;
+            best[u] = -1.0;
+        }
+        auto scan = [&](int k) {
+            const double xk = own.at(k);
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const double t = fabs(xk - y[u * Dm + k]);
+                if (t > best[u]) {
+                    best[u] = t;
+                    ks[u] = k;
+                }
+            }
+        };
+        if constexpr (D > 0) {
+#pragma unroll
+            for (int k = 0; k < D; ++k) scan(k);
+        } else {
+            for (int k = 0; k < Dm; ++k) scan(k);
+        }
+    }
+#pragma unroll
+    for (int v = 0; v < KC; ++v) {
+        if constexpr (D == 0) __builtin_amdgcn_sched_barrier(0);
+        if (v >= nc) continue;   // uniform
+        const double xk = own.at(c0 + v);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const double t = y[u * Dm + c0 + v] - xk;
+            const bool on = metric == METRIC_L1 || ks[u] == c0 + v;
+            s[v] += on && t != 0.0 ? copysign(0.5 * w[u], t) : 0.0;
+        }
+    }
+}
+
+// The gradient sums for the dimensions without a packed form: KC of them a block (blockIdx.y the chunk),
+// in registers.  The run-time form (M = -1, D = 0) recomputes the weights for every chunk of at most
+// 32 coordinates.  part as adjoint_sweep's.
+template <int M, int D, int KC>
+__global__ __launch_bounds__(BLOCK) void adjoint_sweep_any(Consts kc, int Dm, int chunk, double cA, OwnPts xs,
                                                            const double* __restrict__ yc,
-                                                           const float* __restrict__ ycf,
                                                            const double* __restrict__ gA,
                                                            double* __restrict__ part, int64_t split) {
     const SweepBlock sb = sweep_block(kc.m, split);
     const int64_t i = sb.bx * BLOCK + threadIdx.x;
-    const int64_t p = sb.p;
-    const int64_t j0 = p * split;
-    const int64_t j1 = min(kc.m, j0 + split);
     if (i >= kc.n) return;
-    const double* xi = xc + i * D;
-    double* o = part + (p * kc.n + i) * (D + 2);
-    for (int k = 0; k < D; ++k) o[2 + k] = 0.0;
-    double off = -__builtin_inf(), s0 = 0.0;
-    for (int64_t j = j0; j < j1; ++j) {
-        const double* yj = yc + j * D;
-        double e = fma(cA, pair_term_dyn(kc, D, xi, yj, 0.0), gA[j]);
-        if (e > off) {   // raise the offset to ceil(e), rescaling the sums exactly
-            const double nm = ceil(e);
-            const int sh = j == j0 ? 0 : (int)(off - nm);
+    const int64_t j0 = sb.p * split;
+    const int c0 = D > 0 ? 0 : (int)blockIdx.y * chunk, nc = D > 0 ? D : min(chunk, Dm - c0);
+    const int metric = D > 0 ? M : kc.metric;
+    const OwnPoint<M, D> own(xs.p + i * xs.point, xs.coord, Dm, kc);
+    double s0 = 0.0, s1[KC];
+#pragma unroll
+    for (int k = 0; k < KC; ++k) s1[k] = 0.0;
+    const double off = offset_weights(
+        own, Dm, cA, yc, gA, j0, min(kc.m, j0 + split),
+        [&](int sh) {
             s0 = ldexp(s0, sh);
-            for (int k = 0; k < D; ++k) o[2 + k] = ldexp(o[2 + k], sh);
-            off = nm;
-        }
-        const double q = (double)fexp2(e - off);
-        s0 += q;
-        if (kc.metric == METRIC_SQEUCLID) {
-            for (int k = 0; k < D; ++k) o[2 + k] += q * (double)ycf[j * D + k];
-        } else if (kc.metric == METRIC_L1) {
-            for (int k = 0; k < D; ++k) o[2 + k] += -0.5 * q * (double)sgnf(xi[k] - yj[k]);
-        } else {
-            int ks = 0;
-            double best = -1.0;
-            for (int k = 0; k < D; ++k) {
-                const double t = fabs(xi[k] - yj[k]);
-                if (t > best) {
-                    best = t;
-                    ks = k;
-                }
-            }
-            o[2 + ks] += -0.5 * q * (double)sgnf(xi[ks] - yj[ks]);
-        }
+#pragma unroll
+            for (int k = 0; k < KC; ++k) s1[k] = ldexp(s1[k], sh);
+        },
+        [&](const auto& q, const auto&, int64_t j) {
+            constexpr int U = sizeof(q) / sizeof(double);
+#pragma unroll
+            for (int u = 0; u < U; ++u) s0 += q[u];
+            add_derivatives<D, KC, U>(metric, Dm, c0, nc, q, own, yc + j * Dm, s1);
+        });
+    double* o = part + (sb.p * kc.n + i) * (Dm + 2);
+    if (c0 == 0) {
+        o[0] = off;
+        o[1] = s0;
     }
-    o[0] = off;
-    o[1] = s0;
+#pragma unroll
+    for (int k = 0; k < KC; ++k)
+        if (k < nc) o[2 + c0 + k] = s1[k];
 }
 
 // ---------------------------------------------------------------------------
@@ -2500,50 +2591,46 @@ __global__ __launch_bounds__(BLOCK) void adjoint_y_sweep(Consts kc, double cA, c
     }
 }
 
-__global__ __launch_bounds__(BLOCK) void adjoint_y_sweep_dyn(Consts kc, int D, double cA,
+// The same for the dimensions without a packed form, chunks as in adjoint_sweep_any: the coupling's terms
+// X_ij = w_i 2^(cfac (k_i + P_ij) + g_j), every sum FP64.
+template <int M, int D, int KC>
+__global__ __launch_bounds__(BLOCK) void adjoint_y_sweep_any(Consts kc, int Dm, int chunk, double cA, OwnPts ys,
                                                              const double* __restrict__ xc,
-                                                             const float* __restrict__ xcf,
-                                                             const double* __restrict__ yc,
                                                              const double* __restrict__ gA,
                                                              const RowVar* __restrict__ rowvar,
                                                              double* __restrict__ part, int64_t split) {
     const SweepBlock sb = sweep_block(kc.n, split);
     const int64_t j = sb.bx * BLOCK + threadIdx.x;
-    const int64_t p = sb.p;
-    const int64_t i0 = p * split;
-    const int64_t i1 = min(kc.n, i0 + split);
-    const int64_t jj = j < kc.m ? j : kc.m - 1;
-    const double* yj = yc + jj * D;
-    const double g = gA[jj];
-    double* o = part + (p * kc.m + jj) * (D + 1);
-    double s0 = 0.0;
-    if (j < kc.m)
-        for (int k = 0; k < D; ++k) o[1 + k] = 0.0;
-    for (int64_t i = i0; i < i1; ++i) {
-        const RowVar rv = rowvar[i];
-        const double* xi = xc + i * D;
-        const double xij = (double)rv.wA * (double)fexp2(fma(cA, pair_term_dyn(kc, D, yj, xi, rv.k), g));
-        if (kc.metric == METRIC_SQEUCLID) {
-            s0 += xij;
-            if (j < kc.m)
-                for (int k = 0; k < D; ++k) o[1 + k] += xij * (double)xcf[i * D + k];
-        } else if (kc.metric == METRIC_L1) {
-            if (j < kc.m)
-                for (int k = 0; k < D; ++k) o[1 + k] += 0.5 * xij * (double)sgnf(xi[k] - yj[k]);
-        } else {
-            int ks = 0;
-            double best = -1.0;
-            for (int k = 0; k < D; ++k) {
-                const double t = fabs(xi[k] - yj[k]);
-                if (t > best) {
-                    best = t;
-                    ks = k;
-                }
-            }
-            if (j < kc.m) o[1 + ks] += 0.5 * xij * (double)sgnf(xi[ks] - yj[ks]);
+    if (j >= kc.m) return;
+    const int64_t i1 = min(kc.n, (sb.p + 1) * split);
+    const int c0 = D > 0 ? 0 : (int)blockIdx.y * chunk, nc = D > 0 ? D : min(chunk, Dm - c0);
+    const int metric = D > 0 ? M : kc.metric;
+    const OwnPoint<M, D> own(ys.p + j * ys.point, ys.coord, Dm, kc);
+    const double g = gA[j];
+    double s0 = 0.0, s1[KC];
+#pragma unroll
+    for (int k = 0; k < KC; ++k) s1[k] = 0.0;
+    auto run = [&](auto cnt, int64_t i) {
+        constexpr int U = decltype(cnt)::value;
+        double w[U];
+        if constexpr (U == 1) w[0] = own.pair(xc + i * Dm);
+        else own.pairs(xc + i * Dm, w);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const RowVar rv = rowvar[i + u];
+            w[u] = (double)rv.wA * (double)fexp2(fma(cA, rv.k + w[u], g));
+            if (metric == METRIC_SQEUCLID) s0 += w[u];
         }
-    }
-    if (j < kc.m) o[0] = s0;
+        add_derivatives<D, KC, U>(metric, Dm, c0, nc, w, own, xc + i * Dm, s1);
+    };
+    int64_t i = sb.p * split;
+    for (; i + UNROLL <= i1; i += UNROLL) run(std::integral_constant<int, UNROLL>{}, i);
+    for (; i < i1; ++i) run(std::integral_constant<int, 1>{}, i);
+    double* o = part + (sb.p * kc.m + j) * (Dm + 1);
+    if (c0 == 0) o[0] = s0;
+#pragma unroll
+    for (int k = 0; k < KC; ++k)
+        if (k < nc) o[1 + c0 + k] = s1[k];
 }
 
 // One thread a coordinate (point e / D, coordinate e % D): neighbouring threads read neighbouring
