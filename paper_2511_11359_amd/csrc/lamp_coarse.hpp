@@ -235,14 +235,12 @@ __global__ __launch_bounds__(BLOCK, 2) void row_extreme_coarse(Consts kc, int d,
         }
     }
 #pragma unroll
-    for (int u = 0; u < RT; ++u)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-#pragma unroll
-            for (int o = 8; o > 0; o >>= 1) best[u][r] = fmin(best[u][r], __shfl_xor(best[u][r], o, 64));
-            const int64_t row = (rt0 + u) * 16 + (PICK ? 4 * r + grp : 4 * grp + r);
-            if (c16 == r && row < kc.n && rt0 + u < n_tiles) part[(int64_t)p * kc.n + row] = best[u][r];
-        }
+    for (int u = 0; u < RT; ++u) {
+        reduce_lanes<4, 8>(best[u], [](double x, double y) { return fmin(x, y); });
+        const int r = c16 >> 2;
+        const int64_t row = (rt0 + u) * 16 + (PICK ? 4 * r + grp : 4 * grp + r);
+        if (c16 % 4 == 0 && row < kc.n && rt0 + u < n_tiles) part[(int64_t)p * kc.n + row] = best[u][0];
+    }
 }
 
 // The row tiles that can hold the largest value xn2_i - 2 min_i: some row's coarse value (rowmax)

@@ -58,6 +58,49 @@ constexpr float PAD_NEG = -1e30f;   // exponent of padded entries: 2^PAD_NEG = 0
 
 __device__ __forceinline__ int mfma_row(int r, int hf) { return 8 * (r >> 2) + 4 * hf + (r & 3); }
 
+// The value of lane ^ O (O < 16: within a DPP row; xor 4 is a mirror of eight, xor 7, after xor 3).
+template <int O>
+__device__ __forceinline__ int lane_xor(int v) {
+    if constexpr (O == 8) return __builtin_amdgcn_mov_dpp(v, 0x128, 0xf, 0xf, true);   // row_ror:8
+    else if constexpr (O == 4)
+        return __builtin_amdgcn_mov_dpp(__builtin_amdgcn_mov_dpp(v, 0x1b, 0xf, 0xf, true), 0x141, 0xf, 0xf, true);
+    else if constexpr (O == 2) return __builtin_amdgcn_mov_dpp(v, 0x4e, 0xf, 0xf, true);   // quad_perm 2,3,0,1
+    else return __builtin_amdgcn_mov_dpp(v, 0xb1, 0xf, 0xf, true);                          // quad_perm 1,0,3,2
+}
+template <int O>
+__device__ __forceinline__ float lane_xor(float v) { return __int_as_float(lane_xor<O>(__float_as_int(v))); }
+template <int O>
+__device__ __forceinline__ double lane_xor(double v) {
+    return __hiloint2double(lane_xor<O>(__double2hiint(v)), lane_xor<O>(__double2loint(v)));
+}
+
+// Reduces each of the R values over the lanes that differ in the bits O, O/2, ..., 1 by the tree
+// v <- op(v, value of lane ^ O), O descending.  While there are several values a step hands half of them to
+// the partner, so that the lane ends with one: number (lane & (2 O - 1)) / (2 O / R), in v[0].  The pairs of
+// every addition are those of R full butterflies, so the sums keep every bit; 16 values over 32 lanes take
+// 16 exchanges instead of 80 LDS permutes (with two couplings these were 20 us of a 4096 x 4096 sweep's 36).
+template <int R, int O, typename V, typename F>
+__device__ __forceinline__ void reduce_lanes(V* v, F&& op) {
+    const int lane = threadIdx.x & 63;
+    if constexpr (R > 1) {
+#pragma unroll
+        for (int u = 0; u < R / 2; ++u) {
+            if constexpr (O == 16 && std::is_same_v<V, float>) {
+                const auto x = __builtin_amdgcn_permlane16_swap(__float_as_uint(v[u]), __float_as_uint(v[u + R / 2]),
+                                                                false, false);
+                v[u] = op(__uint_as_float(x[0]), __uint_as_float(x[1]));
+            } else {
+                const V keep = lane & O ? v[u + R / 2] : v[u];
+                const V send = lane & O ? v[u] : v[u + R / 2];
+                v[u] = op(keep, lane_xor<O>(send));
+            }
+        }
+    } else {
+        v[0] = op(v[0], lane_xor<O>(v[0]));
+    }
+    if constexpr (O > 1) reduce_lanes<(R > 1 ? R / 2 : 1), O / 2>(v, op);
+}
+
 // Operand copies: out[i][k] = T(x~[i][k]) for k < d, 0 for k >= d or i >= cnt.
 template <typename T>
 __global__ void prep_operands(const double* __restrict__ src, int64_t cnt, int d, int KP, int64_t cnt_pad,
@@ -200,16 +243,9 @@ __global__ __launch_bounds__(BLOCK) void row_extreme_mfma64(Consts kc, const dou
 #pragma unroll
         for (int q = 0; q < 4; ++q) best[q] = fmin(best[q], aval + d[q]);
     }
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-#pragma unroll
-        for (int o = 8; o > 0; o >>= 1) best[q] = fmin(best[q], __shfl_xor(best[q], o, 64));
-    }
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const int64_t row = i0 + 4 * q + grp;
-        if (c16 == q && row < kc.n) part[(int64_t)p * kc.n + row] = best[q];
-    }
+    reduce_lanes<4, 8>(best, [](double x, double y) { return fmin(x, y); });
+    const int64_t row = i0 + 4 * (c16 >> 2) + grp;
+    if (c16 % 4 == 0 && row < kc.n) part[(int64_t)p * kc.n + row] = best[0];
 }
 
 // ---------------------------------------------------------------------------
@@ -533,19 +569,11 @@ __global__ __launch_bounds__(BLOCK, (row_sweep_min_waves<T, KP>())) void row_swe
         }
     }
     if (!active) return;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-#pragma unroll
-        for (int o = 16; o > 0; o >>= 1) {
-            accA[r] += __shfl_xor(accA[r], o, 64);
-            accB[r] += __shfl_xor(accB[r], o, 64);
-        }
-    }
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-        const int64_t row = i0 + mfma_row(r, hf);
-        if (c32 == r && row < kc.n) part[(int64_t)p * kc.n + row] = make_double2(accA[r], accB[r]);
-    }
+    auto add = [](float x, float y) { return x + y; };
+    reduce_lanes<16, 16>(accA, add);
+    reduce_lanes<16, 16>(accB, add);
+    const int64_t row = i0 + mfma_row(c32 >> 1, hf);
+    if (c32 % 2 == 0 && row < kc.n) part[(int64_t)p * kc.n + row] = make_double2(accA[0], accB[0]);
 }
 
 // Offsets of the matrix-core forms: part[p][i] = -max_j (c^B x~_i . y~_j + g^B_j) / c^B over
@@ -607,16 +635,9 @@ __global__ __launch_bounds__(BLOCK) void row_extreme_mfma_lds(const Ctrl* ctrl, 
         __syncthreads();
     }
     if (!active) return;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-#pragma unroll
-        for (int o = 16; o > 0; o >>= 1) mx[r] = fmaxf(mx[r], __shfl_xor(mx[r], o, 64));
-    }
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-        const int64_t row = i0 + mfma_row(r, hf);
-        if (c32 == r && row < kc.n) part[(int64_t)p * kc.n + row] = -(double)mx[r] / (double)cB;
-    }
+    reduce_lanes<16, 16>(mx, [](float x, float y) { return fmaxf(x, y); });
+    const int64_t row = i0 + mfma_row(c32 >> 1, hf);
+    if (c32 % 2 == 0 && row < kc.n) part[(int64_t)p * kc.n + row] = -(double)mx[0] / (double)cB;
 }
 
 // Column sweep of the matrix-core forms with the roles of the operands swapped, LDS-shared
@@ -776,19 +797,11 @@ __global__ __launch_bounds__(BLOCK) void col_sweep_mfma_t_lds(const Ctrl* ctrl, 
         }
     }
     if (!active) return;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-#pragma unroll
-        for (int o = 16; o > 0; o >>= 1) {
-            accA[r] += __shfl_xor(accA[r], o, 64);
-            accB[r] += __shfl_xor(accB[r], o, 64);
-        }
-    }
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-        const int64_t j = j0 + mfma_row(r, hf);
-        if (c32 == r && j < kc.m) cpart[(int64_t)p * kc.m + j] = make_double2(accA[r], accB[r]);
-    }
+    auto add = [](float x, float y) { return x + y; };
+    reduce_lanes<16, 16>(accA, add);
+    reduce_lanes<16, 16>(accB, add);
+    const int64_t j = j0 + mfma_row(c32 >> 1, hf);
+    if (c32 % 2 == 0 && j < kc.m) cpart[(int64_t)p * kc.m + j] = make_double2(accA[0], accB[0]);
 }
 
 // FP64 matrix-core sweeps with LDS-shared tiles of 16 points (see the LDS-shared
@@ -1000,20 +1013,15 @@ __device__ __forceinline__ void row_sweep_mfma64_body(const Ctrl* ctrl, const Sc
         sumA[q] += (double)accA[q];
         sumB[q] += (double)accB[q];
         if constexpr (DT) sumT[q] += (double)accT[q];
-#pragma unroll
-        for (int o = 8; o > 0; o >>= 1) {
-            sumA[q] += __shfl_xor(sumA[q], o, 64);
-            sumB[q] += __shfl_xor(sumB[q], o, 64);
-            if constexpr (DT) sumT[q] += __shfl_xor(sumT[q], o, 64);
-        }
     }
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const int64_t row = i0 + 4 * q + grp;
-        if (c16 == q && row < kc.n) {
-            part[(int64_t)p * kc.n + row] = make_double2(sumA[q], sumB[q]);
-            if constexpr (DT) tpart[(int64_t)p * kc.n + row] = sumT[q];
-        }
+    auto add = [](double x, double y) { return x + y; };
+    reduce_lanes<4, 8>(sumA, add);
+    reduce_lanes<4, 8>(sumB, add);
+    if constexpr (DT) reduce_lanes<4, 8>(sumT, add);
+    const int64_t row = i0 + 4 * (c16 >> 2) + grp;
+    if (c16 % 4 == 0 && row < kc.n) {
+        part[(int64_t)p * kc.n + row] = make_double2(sumA[0], sumB[0]);
+        if constexpr (DT) tpart[(int64_t)p * kc.n + row] = sumT[0];
     }
 }
 
