@@ -634,23 +634,43 @@ void launch_row_extreme(const Layout& L, Consts kc, int d, void* ws, const doubl
     if (!done) hipLaunchKernelGGL(row_extreme_dyn, g, dim3(BLOCK), 0, st, kc, d, xc, yc, a, sgn, part, L.split_r);
 }
 
+// Splits a block of a matrix-core sweep takes one after another: enough for 8 tiles, at most 4, and not
+// below 1024 blocks.  Row / column sweep, BF16, d = 4, by 1, 2, 4, 8 splits: 4096 x 4096 (1 tile a split)
+// 21.7 / 25.7, 16.3 / 18.9, 14.2 / 15.2, 14.3 / 14.7 us; 8192 x 8192 (2) 32.0 / 36.8, 28.7 / 30.9,
+// 27.0 / 28.8, 29.4 / 30.3; 38568 x 4980 (5) 61 / 65, 60 / 63, 61 / 68, 74 / 82; 16384 x 16384 (8)
+// 76 / 84, 76 / 81, 76 / 80, 86 / 89.
+int splits_per_block(int64_t owned_blocks, int64_t P, int64_t tiles_per_split) {
+    return (int)std::max<int64_t>(1, std::min<int64_t>({4, cdiv(8, tiles_per_split), owned_blocks * P / 1024}));
+}
+
 template <typename T, int KP>
 void row_mfma(const Layout& L, Consts kc, void* ws, hipStream_t st) {
-    const int64_t n_waves = L.n_pad / 32;
-    dim3 g((unsigned)(cdiv(n_waves, 4) * L.P_rm));
-    hipLaunchKernelGGL((row_sweep_mfma_lds<T, KP>), g, dim3(BLOCK), 0, st, at<Ctrl>(ws, L.ctrl), at<Sched>(ws, L.sched),
-                       kc, at<T>(ws, L.xop), at<T>(ws, L.yop), at<float2>(ws, L.gtabf), L.m_pad, at<double>(ws, L.H),
-                       at<double2>(ws, L.rpart), L.tps_r, (int)L.P_rm, L.m_pad / 32, n_waves);
+    const int64_t n_waves = L.n_pad / 32, blocks = cdiv(n_waves, 4);
+    const int G = splits_per_block(blocks, L.P_rm, L.tps_r);
+    auto launch = [&](auto runs) {
+        hipLaunchKernelGGL((row_sweep_mfma_lds<T, KP, decltype(runs)::value>),
+                           dim3((unsigned)(blocks * cdiv(L.P_rm, G))), dim3(BLOCK), 0, st, at<Ctrl>(ws, L.ctrl),
+                           at<Sched>(ws, L.sched), kc, at<T>(ws, L.xop), at<T>(ws, L.yop), at<float2>(ws, L.gtabf),
+                           L.m_pad, at<double>(ws, L.H), at<double2>(ws, L.rpart), L.tps_r, (int)L.P_rm, G,
+                           L.m_pad / 32, n_waves);
+    };
+    if (G > 1) launch(std::true_type{});
+    else launch(std::false_type{});
 }
 
 template <typename T, int KP>
 void col_mfma(const Layout& L, Consts kc, void* ws, hipStream_t st) {
-    const int64_t m_waves = L.m_pad / 32;
-    dim3 g((unsigned)(cdiv(m_waves, 4) * L.P_cm));
-    hipLaunchKernelGGL((col_sweep_mfma_t_lds<T, KP>), g, dim3(BLOCK), 0, st, at<Ctrl>(ws, L.ctrl),
-                       at<Sched>(ws, L.sched), kc, at<T>(ws, L.xop), at<T>(ws, L.yop), at<float2>(ws, L.gtabf),
-                       L.m_pad, at<float4>(ws, L.rowq), at<double2>(ws, L.cpart), L.tps_c, (int)L.P_cm,
-                       L.n_pad / 32, m_waves);
+    const int64_t m_waves = L.m_pad / 32, blocks = cdiv(m_waves, 4);
+    const int G = splits_per_block(blocks, L.P_cm, L.tps_c);
+    auto launch = [&](auto runs) {
+        hipLaunchKernelGGL((col_sweep_mfma_t_lds<T, KP, decltype(runs)::value>),
+                           dim3((unsigned)(blocks * cdiv(L.P_cm, G))), dim3(BLOCK), 0, st, at<Ctrl>(ws, L.ctrl),
+                           at<Sched>(ws, L.sched), kc, at<T>(ws, L.xop), at<T>(ws, L.yop), at<float2>(ws, L.gtabf),
+                           L.m_pad, at<float4>(ws, L.rowq), at<double2>(ws, L.cpart), L.tps_c, (int)L.P_cm, G,
+                           L.n_pad / 32, m_waves);
+    };
+    if (G > 1) launch(std::true_type{});
+    else launch(std::false_type{});
 }
 
 template <bool ROW>

@@ -460,10 +460,23 @@ __device__ __forceinline__ floatx16 tile_dot(const char* lds, int c32, int hf,
     return d;
 }
 
-// Row sweep: wave w of block b owns rows [32 rw, 32 rw + 32), rw = (b / P) * 4 + w,
-// and streams column tiles of split p = b mod P (P a multiple of 8 maps each split to
-// one XCD, whose L2 then holds that split's operand rows).
-// LDS-shared column tiles (see above).
+// RUNS: a block takes G consecutive splits of the P (the split count, and with it the order of every
+// sum, is the layout's): it streams their tiles as one range and writes each split's sums at its end,
+// so that the operands, offsets and first tiles are loaded once for G splits.  Without RUNS G is 1: the
+// test for a split's end costs the loop over long splits up to 10% (65536 x 65536, d = 64).
+struct SplitRun {
+    int first, tile0, tile1;   // its first split and its tiles
+    int64_t owned;             // index among the blocks of owned points
+};
+__device__ __forceinline__ SplitRun split_run(int P, int G, int64_t tiles_per_split, int64_t tiles) {
+    const unsigned runs = (unsigned)((P + G - 1) / G), q = blockIdx.x % runs;
+    const int64_t t0 = (int64_t)q * G * tiles_per_split;
+    return SplitRun{(int)q * G, (int)t0, (int)min(tiles, t0 + G * tiles_per_split), (int64_t)(blockIdx.x / runs)};
+}
+
+// Row sweep: wave w of a block owns rows [32 rw, 32 rw + 32), rw = 4 owned + w, and streams the column
+// tiles of the block's splits (a multiple of 8 runs maps each to one XCD, whose L2 then holds their
+// operand rows).  LDS-shared column tiles (see above).
 // Waves per SIMD the register allocation of row_sweep_mfma_lds must allow: three for the
 // half-precision forms up to 64 coordinates (their loop fits 168 registers without
 // spilling; the compiler's own choice is a few registers above, i.e. two waves).
@@ -472,13 +485,13 @@ constexpr int row_sweep_min_waves() {
     return (sizeof(T) == 2 && KP <= 64) ? 3 : 1;
 }
 
-template <typename T, int KP>
+template <typename T, int KP, bool RUNS>
 __global__ __launch_bounds__(BLOCK, (row_sweep_min_waves<T, KP>())) void row_sweep_mfma_lds(const Ctrl* ctrl, const Sched* sched, Consts kc,
                                                             const T* __restrict__ xop, const T* __restrict__ yop,
                                                             const float2* __restrict__ gtabf, int64_t m_pad,
                                                             const double* __restrict__ H,
                                                             double2* __restrict__ part, int64_t tiles_per_split,
-                                                            int P, int64_t m_tiles, int64_t n_waves) {
+                                                            int P, int G, int64_t m_tiles, int64_t n_waves) {
     using L = LdsTile<T, KP>;
     using Op = MfmaOp<T>;
     using vec = typename Op::vec;
@@ -495,9 +508,8 @@ __global__ __launch_bounds__(BLOCK, (row_sweep_min_waves<T, KP>())) void row_swe
     const float2* __restrict__ g = gtabf + (t & 1) * m_pad;
     const int lane = threadIdx.x & 63;
     const int hf = lane >> 5, c32 = lane & 31;
-    const int64_t b = blockIdx.x;
-    const int p = (int)(b % P);
-    const int64_t rw = (b / P) * 4 + (threadIdx.x >> 6);
+    const SplitRun run = split_run(P, G, tiles_per_split, m_tiles);
+    const int64_t rw = run.owned * 4 + (threadIdx.x >> 6);
     const bool active = rw < n_waves;   // whole waves; the block still joins every barrier
     const int64_t i0 = (active ? rw : 0) * 32;
 
@@ -517,8 +529,19 @@ __global__ __launch_bounds__(BLOCK, (row_sweep_min_waves<T, KP>())) void row_swe
 #pragma unroll
     for (int r = 0; r < 16; ++r) accA[r] = accB[r] = 0.f;
 
-    const int jt0 = p * (int)tiles_per_split;
-    const int jt1 = min((int)m_tiles, jt0 + (int)tiles_per_split);
+    const int jt0 = run.tile0, jt1 = run.tile1;
+    int p = run.first, left = (int)tiles_per_split;
+    auto end_split = [&] {   // the split's sums, and the next begins
+        auto add = [](float x, float y) { return x + y; };
+        reduce_lanes<16, 16>(accA, add);
+        reduce_lanes<16, 16>(accB, add);
+        const int64_t row = i0 + mfma_row(c32 >> 1, hf);
+        if (active && c32 % 2 == 0 && row < kc.n) part[(int64_t)p * kc.n + row] = make_double2(accA[0], accB[0]);
+#pragma unroll
+        for (int r = 0; r < 16; ++r) accA[r] = accB[r] = 0.f;
+        ++p;
+        left = (int)tiles_per_split;
+    };
     const TileSrc src = make_tile_src(yop, (uint32_t)(m_pad * KP * (int64_t)sizeof(T)), g, (uint32_t)(m_pad * 8));
     TileRegs pf;
     if (jt0 < jt1) {
@@ -566,14 +589,11 @@ __global__ __launch_bounds__(BLOCK, (row_sweep_min_waves<T, KP>())) void row_swe
             __syncthreads();
             dc = dn;
             gc = gn;
+            if constexpr (RUNS)
+                if (--left == 0 || jt + 1 == jt1) end_split();
         }
+        if constexpr (!RUNS) end_split();
     }
-    if (!active) return;
-    auto add = [](float x, float y) { return x + y; };
-    reduce_lanes<16, 16>(accA, add);
-    reduce_lanes<16, 16>(accB, add);
-    const int64_t row = i0 + mfma_row(c32 >> 1, hf);
-    if (c32 % 2 == 0 && row < kc.n) part[(int64_t)p * kc.n + row] = make_double2(accA[0], accB[0]);
 }
 
 // Offsets of the matrix-core forms: part[p][i] = -max_j (c^B x~_i . y~_j + g^B_j) / c^B over
@@ -658,13 +678,13 @@ __global__ __launch_bounds__(BLOCK) void row_extreme_mfma_lds(const Ctrl* ctrl, 
 // by the column tables of iteration t, CA_j = LOG2E K tau1 (lam_t / lam_{t+1})
 // (theta_j - nu_j), so |CA_j| <= 2 LOG2E K tau1 (2.9 with the default tau1); the host
 // keeps the per-term add when that bound exceeds 64.
-template <typename T, int KP>
+template <typename T, int KP, bool RUNS>
 __global__ __launch_bounds__(BLOCK) void col_sweep_mfma_t_lds(const Ctrl* ctrl, const Sched* sched, Consts kc,
                                                               const T* __restrict__ xop, const T* __restrict__ yop,
                                                               const float2* __restrict__ gtabf, int64_t m_pad,
                                                               const float4* __restrict__ rowq,
                                                               double2* __restrict__ cpart, int64_t tiles_per_split,
-                                                              int P, int64_t n_tiles, int64_t m_waves) {
+                                                              int P, int G, int64_t n_tiles, int64_t m_waves) {
     using L = LdsTile<T, KP>;
     using Op = MfmaOp<T>;
     using vec = typename Op::vec;
@@ -681,9 +701,8 @@ __global__ __launch_bounds__(BLOCK) void col_sweep_mfma_t_lds(const Ctrl* ctrl, 
     const float cBd = (float)(2.0 * kc.s * sc.lamB * LOG2E * kc.dscale);
     const int lane = threadIdx.x & 63;
     const int hf = lane >> 5, c32 = lane & 31;
-    const int64_t b = blockIdx.x;
-    const int p = (int)(b % P);
-    const int64_t cw = (b / P) * 4 + (threadIdx.x >> 6);
+    const SplitRun run = split_run(P, G, tiles_per_split, n_tiles);
+    const int64_t cw = run.owned * 4 + (threadIdx.x >> 6);
     const bool active = cw < m_waves;
     const int64_t j0 = (active ? cw : 0) * 32;
     vec a[NS];
@@ -709,8 +728,23 @@ __global__ __launch_bounds__(BLOCK) void col_sweep_mfma_t_lds(const Ctrl* ctrl, 
     float accA[16], accB[16];
 #pragma unroll
     for (int r = 0; r < 16; ++r) accA[r] = accB[r] = 0.f;
-    const int it0 = p * (int)tiles_per_split;
-    const int it1 = min((int)n_tiles, it0 + (int)tiles_per_split);
+    const int it0 = run.tile0, it1 = run.tile1;
+    int p = run.first, left = (int)tiles_per_split;
+    auto end_split = [&](bool factor) {   // the split's sums, and the next begins
+        if (factor) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) accA[r] *= __builtin_amdgcn_exp2f(CA[r]);
+        }
+        auto add = [](float x, float y) { return x + y; };
+        reduce_lanes<16, 16>(accA, add);
+        reduce_lanes<16, 16>(accB, add);
+        const int64_t j = j0 + mfma_row(c32 >> 1, hf);
+        if (active && c32 % 2 == 0 && j < kc.m) cpart[(int64_t)p * kc.m + j] = make_double2(accA[0], accB[0]);
+#pragma unroll
+        for (int r = 0; r < 16; ++r) accA[r] = accB[r] = 0.f;
+        ++p;
+        left = (int)tiles_per_split;
+    };
     const int64_t n_rows = n_tiles * 32;
     const TileSrc src = make_tile_src(xop, (uint32_t)(n_rows * KP * (int64_t)sizeof(T)), rowq,
                                       (uint32_t)(n_rows * 16));
@@ -782,26 +816,18 @@ __global__ __launch_bounds__(BLOCK) void col_sweep_mfma_t_lds(const Ctrl* ctrl, 
                 dcA = dnA;
                 dcB = dnB;
                 qc = qn;
+                if constexpr (RUNS)
+                    if (--left == 0 || it + 1 == it1) end_split(FACTOR);
             }
+            if constexpr (!RUNS) end_split(FACTOR);
         };
         if constexpr (ONE_CHAIN) {
-            if (kc.factor_cols) {
-                stream_tiles(std::true_type{});
-#pragma unroll
-                for (int r = 0; r < 16; ++r) accA[r] *= __builtin_amdgcn_exp2f(CA[r]);
-            } else {
-                stream_tiles(std::false_type{});
-            }
+            if (kc.factor_cols) stream_tiles(std::true_type{});
+            else stream_tiles(std::false_type{});
         } else {
             stream_tiles(std::false_type{});
         }
     }
-    if (!active) return;
-    auto add = [](float x, float y) { return x + y; };
-    reduce_lanes<16, 16>(accA, add);
-    reduce_lanes<16, 16>(accB, add);
-    const int64_t j = j0 + mfma_row(c32 >> 1, hf);
-    if (c32 % 2 == 0 && j < kc.m) cpart[(int64_t)p * kc.m + j] = make_double2(accA[0], accB[0]);
 }
 
 // FP64 matrix-core sweeps with LDS-shared tiles of 16 points (see the LDS-shared
