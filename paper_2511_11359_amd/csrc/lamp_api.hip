@@ -635,12 +635,14 @@ void launch_row_extreme(const Layout& L, Consts kc, int d, void* ws, const doubl
 }
 
 // Splits a block of a matrix-core sweep takes one after another: enough for 8 tiles, at most 4, and not
-// below 1024 blocks.  Row / column sweep, BF16, d = 4, by 1, 2, 4, 8 splits: 4096 x 4096 (1 tile a split)
+// below 512 blocks.  Row / column sweep, BF16, d = 4, by 1, 2, 4, 8 splits: 4096 x 4096 (1 tile a split)
 // 21.7 / 25.7, 16.3 / 18.9, 14.2 / 15.2, 14.3 / 14.7 us; 8192 x 8192 (2) 32.0 / 36.8, 28.7 / 30.9,
 // 27.0 / 28.8, 29.4 / 30.3; 38568 x 4980 (5) 61 / 65, 60 / 63, 61 / 68, 74 / 82; 16384 x 16384 (8)
-// 76 / 84, 76 / 81, 76 / 80, 86 / 89.
+// 76 / 84, 76 / 81, 76 / 80, 86 / 89.  512 blocks against 1024: 2048 x 2048 7.8 / 8.7 -> 6.9 / 7.0.
+// FP64 products, d = 64 (they also compute a tile ahead, which a split of one tile wastes): 1024 x 1024
+// 10.4 / 10.6 -> 8.4 / 8.4, 2048 x 2048 31.0 / 31.4 -> 18.8 / 18.6, 4096 x 4096 55.7 / 59.4 -> 47.7 / 49.7.
 int splits_per_block(int64_t owned_blocks, int64_t P, int64_t tiles_per_split) {
-    return (int)std::max<int64_t>(1, std::min<int64_t>({4, cdiv(8, tiles_per_split), owned_blocks * P / 1024}));
+    return (int)std::max<int64_t>(1, std::min<int64_t>({4, cdiv(8, tiles_per_split), owned_blocks * P / 512}));
 }
 
 template <typename T, int KP>
@@ -703,12 +705,17 @@ void sweep_mfma(const Layout& L, Consts kc, void* ws, hipStream_t st) {
 
 template <int KP>
 void row_mfma64(const Layout& L, Consts kc, void* ws, hipStream_t st) {
-    const int64_t n_waves = L.n_pad64 / 16;
-    dim3 g((unsigned)(cdiv(n_waves, 4) * L.P_r64));
-    hipLaunchKernelGGL((row_sweep_mfma64_lds<KP>), g, dim3(BLOCK), 0, st, at<Ctrl>(ws, L.ctrl), at<Sched>(ws, L.sched),
-                       kc, at<double>(ws, L.xop64), at<double>(ws, L.yop64), at<double2>(ws, L.gtab),
-                       at<double>(ws, L.H), at<double2>(ws, L.rpart), L.tps_r64, (int)L.P_r64, L.m_pad64 / 16,
-                       n_waves);
+    const int64_t n_waves = L.n_pad64 / 16, blocks = cdiv(n_waves, 4);
+    const int G = splits_per_block(blocks, L.P_r64, L.tps_r64);
+    auto launch = [&](auto runs) {
+        hipLaunchKernelGGL((row_sweep_mfma64_lds<KP, decltype(runs)::value>),
+                           dim3((unsigned)(blocks * cdiv(L.P_r64, G))), dim3(BLOCK), 0, st, at<Ctrl>(ws, L.ctrl),
+                           at<Sched>(ws, L.sched), kc, at<double>(ws, L.xop64), at<double>(ws, L.yop64),
+                           at<double2>(ws, L.gtab), at<double>(ws, L.H), at<double2>(ws, L.rpart), L.tps_r64,
+                           (int)L.P_r64, G, L.m_pad64 / 16, n_waves);
+    };
+    if (G > 1) launch(std::true_type{});
+    else launch(std::false_type{});
 }
 
 // The D_t-tracked FP64 matrix-core row sweep: cost sums into tpart ([P_r64][n]).
@@ -724,12 +731,12 @@ void row_mfma64_dt(const Layout& L, Consts kc, void* ws, double* tpart, hipStrea
 
 template <int KP>
 void col_mfma64(const Layout& L, Consts kc, void* ws, hipStream_t st) {
-    const int64_t m_waves = L.m_pad64 / 16;
-    dim3 g((unsigned)(cdiv(m_waves, 4) * L.P_c64));
-    hipLaunchKernelGGL((col_sweep_mfma64_lds<KP>), g, dim3(BLOCK), 0, st, at<Ctrl>(ws, L.ctrl), at<Sched>(ws, L.sched),
-                       kc, at<double>(ws, L.xop64), at<double>(ws, L.yop64), at<double2>(ws, L.gtab),
-                       at<RowVar>(ws, L.rowvar), at<double2>(ws, L.cpart), L.tps_c64, (int)L.P_c64,
-                       L.n_pad64 / 16, m_waves);
+    const int64_t m_waves = L.m_pad64 / 16, blocks = cdiv(m_waves, 4);
+    const int G = splits_per_block(blocks, L.P_c64, L.tps_c64);
+    hipLaunchKernelGGL((col_sweep_mfma64_lds<KP>), dim3((unsigned)(blocks * cdiv(L.P_c64, G))), dim3(BLOCK), 0, st,
+                       at<Ctrl>(ws, L.ctrl), at<Sched>(ws, L.sched), kc, at<double>(ws, L.xop64),
+                       at<double>(ws, L.yop64), at<double2>(ws, L.gtab), at<RowVar>(ws, L.rowvar),
+                       at<double2>(ws, L.cpart), L.tps_c64, (int)L.P_c64, G, L.n_pad64 / 16, m_waves);
 }
 
 template <bool ROW>

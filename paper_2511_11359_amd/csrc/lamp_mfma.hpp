@@ -906,14 +906,14 @@ __device__ __forceinline__ void pipelined_tiles(int it0, int it1, int it_mask, S
 // Body of the FP64 matrix-core row sweep; with DT it also sums the B coupling's cost terms
 // for D_t tracking, 2^eB C_ij / s with C_ij / s = (|x~_i|^2 + 2 h_i) + |y~_j|^2 - 2 dot from the
 // accumulator dot = h_i + x~_i . y~_j (tpart[p][i], under the row offset of the B sums).
-template <int KP, bool DT>
+template <int KP, bool DT, bool RUNS>
 __device__ __forceinline__ void row_sweep_mfma64_body(const Ctrl* ctrl, const Sched* sched, Consts kc,
                                                       const double* __restrict__ xop,
                                                       const double* __restrict__ yop,
                                                       const double2* __restrict__ gtab2,
                                                       const double* __restrict__ H,
                                                       double2* __restrict__ part, int64_t tiles_per_split,
-                                                      int P, int64_t m_tiles, int64_t n_waves,
+                                                      int P, int G, int64_t m_tiles, int64_t n_waves,
                                                       const double* __restrict__ xn2, const double* __restrict__ yn2,
                                                       double* __restrict__ tpart) {
     using L = LdsTile64<KP>;
@@ -927,9 +927,8 @@ __device__ __forceinline__ void row_sweep_mfma64_body(const Ctrl* ctrl, const Sc
     const double2* __restrict__ g = gtab2 + (t & 1) * kc.m;
     const int lane = threadIdx.x & 63;
     const int grp = lane >> 4, c16 = lane & 15;
-    const int64_t b = blockIdx.x;
-    const int p = (int)(b % P);
-    const int64_t rw = (b / P) * 4 + (threadIdx.x >> 6);
+    const SplitRun run = split_run(P, G, tiles_per_split, m_tiles);
+    const int64_t rw = run.owned * 4 + (threadIdx.x >> 6);
     const bool active = rw < n_waves;
     const int64_t i0 = (active ? rw : 0) * 16;
     double a[NS];
@@ -961,8 +960,33 @@ __device__ __forceinline__ void row_sweep_mfma64_body(const Ctrl* ctrl, const Sc
         const int64_t j = (int64_t)jt * 16 + c16;
         return yn2[j < kc.m ? j : kc.m - 1];
     };
-    const int jt0 = (int)((int64_t)p * tiles_per_split);
-    const int jt1 = (int)min(m_tiles, (int64_t)jt0 + tiles_per_split);
+    const int jt0 = run.tile0, jt1 = run.tile1;
+    int p = run.first, left = (int)tiles_per_split, cnt = 0;
+    auto end_split = [&] {   // the split's sums, and the next begins
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            sumA[q] += (double)accA[q];
+            sumB[q] += (double)accB[q];
+            if constexpr (DT) sumT[q] += (double)accT[q];
+        }
+        auto add = [](double x, double y) { return x + y; };
+        reduce_lanes<4, 8>(sumA, add);
+        reduce_lanes<4, 8>(sumB, add);
+        if constexpr (DT) reduce_lanes<4, 8>(sumT, add);
+        const int64_t row = i0 + 4 * (c16 >> 2) + grp;
+        if (active && c16 % 4 == 0 && row < kc.n) {
+            part[(int64_t)p * kc.n + row] = make_double2(sumA[0], sumB[0]);
+            if constexpr (DT) tpart[(int64_t)p * kc.n + row] = sumT[0];
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            accA[q] = accB[q] = accT[q] = 0.f;
+            sumA[q] = sumB[q] = sumT[q] = 0.0;
+        }
+        ++p;
+        left = (int)tiles_per_split;
+        cnt = 0;
+    };
     const TileSrc src = make_tile_src(yop, (uint32_t)(m_tiles * L::TILE_BYTES), g, (uint32_t)(kc.m * 16));
     TileRegs pf;
     // column j's table entry; columns past m (padding) never contribute
@@ -985,7 +1009,6 @@ __device__ __forceinline__ void row_sweep_mfma64_body(const Ctrl* ctrl, const Sc
         tile64_store<KP>(lds[1], pf);
         __syncthreads();
         loads_done();
-        int cnt = 0;
         auto step = [&](int jt, auto nxtc, auto check) {
             const int nxt = nxtc;   // a constant in the paired iterations
             tile64_fetch<KP>(src, min(jt + 2, jl), pf);
@@ -1029,38 +1052,25 @@ __device__ __forceinline__ void row_sweep_mfma64_body(const Ctrl* ctrl, const Sc
             dc = dn;
             gc = gn;
             if constexpr (DT) yc = yn;
+            if constexpr (RUNS)
+                if (--left == 0 || jt + 1 == jt1) end_split();
         };
         // iteration jt reads the scalars of tile jt + 1: whole tiles (16 columns below m) for jt < m / 16 - 1
         pipelined_tiles(jt0, jt1, max(jt0, min(jt1, (int)(kc.m / 16) - 1)), step);
     }
-    if (!active) return;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        sumA[q] += (double)accA[q];
-        sumB[q] += (double)accB[q];
-        if constexpr (DT) sumT[q] += (double)accT[q];
-    }
-    auto add = [](double x, double y) { return x + y; };
-    reduce_lanes<4, 8>(sumA, add);
-    reduce_lanes<4, 8>(sumB, add);
-    if constexpr (DT) reduce_lanes<4, 8>(sumT, add);
-    const int64_t row = i0 + 4 * (c16 >> 2) + grp;
-    if (c16 % 4 == 0 && row < kc.n) {
-        part[(int64_t)p * kc.n + row] = make_double2(sumA[0], sumB[0]);
-        if constexpr (DT) tpart[(int64_t)p * kc.n + row] = sumT[0];
-    }
+    if constexpr (!RUNS) end_split();
 }
 
-template <int KP>
+template <int KP, bool RUNS>
 __global__ __launch_bounds__(BLOCK) void row_sweep_mfma64_lds(const Ctrl* ctrl, const Sched* sched, Consts kc,
                                                               const double* __restrict__ xop,
                                                               const double* __restrict__ yop,
                                                               const double2* __restrict__ gtab2,
                                                               const double* __restrict__ H,
                                                               double2* __restrict__ part, int64_t tiles_per_split,
-                                                              int P, int64_t m_tiles, int64_t n_waves) {
-    row_sweep_mfma64_body<KP, false>(ctrl, sched, kc, xop, yop, gtab2, H, part, tiles_per_split, P, m_tiles, n_waves,
-                                     nullptr, nullptr, nullptr);
+                                                              int P, int G, int64_t m_tiles, int64_t n_waves) {
+    row_sweep_mfma64_body<KP, false, RUNS>(ctrl, sched, kc, xop, yop, gtab2, H, part, tiles_per_split, P, G, m_tiles,
+                                           n_waves, nullptr, nullptr, nullptr);
 }
 
 // The FP64 matrix-core row sweep of a D_t-tracked iteration, tpart: [P][n].
@@ -1075,8 +1085,8 @@ __global__ __launch_bounds__(BLOCK) void row_sweep_mfma64_dt(const Ctrl* ctrl, c
                                                              const double* __restrict__ xn2,
                                                              const double* __restrict__ yn2,
                                                              double* __restrict__ tpart) {
-    row_sweep_mfma64_body<KP, true>(ctrl, sched, kc, xop, yop, gtab2, H, part, tiles_per_split, P, m_tiles, n_waves,
-                                    xn2, yn2, tpart);
+    row_sweep_mfma64_body<KP, true, false>(ctrl, sched, kc, xop, yop, gtab2, H, part, tiles_per_split, P, 1, m_tiles,
+                                           n_waves, xn2, yn2, tpart);
 }
 
 // Four waves per SIMD for KP <= 64 (128 VGPRs, no spills): 10.59 -> 10.35 ms at
@@ -1084,6 +1094,8 @@ __global__ __launch_bounds__(BLOCK) void row_sweep_mfma64_dt(const Ctrl* ctrl, c
 template <int KP>
 constexpr int col64_min_waves() { return KP <= 64 ? 4 : 2; }
 
+// The test for a split's end stands in the loop for every G: 65536 x 65536, d = 64, 9.01 -> 8.77 ms (the
+// carry of every second tile then no longer follows the buffer, and fewer registers spill).
 template <int KP>
 __global__ __launch_bounds__(BLOCK, (col64_min_waves<KP>())) void col_sweep_mfma64_lds(const Ctrl* ctrl, const Sched* sched, Consts kc,
                                                               const double* __restrict__ xop,
@@ -1091,7 +1103,7 @@ __global__ __launch_bounds__(BLOCK, (col64_min_waves<KP>())) void col_sweep_mfma
                                                               const double2* __restrict__ gtab2,
                                                               const RowVar* __restrict__ rowvar,
                                                               double2* __restrict__ cpart, int64_t tiles_per_split,
-                                                              int P, int64_t n_tiles, int64_t m_waves) {
+                                                              int P, int G, int64_t n_tiles, int64_t m_waves) {
     using L = LdsTile64<KP>;
     constexpr int NS = KP / 4;
     __shared__ __align__(16) char lds[2][L::BUF];
@@ -1102,9 +1114,8 @@ __global__ __launch_bounds__(BLOCK, (col64_min_waves<KP>())) void col_sweep_mfma
     const double cB = 2.0 * kc.s * sc.lamB * LOG2E;
     const int lane = threadIdx.x & 63;
     const int grp = lane >> 4, c16 = lane & 15;
-    const int64_t b = blockIdx.x;
-    const int p = (int)(b % P);
-    const int64_t cw = (b / P) * 4 + (threadIdx.x >> 6);
+    const SplitRun run = split_run(P, G, tiles_per_split, n_tiles);
+    const int64_t cw = run.owned * 4 + (threadIdx.x >> 6);
     const bool active = cw < m_waves;
     const int64_t j = (active ? cw : 0) * 16 + c16;
     // B operand: the wave's 16 columns y_j (lane c16 holds column j of D); the streamed
@@ -1123,8 +1134,21 @@ __global__ __launch_bounds__(BLOCK, (col64_min_waves<KP>())) void col_sweep_mfma
     }
     float accA = 0.f, accB = 0.f;
     double sumA = 0.0, sumB = 0.0;
-    const int it0 = (int)((int64_t)p * tiles_per_split);
-    const int it1 = (int)min(n_tiles, (int64_t)it0 + tiles_per_split);
+    const int it0 = run.tile0, it1 = run.tile1;
+    int p = run.first, left = (int)tiles_per_split;
+    auto end_split = [&] {   // the split's sums, and the next begins
+        sumA += (double)accA;
+        sumB += (double)accB;
+        sumA += __shfl_xor(sumA, 16, 64);
+        sumB += __shfl_xor(sumB, 16, 64);
+        sumA += __shfl_xor(sumA, 32, 64);
+        sumB += __shfl_xor(sumB, 32, 64);
+        if (active && grp == 0 && j < kc.m) cpart[(int64_t)p * kc.m + j] = make_double2(sumA, sumB);
+        accA = accB = 0.f;
+        sumA = sumB = 0.0;
+        ++p;
+        left = (int)tiles_per_split;
+    };
     const TileSrc src = make_tile_src(xop, (uint32_t)(n_tiles * L::TILE_BYTES), rowvar, (uint32_t)(kc.n * 16));
     // rows of the tile: offsets k (accumulator input of the dot products) and weights
     struct RowTerms {
@@ -1183,8 +1207,8 @@ __global__ __launch_bounds__(BLOCK, (col64_min_waves<KP>())) void col_sweep_mfma
                 accB = fmaf(rc.wb[q], fexp2(fma(dc[q], cB, gB)), accB);
             }
             pin(accA, accB);
-            // carry in FP64 after every second tile of the range (nxt = 0 on those)
-            if (nxt == 0) {
+            // carry in FP64 after every second tile of the split
+            if (((int)tiles_per_split - left) % 2 == 1) {
                 sumA += (double)accA;
                 sumB += (double)accB;
                 accA = accB = 0.f;
@@ -1193,18 +1217,11 @@ __global__ __launch_bounds__(BLOCK, (col64_min_waves<KP>())) void col_sweep_mfma
             __syncthreads();
             dc = dn;
             rc = rn;
+            if (--left == 0 || it + 1 == it1) end_split();
         };
         // iteration it reads the row data of tile it + 1: whole tiles (16 rows below n) for it < n / 16 - 1
         pipelined_tiles(it0, it1, max(it0, min(it1, (int)(kc.n / 16) - 1)), step);
     }
-    if (!active) return;
-    sumA += (double)accA;
-    sumB += (double)accB;
-    sumA += __shfl_xor(sumA, 16, 64);
-    sumB += __shfl_xor(sumB, 16, 64);
-    sumA += __shfl_xor(sumA, 32, 64);
-    sumB += __shfl_xor(sumB, 32, 64);
-    if (grp == 0 && j < kc.m) cpart[(int64_t)p * kc.m + j] = make_double2(sumA, sumB);
 }
 
 }  // namespace lampk
