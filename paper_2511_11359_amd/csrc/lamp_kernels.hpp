@@ -1940,7 +1940,7 @@ __global__ void round_col_sums(Consts kc, int D, const double* __restrict__ yc, 
 // (C dc)_i by a pass over all pairs (the l1 / l_inf costs, whose C dc has no closed form;
 // C_ij = -2 s P(x~_i, y~_j)): part[p][i] = sum of P(x~_i, y~_j) dc_j over column split p, FP64.  One
 // thread a row and a run-time dimension took 14.2 ms for 13378 x 38523 x 3, l1, against 0.3 ms of the
-// other pair passes; split and compiled like them 0.16 ms.
+// other pair passes; split and compiled like them 0.13 ms.
 template <int M, int D>
 __global__ __launch_bounds__(BLOCK) void round_rank_one_pairs(Consts kc, int Dm, OwnPts xs,
                                                               const double* __restrict__ yc,
@@ -2256,9 +2256,6 @@ __global__ __launch_bounds__(BLOCK) void norm_sweep(Consts kc, double cA, const 
     weighted_row_sums<M, D>(kc, cA, xc, cols, NormSums<D>{}, part, split);
 }
 
-// X^t's row data for the column-side adjoint from the splits' (M, Z) at their common offset:
-// sigma_i = M + log2 Z (base 2), k_i = -sigma_i / cfac, so that
-// X_ij = r_i 2^(cfac (k_i + P_ij) + g_j); wA = wB = r_i.
 // Split partials of a row under their own offsets (o[0] = M_p; -inf: no finite term) at the common
 // offset: 2^(M_p - off) v, exact.
 __device__ __forceinline__ double at_offset(double m, double v, double off) {
@@ -2275,6 +2272,10 @@ __device__ __forceinline__ double common_offset(const double* __restrict__ part,
 
 // The merges run one wave a block, with 16 splits' loads in flight: they are bound by latency, and
 // blocks of 256 rows left most of the chip idle (941 rows of 107 splits: 29 us on 4 CUs).
+//
+// X^t's row data for the column-side adjoint from the splits' (M, Z) at their common offset:
+// sigma_i = M + log2 Z (base 2), k_i = -sigma_i / cfac, so that
+// X_ij = r_i 2^(cfac (k_i + P_ij) + g_j); wA = wB = r_i.
 __global__ __launch_bounds__(64) void norm_finish(Consts kc, int P, double cA, const double* __restrict__ r,
                             const double* __restrict__ part, RowVar* __restrict__ rowvar) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
