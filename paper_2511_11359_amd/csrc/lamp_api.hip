@@ -2148,7 +2148,6 @@ lamp_status lamp_certificate(const lamp_problem* prob, const lamp_params* params
     // column and row data of single passes, in arrays that a later pass fills
     float* wf = reinterpret_cast<float*>(dr);             // n, until round_rows_merge
     float2* yff = reinterpret_cast<float2*>(tr1);         // m, until round_rank_one
-    double2* soft_cols = reinterpret_cast<double2*>(dr);  // m, after the sums of cpp, tr1, absdr
     const dim3 split_grid(sweep_grid(kc.n, L.P_r));
     hipLaunchKernelGGL(col_residual, grid1(kc.m), dim3(BLOCK), 0, st, kc, at<double2>(ws, L.cpart), col_parts(LV),
                        prob->c, colres);
@@ -2263,12 +2262,10 @@ lamp_status lamp_certificate(const lamp_problem* prob, const lamp_params* params
         double* sv = vals;   // 2n (the row values above are reduced)
         // the minima: from the certificate row pass (recovered from r_i min for the explicit cost)
         if (L.cost) hipLaunchKernelGGL(row_minima_of_vals, grid1(kc.n), dim3(BLOCK), 0, st, kc, prob->r, vals, mu);
-        hipLaunchKernelGGL(cert_soft_cols, grid1(kc.m), dim3(BLOCK), 0, st, kc, 1.0 / params->eta,
-                           at<double>(ws, L.yn2), state->nu, state->theta, soft_cols);
         by_md([&](auto m, auto dd) {
             hipLaunchKernelGGL((cert_soft_rows<decltype(m)::value, decltype(dd)::value>), split_grid, dim3(BLOCK),
                                0, st, kc, prob->d, 1.0 / params->eta, xs, at<double>(ws, L.yc), at<double>(ws, L.xn2),
-                               (const double2*)soft_cols, (const double*)mu, part, L.split_r);
+                               at<double>(ws, L.yn2), state->nu, state->theta, (const double*)mu, part, L.split_r);
         });
         hipLaunchKernelGGL(cert_soft_merge, grid1(kc.n), dim3(BLOCK), 0, st, kc, (int)L.P_r, 1.0 / params->eta,
                            prob->r, (const double*)mu, (const double*)part, sv);
