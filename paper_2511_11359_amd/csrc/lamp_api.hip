@@ -1442,16 +1442,6 @@ lamp_status state_normalisers(const lamp_problem* p, const lamp_params* q, const
 }
 
 // g^A_j = -lam_t LOG2E (s |y~_j|^2 + K nu_j): the column term of X^t's exponents (base 2).
-// mu_i = vals[2 + k][i] / r_i: the row minima of the explicit-cost certificate pass (which
-// reports them weighted by r_i > 0), the shifts of the entropic pass.
-__global__ void row_minima_of_vals(Consts kc, const double* __restrict__ r, const double* __restrict__ vals,
-                                   double* __restrict__ mu) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= kc.n) return;
-    mu[i] = vals[2 * kc.n + i] / r[i];
-    mu[kc.n + i] = vals[3 * kc.n + i] / r[i];
-}
-
 __global__ void state_col_term(Consts kc, double lam, const double* __restrict__ yn2,
                                const double* __restrict__ nu, double* __restrict__ gA) {
     int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -2178,7 +2168,7 @@ lamp_status lamp_certificate(const lamp_problem* prob, const lamp_params* params
         by_cost_type(kc.cost_type, [&](auto tag) {
             using T = std::remove_pointer_t<decltype(tag)>;
             hipLaunchKernelGGL((cert_rows_cost<T>), cost_rows_grid, dim3(BLOCK), 0, st, kc, cA, gA, at<double>(ws, L.H),
-                           prob->r, state->nu, state->theta, vals, psum);
+                           prob->r, state->nu, state->theta, vals, psum, mu);
         });
     } else {
         by_md([&](auto m, auto dd) {
@@ -2260,8 +2250,6 @@ lamp_status lamp_certificate(const lamp_problem* prob, const lamp_params* params
     const bool soft = params->eta > 0.0;
     if (soft) {
         double* sv = vals;   // 2n (the row values above are reduced)
-        // the minima: from the certificate row pass (recovered from r_i min for the explicit cost)
-        if (L.cost) hipLaunchKernelGGL(row_minima_of_vals, grid1(kc.n), dim3(BLOCK), 0, st, kc, prob->r, vals, mu);
         by_md([&](auto m, auto dd) {
             hipLaunchKernelGGL((cert_soft_rows<decltype(m)::value, decltype(dd)::value>), split_grid, dim3(BLOCK),
                                0, st, kc, prob->d, 1.0 / params->eta, xs, at<double>(ws, L.yc), at<double>(ws, L.xn2),

@@ -262,13 +262,15 @@ struct CostRows {
     }
 };
 
-// vals[0..3][i] and psum_out[i] as cert_rows.
+// vals[0..3][i], psum_out[i] and mu as cert_rows_merge; the minima are formed with the operations of
+// cert_soft_rows, whose exponents are 0 at them.
 template <typename T>
 __global__ __launch_bounds__(BLOCK) void cert_rows_cost(Consts kc, double cA, const double* __restrict__ gA,
                                                         const double* __restrict__ H, const double* __restrict__ r,
                                                         const double* __restrict__ nu,
                                                         const double* __restrict__ theta,
-                                                        double* __restrict__ vals, double* __restrict__ psum_out) {
+                                                        double* __restrict__ vals, double* __restrict__ psum_out,
+                                                        double* __restrict__ mu) {
     const CostRows<T> cr(kc);
     double h[COST_ROWS], psum[COST_ROWS], csum[COST_ROWS], mth[COST_ROWS], mnu[COST_ROWS];
 #pragma unroll
@@ -300,8 +302,8 @@ __global__ __launch_bounds__(BLOCK) void cert_rows_cost(Consts kc, double cA, co
                 const double cij = kc.s * (double)cv[r_][u];
                 ap += p;
                 ac = fmaf((float)cij, p, ac);
-                mth[r_] = fmin(mth[r_], cij + kc.K * th[u]);
-                mnu[r_] = fmin(mnu[r_], cij + kc.K * nv[u]);
+                mth[r_] = fmin(mth[r_], fma(kc.K, th[u], cij));
+                mnu[r_] = fmin(mnu[r_], fma(kc.K, nv[u], cij));
             }
             psum[r_] += (double)ap;
             csum[r_] += (double)ac;
@@ -318,7 +320,9 @@ __global__ __launch_bounds__(BLOCK) void cert_rows_cost(Consts kc, double cA, co
             vals[kc.n + i] = ri * cs;
             vals[2 * kc.n + i] = ri * a;
             vals[3 * kc.n + i] = ri * b;
-            if (psum_out) psum_out[i] = ps;
+            psum_out[i] = ps;
+            mu[i] = a;
+            mu[kc.n + i] = b;
         }
     }
 }

@@ -47,3 +47,16 @@ def test_points(n, m, d, kind):
     prob = P.Problem(wl.x, wl.y, wl.r, wl.c, cost_scale=s, cost_norm=1.0, metric=kind)
     for eta in ETAS:
         _check(prob, C, at, st, wl.r, wl.c, eta, d)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16, torch.float16])
+def test_cost_matrix(dtype):
+    wl = W.random_small(130, 301, 3, seed=44, eta=1e-2)
+    x, y = wl.x.astype(np.float64), wl.y.astype(np.float64)
+    mat = torch.tensor(OL.ground_cost(x, y, 1.0, "sqeuclid"), dtype=dtype)
+    full = mat.double().numpy()
+    s = 1.0 / float(full.max())
+    at, st = _state(s * full, wl)
+    prob = P.Problem.from_cost(mat.cuda(), wl.r, wl.c, cost_scale=s, cost_norm=1.0)
+    for eta in ETAS:
+        _check(prob, s * full, at, st, wl.r, wl.c, eta, 1)
