@@ -393,6 +393,9 @@ double* marginals_ptr(const Layout& L, void* ws) { return at<double>(ws, L.small
 
 dim3 grid1(int64_t cnt) { return dim3((unsigned)cdiv(cnt, BLOCK)); }
 dim3 wave_grid(int64_t cnt) { return dim3((unsigned)cdiv(cnt, 64)); }
+// For a kernel that strides by its grid over the coordinates of a cloud, which may be more than the 2^32 - 1
+// threads of one launch.
+dim3 strided_wave_grid(int64_t cnt) { return wave_grid(std::min<int64_t>(cnt, (int64_t)1 << 31)); }
 
 template <typename T>
 void prep_ops(const lamp_problem* p, const Layout& L, void* ws, hipStream_t st) {
@@ -2308,7 +2311,7 @@ lamp_status lamp_backward(const lamp_problem* prob, const lamp_params* params, c
     hipLaunchKernelGGL(state_col_term, grid1(kc.m), dim3(BLOCK), 0, st, kc, state->inv_eta, at<double>(ws, L.yn2),
                        state->nu, gA);
     launch_adjoint(L, kc, prob->d, ws, cA, gA, st);
-    hipLaunchKernelGGL(adjoint_finish, wave_grid(kc.n * prob->d), dim3(64), 0, st, kc, prob->d, (int)L.P_r,
+    hipLaunchKernelGGL(adjoint_finish, strided_wave_grid(kc.n * prob->d), dim3(64), 0, st, kc, prob->d, (int)L.P_r,
                        grad_out * 2.0 * R.s, at<double>(ws, L.xc), prob->r, at<double>(ws, L.rpart), grad_x);
     HIPCHK(hipGetLastError());
     return LAMP_OK;
@@ -2405,7 +2408,7 @@ lamp_status lamp_backward_y(const lamp_problem* prob, const lamp_params* params,
                                dim3(g.x, (unsigned)chunks), dim3(BLOCK), 0, st, kc, d, chunk, cA, ys, xc,
                                (const double*)gA, rv, part, L.split_c);
         });
-    hipLaunchKernelGGL(adjoint_y_finish, wave_grid(kc.m * d), dim3(64), 0, st, kc, d, (int)L.P_c, grad_out * 2.0 * R.s,
+    hipLaunchKernelGGL(adjoint_y_finish, strided_wave_grid(kc.m * d), dim3(64), 0, st, kc, d, (int)L.P_c, grad_out * 2.0 * R.s,
                        yc, part, grad_y);
     HIPCHK(hipGetLastError());
     return LAMP_OK;

@@ -2630,41 +2630,43 @@ __global__ __launch_bounds__(BLOCK) void adjoint_y_sweep_any(Consts kc, int Dm, 
         if (k < nc) o[1 + c0 + k] = s1[k];
 }
 
-// One thread a coordinate (point e / D, coordinate e % D): neighbouring threads read neighbouring
-// doubles of a partial.
+// A thread takes one coordinate (point e / D, coordinate e % D) a turn: neighbouring threads read
+// neighbouring doubles of a partial.
 __global__ __launch_bounds__(64) void adjoint_y_finish(Consts kc, int D, int P, double scale,
                                                        const double* __restrict__ yc,
                                                        const double* __restrict__ part, float* __restrict__ grad) {
-    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= kc.m * D) return;
-    const int64_t j = e / D, k = e % D;
-    double s0 = 0.0, s1 = 0.0;
+    const int64_t step = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < kc.m * D; e += step) {
+        const int64_t j = e / D, k = e % D;
+        double s0 = 0.0, s1 = 0.0;
 #pragma unroll 16
-    for (int p = 0; p < P; ++p) {
-        const double* o = part + ((int64_t)p * kc.m + j) * (D + 1);
-        s0 += o[0];
-        s1 += o[1 + k];
+        for (int p = 0; p < P; ++p) {
+            const double* o = part + ((int64_t)p * kc.m + j) * (D + 1);
+            s0 += o[0];
+            s1 += o[1 + k];
+        }
+        grad[e] = (float)(scale * (s0 * yc[e] - s1));
     }
-    grad[e] = (float)(scale * (s0 * yc[e] - s1));
 }
 
 __global__ __launch_bounds__(64) void adjoint_finish(Consts kc, int D, int P, double scale,
                                                      const double* __restrict__ xc, const double* __restrict__ r,
                                                      const double* __restrict__ part, float* __restrict__ grad) {
-    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= kc.n * D) return;
-    const int64_t i = e / D, k = e % D;
+    const int64_t step = (int64_t)gridDim.x * blockDim.x;
     const int W = D + 2;
-    const double off = common_offset(part, P, kc.n, W, i);
-    double s0 = 0.0, s1 = 0.0;
-#pragma unroll 16
-    for (int p = 0; p < P; ++p) {
-        const double* o = part + ((int64_t)p * kc.n + i) * W;
-        s0 += at_offset(o[0], o[1], off);
-        s1 += at_offset(o[0], o[2 + k], off);
-    }
     const double cx = kc.metric == METRIC_SQEUCLID ? 1.0 : 0.0;
-    grad[e] = (float)(scale * r[i] * (cx * xc[e] - s1 / s0));
+    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < kc.n * D; e += step) {
+        const int64_t i = e / D, k = e % D;
+        const double off = common_offset(part, P, kc.n, W, i);
+        double s0 = 0.0, s1 = 0.0;
+#pragma unroll 16
+        for (int p = 0; p < P; ++p) {
+            const double* o = part + ((int64_t)p * kc.n + i) * W;
+            s0 += at_offset(o[0], o[1], off);
+            s1 += at_offset(o[0], o[2 + k], off);
+        }
+        grad[e] = (float)(scale * r[i] * (cx * xc[e] - s1 / s0));
+    }
 }
 
 }  // namespace lampk
