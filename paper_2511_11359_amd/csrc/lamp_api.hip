@@ -69,6 +69,7 @@ int64_t target_blocks_default() {
 // Threads per block of the kernels that merge the splits (row_finish, dual_update): one wave, so that
 // a few thousand points spread over as many CUs as they have waves.
 constexpr int MERGE_BLOCK = 64;
+static_assert(MERGE_BLOCK == 64, "row_finish completes an iteration with 64 threads");
 
 inline size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 inline int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }

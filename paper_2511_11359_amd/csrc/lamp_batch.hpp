@@ -303,7 +303,7 @@ __global__ __launch_bounds__(BLOCK) void batch_dual_update(const ProbDesc* __res
 // Block p completes the iteration of problem p (residual, stop decision, t + 1).
 __global__ __launch_bounds__(BLOCK) void batch_dual_finish(const ProbDesc* __restrict__ pd, const Sched* sched) {
     const ProbDesc& P = pd[blockIdx.x];
-    complete_iteration(P.ctrl, sched, P.respart, nullptr, P.n_dual_blocks);
+    complete_iteration<BLOCK>(P.ctrl, sched, P.respart, nullptr, P.n_dual_blocks);
 }
 
 }  // namespace lampk

@@ -1372,16 +1372,41 @@ __device__ __forceinline__ void dual_update_body(Ctrl* ctrl, const Sched* sched,
 // residual ||col(X^t) - c||_1 as a fixed-order sum over the block partials, the stop decision
 // (iterates t >= 1 only; t = 0 is the product coupling of eta_0 = infinity), and otherwise the D_t
 // summand of the step and t + 1.
+template <int THREADS>
 __device__ __forceinline__ void complete_iteration(Ctrl* ctrl, const Sched* sched, const double* __restrict__ respart,
                                                    const double* __restrict__ dtpart, int64_t nb) {
     const int64_t t = ctrl->t;   // the same control block for every thread: uniform
     if (ctrl->done != 0 || ctrl->t_row != t + 1) return;
-    double a = 0.0, b = 0.0;
-    for (int64_t k = threadIdx.x; k < nb; k += blockDim.x) {
-        a += respart[k];
-        if (dtpart) b += dtpart[k];
+    // BLOCK strided sums in BLOCK / 64 groups of 64 lanes, whatever the block: res_t, and with it the stop,
+    // does not depend on which launch completes the iteration.  16 loads in flight a thread (one at a time,
+    // the wave of row_finish took 32 turns of a full wait for the 2048 partials of 131072 columns).
+    constexpr int R = BLOCK / THREADS, U = 16 / R;
+    double a[R] = {}, b[R] = {};
+    auto add = [&](const double* __restrict__ v, double (&sum)[R]) {
+        for (int64_t k = threadIdx.x; k < nb; k += BLOCK * U) {
+            double x[U][R];
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    const int64_t q = k + u * BLOCK + r * THREADS;
+                    x[u][r] = q < nb ? v[q] : 0.0;
+                }
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int r = 0; r < R; ++r) sum[r] += x[u][r];
+        }
+    };
+    add(respart, a);
+    if (dtpart) add(dtpart, b);
+    double2 sums = make_double2(0.0, 0.0);
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const double2 g = block_sums(a[r], b[r]);
+        sums.x += g.x;
+        sums.y += g.y;
     }
-    const double2 sums = block_sums(a, b);
     __syncthreads();   // every thread has read t and done
     if (threadIdx.x != 0) return;
     const double tot = sums.x;
@@ -1414,7 +1439,7 @@ __global__ void row_finish(Ctrl* ctrl, const Sched* sched, Consts kc, int D,
                            double* __restrict__ log_za, double* __restrict__ log_zb, RowVarF32 rf,
                            const double* __restrict__ respart, int64_t nb) {
     if (nb > 0 && blockIdx.x == gridDim.x - 1) {
-        complete_iteration(ctrl, sched, respart, nullptr, nb);
+        complete_iteration<64>(ctrl, sched, respart, nullptr, nb);
         return;
     }
     row_finish_body(ctrl, sched, kc, D, xc, yc, gtab2, r, xn2, part, P, H, rowvar, rowck, log_za, log_zb, rf,
@@ -1423,7 +1448,7 @@ __global__ void row_finish(Ctrl* ctrl, const Sched* sched, Consts kc, int D,
 
 __global__ __launch_bounds__(BLOCK) void dual_finish(Ctrl* ctrl, const Sched* sched, const double* __restrict__ respart,
                                                      const double* __restrict__ dtpart, int64_t nb) {
-    complete_iteration(ctrl, sched, respart, dtpart, nb);
+    complete_iteration<BLOCK>(ctrl, sched, respart, dtpart, nb);
 }
 
 __global__ __launch_bounds__(BLOCK) void dual_update(Ctrl* ctrl, const Sched* sched, Consts kc,
