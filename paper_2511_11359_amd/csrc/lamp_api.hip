@@ -1359,6 +1359,32 @@ void launch_iteration(const lamp_problem* p, const Layout& L, Consts kc, void* w
     if (!ia.fused) launch_finish(L, kc, ws, ia, st);
 }
 
+// Picoseconds a pair of one row sweep, measured at 16384 x 16384 points: vector ALU d = 1, 3, 8, 16: 0.34, 0.40,
+// 0.60, 0.78 (l1 / l_inf d = 8: 0.74); FP64 matrix cores 32, 64, 128 coordinates: 1.2, 2.1, 3.9; FP32: 4, 16, 64,
+// 128: 0.32, 0.53, 1.2, 2.1; half types 16, 64, 128, 192: 0.28, 0.31, 0.42, 0.54; cost matrix FP32 0.66, 2-byte
+// 0.50; the run-time form d = 9, 20, 150: 19, 76, 1300.
+double row_sweep_ps(const lamp_problem* p, const Layout& L) {
+    if (L.cost) return p->cost_type == COST_F32 ? 0.65 : 0.5;
+    if (is_mfma(L.prec)) return L.esize == 4 ? 0.3 + 0.0145 * L.KP : 0.24 + 0.0015 * L.KP;
+    if (L.use64) return 0.25 + 0.028 * L.KP64;
+    if (p->d > (p->metric == LAMP_SQEUCLID ? 16 : 8)) return std::min(0.2 * p->d * p->d, 1000.0);
+    return 0.32 + 0.028 * p->d;
+}
+
+// Whether a solve completes its iterations in the next one's row_finish.  That saves one of five launches an
+// iteration, 4.5 us of one that runs and 1.5 us of one queued past the stop, and costs a row sweep after a stop.
+// Without a tolerance there is no stop; with one the sweep has to cost less than the launches of the
+// 2 check_every iterations queued for one host check return where the solve stops at once (16384 x 16384,
+// check_every = 64, a stop after the first iteration, fused / not: d = 3 1.77 / 1.86 ms, 16 2.49 / 2.49,
+// 64 4.67 / 4.40, 100 7.25 / 6.43).  Up to 2^28 pairs a launch matters at all.  A tracked iteration's D_t
+// summand waits for the decision.
+bool fuse_completion(const lamp_problem* p, const lamp_params* q, const Layout& L) {
+    const double pairs = (double)p->n * (double)p->m;
+    if (q->track_dt || pairs > 0x1p28) return false;
+    const double checked = q->check_every > 0 ? q->check_every : 64;
+    return !(q->tol > 0.0) || pairs * row_sweep_ps(p, L) * 1e-6 <= 2.0 * 1.5 * checked;
+}
+
 Ctrl start_ctrl(int64_t t, int64_t t_end, double tol, double dt_acc) {
     Ctrl c{};
     c.t = c.t_row = c.t_base = t;
@@ -2000,9 +2026,7 @@ lamp_status lamp_solve(const lamp_problem* prob, const lamp_params* params, lamp
 
     IterArgs ia{};
     ia.track_dt = params->track_dt != 0;
-    // A fused iteration saves one of five launches and costs one row sweep after the stop: up to
-    // 2^28 pairs a sweep (100 us at d = 3) and where its D_t summand need not wait for the decision.
-    ia.fused = !ia.track_dt && (double)kc.n * (double)kc.m <= 0x1p28;
+    ia.fused = fuse_completion(prob, params, L);
     ia.buf.nu[t0 & 1] = state->nu;
     ia.buf.theta[t0 & 1] = state->theta;
     ia.buf.nu[(t0 + 1) & 1] = at<double>(ws, L.nu1);

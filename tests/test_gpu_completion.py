@@ -13,7 +13,9 @@ pytestmark = pytest.mark.gpu
 
 # 64 columns a partial: one round of 64 lanes, one and several rounds of the 256 sums, the ends of their groups
 @pytest.mark.parametrize("n,m,d", [(300, 4096, 2), (300, 4097, 2), (200, 9000, 2), (70, 16449, 3), (40, 70001, 3),
-                                   (30, 270000, 2)])
+                                   (30, 270000, 2),
+                                   # a row sweep that is waited for past a stop after some of the checks only
+                                   (4000, 9000, 3), (700, 4200, 64)])
 def test_residual_and_stop_do_not_depend_on_the_host_checks(n, m, d):
     wl = W.random_small(n, m, d, seed=n, eta=1e-2)
     prob = P.Problem(wl.x, wl.y, wl.r, wl.c, cost_scale=0.1, cost_norm=1.0)
