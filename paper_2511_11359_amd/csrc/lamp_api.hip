@@ -296,8 +296,8 @@ struct Resolved {
 constexpr int SCALARS_SLOT = 40;
 constexpr int SPLIT_SCALE_SLOT = SCALARS_SLOT;   // split FP16 operands and digit planes
 constexpr int REFINE_SLOT = 42;
-constexpr int TOP_SLOT = 44;
-constexpr int MARGINALS_SLOT = 45;
+constexpr int TOP_SLOT = REFINE_SLOT + sizeof(CoarseWatch) / sizeof(double);
+constexpr int MARGINALS_SLOT = TOP_SLOT + 1;
 
 lamp_status check_problem(const lamp_problem* p) {
     if (!p) return fail(LAMP_EINVAL, "problem is NULL");
@@ -378,11 +378,12 @@ lamp_status judge_marginals(const double* h) {
 // Small scalars of a call that the host reads back, all at once (SCALARS_SLOT).
 struct Scalars {
     double range, range_bits;   // the range scale and its running maximum (SPLIT_SCALE_SLOT)
-    double refined;             // the refined cost maximum, its number of candidate tiles and the
-    int tiles, bad;             // flag of the digit planes (REFINE_SLOT)
+    CoarseWatch watch;          // of the coarse passes (REFINE_SLOT)
     double top;                 // the cost maximum (TOP_SLOT)
     double marginals[6];        // marginal_stats
 };
+static_assert(SCALARS_SLOT * sizeof(double) + sizeof(Scalars) <= 64 * sizeof(double), "the small-scalar area");
+static_assert(sizeof(Scalars) == (MARGINALS_SLOT + 6 - SCALARS_SLOT) * sizeof(double), "one double a slot");
 
 lamp_status read_scalars(const Layout& L, void* ws, hipStream_t st, Scalars* out) {
     HIPCHK(hipMemcpyAsync(out, at<double>(ws, L.small) + SCALARS_SLOT, sizeof(Scalars), hipMemcpyDeviceToHost, st));
@@ -554,51 +555,58 @@ bool by_metric(int metric, F&& f) {
 }
 
 template <int KP>
-void row_extreme64(const Layout& L, Consts kc, void* ws, const double* a, double sgn, hipStream_t st) {
+void row_extreme64(const Layout& L, Consts kc, void* ws, const double* a, double sgn, const int* when, hipStream_t st) {
     const int64_t n_waves = L.n_pad64 / 16;
     dim3 g((unsigned)(cdiv(n_waves, 4) * L.P_r64));
     hipLaunchKernelGGL((row_extreme_mfma64<KP>), g, dim3(BLOCK), 0, st, kc, at<double>(ws, L.xop64),
                        at<double>(ws, L.yop64), a, sgn, at<double>(ws, L.rpart), L.tps_r64, (int)L.P_r64,
-                       L.m_pad64 / 16, n_waves);
+                       L.m_pad64 / 16, n_waves, when);
 }
 
-// The part of Scalars at REFINE_SLOT.
-struct Refined {
-    double max;
-    int tiles, bad;
-};
+void launch_row_extreme64(const Layout& L, Consts kc, void* ws, const double* a, double sgn, const int* when,
+                          hipStream_t st) {
+    switch (L.KP64) {
+        case 32: row_extreme64<32>(L, kc, ws, a, sgn, when, st); return;
+        case 64: row_extreme64<64>(L, kc, ws, a, sgn, when, st); return;
+        default: row_extreme64<128>(L, kc, ws, a, sgn, when, st); return;
+    }
+}
+
+CoarseWatch* watch_ptr(const Layout& L, void* ws) {
+    return reinterpret_cast<CoarseWatch*>(at<double>(ws, L.small) + REFINE_SLOT);
+}
 
 // The digit planes of both clouds.
 void launch_digits(const Layout& L, Consts kc, int d, void* ws, hipStream_t st) {
     const double* range = at<double>(ws, L.small) + SPLIT_SCALE_SLOT;
-    auto* ref = reinterpret_cast<Refined*>(at<double>(ws, L.small) + REFINE_SLOT);
+    CoarseWatch* watch = watch_ptr(L, ws);
     launch_range_scale(L, kc.n, kc.m, d, ws, st);
-    hipLaunchKernelGGL(clear_words, dim3(1), dim3(64), 0, st, (int)(sizeof(Refined) / sizeof(int)), (int*)ref);
+    hipLaunchKernelGGL(clear_words, dim3(1), dim3(64), 0, st, (int)(sizeof(CoarseWatch) / sizeof(int)), (int*)watch);
     hipLaunchKernelGGL(prep_digits, grid1(L.n_pad64 * (L.KP8 / 4)), dim3(BLOCK), 0, st, at<double>(ws, L.xc), kc.n, d,
-                       L.KP8, L.n_pad64, range, at<int8_t>(ws, L.xop8), &ref->bad);
+                       L.KP8, L.n_pad64, range, at<int8_t>(ws, L.xop8), &watch->bad);
     hipLaunchKernelGGL(prep_digits, grid1(L.m_pad64 * (L.KP8 / 4)), dim3(BLOCK), 0, st, at<double>(ws, L.yc), kc.m, d,
-                       L.KP8, L.m_pad64, range, at<int8_t>(ws, L.yop8), &ref->bad);
+                       L.KP8, L.m_pad64, range, at<int8_t>(ws, L.yop8), &watch->bad);
 }
 
 template <int KP, int KP64, bool PICK>
 void row_extreme_coarse_kp(const Layout& L, Consts kc, int d, void* ws, const double* a, double sgn,
-                           const double* coarse, hipStream_t st) {
+                           const double* coarse, const double* xn2, hipStream_t st) {
     const int64_t n_tiles = L.n_pad64 / 16;
     dim3 g((unsigned)(cdiv(n_tiles, 4 * coarse_rows(KP)) * L.P_r64));
-    auto* ref = reinterpret_cast<Refined*>(at<double>(ws, L.small) + REFINE_SLOT);
     hipLaunchKernelGGL((row_extreme_coarse<KP, KP64, PICK>), g, dim3(BLOCK), 0, st, kc, d, at<int8_t>(ws, L.xop8),
                        at<int8_t>(ws, L.yop8), at<double>(ws, L.small) + SPLIT_SCALE_SLOT, a, sgn, coarse,
-                       (const int*)&ref->bad, at<double>(ws, L.xop64), at<double>(ws, L.yop64),
+                       xn2, watch_ptr(L, ws), at<double>(ws, L.xop64), at<double>(ws, L.yop64),
                        at<double>(ws, L.rpart), L.tps_r64, (int)L.P_r64, L.m_pad64 / 16, n_tiles);
 }
 
+// xn2: see row_extreme_coarse.
 template <bool PICK>
 void launch_row_extreme_coarse(const Layout& L, Consts kc, int d, void* ws, const double* a, double sgn,
-                               const double* coarse, hipStream_t st) {
+                               const double* coarse, const double* xn2, hipStream_t st) {
     switch (L.KP64) {
-        case 32: row_extreme_coarse_kp<64, 32, PICK>(L, kc, d, ws, a, sgn, coarse, st); return;
-        case 64: row_extreme_coarse_kp<64, 64, PICK>(L, kc, d, ws, a, sgn, coarse, st); return;
-        default: row_extreme_coarse_kp<128, 128, PICK>(L, kc, d, ws, a, sgn, coarse, st); return;
+        case 32: row_extreme_coarse_kp<64, 32, PICK>(L, kc, d, ws, a, sgn, coarse, xn2, st); return;
+        case 64: row_extreme_coarse_kp<64, 64, PICK>(L, kc, d, ws, a, sgn, coarse, xn2, st); return;
+        default: row_extreme_coarse_kp<128, 128, PICK>(L, kc, d, ws, a, sgn, coarse, xn2, st); return;
     }
 }
 
@@ -619,11 +627,8 @@ void launch_row_extreme(const Layout& L, Consts kc, int d, void* ws, const doubl
         return;
     }
     if (L.use64) {
-        switch (L.KP64) {
-            case 32: row_extreme64<32>(L, kc, ws, a, sgn, st); return;
-            case 64: row_extreme64<64>(L, kc, ws, a, sgn, st); return;
-            default: row_extreme64<128>(L, kc, ws, a, sgn, st); return;
-        }
+        launch_row_extreme64(L, kc, ws, a, sgn, nullptr, st);
+        return;
     }
     const dim3 g(sweep_grid(kc.n, L.P_r));
     double* part = at<double>(ws, L.rpart);
@@ -966,8 +971,8 @@ void launch_max(const lamp_problem* p, const Layout& L, void* ws, unsigned long 
 }
 
 // The same with the coarse products first: the few row tiles near the coarse maximum are evaluated
-// in FP64 into Scalars::refined; with many of them (points on a sphere, one-hot features) or a
-// coordinate that is not finite, the host runs launch_max.
+// in FP64 into watch.max; with many of them (one-hot features) or a coordinate that is not finite, the
+// host runs launch_max.
 void launch_max_coarse(const lamp_problem* p, const Layout& L, void* ws, hipStream_t st) {
     const Consts kc = max_consts(p);
     double* a = at<double>(ws, L.scratch);
@@ -975,18 +980,17 @@ void launch_max_coarse(const lamp_problem* p, const Layout& L, void* ws, hipStre
     int* list = reinterpret_cast<int*>(rowmax + std::max(p->n, p->m));
     double* small = at<double>(ws, L.small);
     const double* xn2 = at<double>(ws, L.xn2);
-    auto* ref = reinterpret_cast<Refined*>(small + REFINE_SLOT);
+    CoarseWatch* watch = watch_ptr(L, ws);
     launch_digits(L, kc, p->d, ws, st);
-    launch_row_extreme_coarse<false>(L, kc, p->d, ws, a, +1.0, nullptr, st);
+    launch_row_extreme_coarse<false>(L, kc, p->d, ws, a, +1.0, nullptr, xn2, st);
     hipLaunchKernelGGL(row_extreme_max, grid1(p->n), dim3(BLOCK), 0, st, kc, (const double*)at<double>(ws, L.rpart),
                        extreme_parts(L), xn2, rowmax, top_ptr(L, ws));
     hipLaunchKernelGGL(select_max_tiles, grid1(p->n), dim3(BLOCK), 0, st, p->n, p->d, (const double*)rowmax,
-                       (const double*)(small + TOP_SLOT), (const double*)(small + SPLIT_SCALE_SLOT), list, &ref->tiles);
+                       (const double*)(small + TOP_SLOT), (const double*)(small + SPLIT_SCALE_SLOT), list, watch);
     auto refine = [&](auto kp) {
         hipLaunchKernelGGL((refine_max<decltype(kp)::value>), dim3(COARSE_MAX_TILES * COARSE_MAX_SPLITS), dim3(BLOCK), 0,
                            st, kc, (const double*)at<double>(ws, L.xop64), (const double*)at<double>(ws, L.yop64), xn2,
-                           (const double*)a, (const int*)list, (const int*)&ref->tiles, L.m_pad64 / 16,
-                           reinterpret_cast<unsigned long long*>(ref));
+                           (const double*)a, (const int*)list, L.m_pad64 / 16, watch);
     };
     if (L.KP64 == 32) refine(IC<32>{});
     else if (L.KP64 == 64) refine(IC<64>{});
@@ -1000,8 +1004,9 @@ lamp_status max_cost(const lamp_problem* p, const Layout& L, void* ws, hipStream
         launch_max_coarse(p, L, ws, st);
         HIPCHK(hipGetLastError());
         if ((e = read_scalars(L, ws, st, sc)) != LAMP_OK) return e;
-        if (!sc->bad && sc->tiles <= COARSE_MAX_TILES) {
-            sc->top = sc->refined;
+        const CoarseWatch& w = sc->watch;
+        if (!w.bad && !w.many && w.tiles <= COARSE_MAX_TILES) {
+            std::memcpy(&sc->top, &w.max, sizeof(double));
             return LAMP_OK;
         }
         hipLaunchKernelGGL(split_scale_clear, dim3(1), dim3(1), 0, st, top_ptr(L, ws));
@@ -1133,12 +1138,15 @@ void launch_offsets(const Layout& L, Consts kc, int d, void* ws, hipStream_t st,
         hipLaunchKernelGGL(row_extreme_merge, grid1(kc.n), dim3(BLOCK), 0, st, kc, at<double>(ws, L.rpart),
                            extreme_parts(L), out);
     };
-    if (L.coarse) {
+    // (The minima of a tile's 16 rows alone put 1 - (1 - 16 / m)^16 of its columns' tiles near one: 40% at m = 512,
+    // where both ways take as long.)
+    if (L.coarse && kc.m >= 1024) {
         double* coarse = a + std::max(kc.n, kc.m);
         launch_digits(L, kc, d, ws, st);
-        launch_row_extreme_coarse<false>(L, kc, d, ws, a, -1.0, nullptr, st);
+        launch_row_extreme_coarse<false>(L, kc, d, ws, a, -1.0, nullptr, nullptr, st);
         merge(coarse);
-        launch_row_extreme_coarse<true>(L, kc, d, ws, a, -1.0, coarse, st);
+        launch_row_extreme_coarse<true>(L, kc, d, ws, a, -1.0, coarse, nullptr, st);
+        launch_row_extreme64(L, kc, ws, a, -1.0, &watch_ptr(L, ws)->many, st);   // if they were given up
     } else {
         launch_row_extreme(L, kc, d, ws, a, -1.0, st);
     }

@@ -207,13 +207,16 @@ __global__ void pad_rowq(int64_t n, int64_t n_pad, float4* __restrict__ q) {
 }
 
 // Row extreme sweep on FP64 matrix cores: out_i = min_j (a_j + sgn x~_i . y~_j), exact FP64.
+// Nothing is done if `when` is given and 0.
 template <int KP>
 __global__ __launch_bounds__(BLOCK) void row_extreme_mfma64(Consts kc, const double* __restrict__ xop,
                                                             const double* __restrict__ yop,
                                                             const double* __restrict__ aj, double sgn,
                                                             double* __restrict__ part, int64_t tiles_per_split,
-                                                            int P, int64_t m_tiles, int64_t n_waves) {
+                                                            int P, int64_t m_tiles, int64_t n_waves,
+                                                            const int* __restrict__ when) {
     constexpr int NS = KP / 4;
+    if (when && *when == 0) return;
     const int lane = threadIdx.x & 63;
     const int grp = lane >> 4, c16 = lane & 15;
     const int64_t b = blockIdx.x;
