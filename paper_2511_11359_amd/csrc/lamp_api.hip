@@ -554,6 +554,27 @@ bool by_metric(int metric, F&& f) {
     return f(IC<METRIC_SQEUCLID>{});
 }
 
+// The certificate's pair passes: those, and 32 and 64 coordinates.  The run-time form fetches the own points anew for
+// every eight streamed ones, from the L2s while the cloud is small enough.  A certificate, run-time / compiled:
+// 12000 x 9000 x 32 1.9 / 1.5 ms, 30000 x 30000 11.5 / 9.9, 65536 x 65536 84.6 / 45.3; x 64 30000 x 30000 22.6 / 26.2,
+// 50000 x 50000 74.1 / 74.3, 65536 x 65536 169 / 123, 131072 x 30000 148 / 114, 16000 x 131072 57.9 / 64.8.
+bool cert_compiled(int metric, int d, int64_t own) {
+    return metric == LAMP_SQEUCLID && (d == 32 || (d == 64 && own >= 49152));   // 24 MiB of points
+}
+
+template <int M, typename F>
+bool cert_dispatch(int d, int64_t own, F&& launch) {
+    if (sweep_dispatch<M>(d, launch)) return true;
+    if constexpr (M == METRIC_SQEUCLID) {
+        if (cert_compiled(M, d, own)) {
+            if (d == 32) launch(IC<32>{});
+            else launch(IC<64>{});
+            return true;
+        }
+    }
+    return false;
+}
+
 template <int KP>
 void row_extreme64(const Layout& L, Consts kc, void* ws, const double* a, double sgn, const int* when, hipStream_t st) {
     const int64_t n_waves = L.n_pad64 / 16;
@@ -2181,23 +2202,19 @@ lamp_status lamp_certificate(const lamp_problem* prob, const lamp_params* params
                        at<double2>(ws, L.gtab), gA);
     // pair passes: the kernel of the problem's metric and dimension, coordinates of the
     // thread's own point in registers where compiled (run-time form otherwise)
-    OwnPts xs{at<double>(ws, L.xc), prob->d, 1}, ys{at<double>(ws, L.yc), prob->d, 1};
-    auto by_md = [&](auto&& launch) {
+    auto by_md = [&](int64_t own, auto&& launch) {
         const bool done = by_metric(kc.metric, [&](auto m) {
-            return sweep_dispatch<decltype(m)::value>(prob->d, [&](auto dd) { launch(m, dd); });
+            return cert_dispatch<decltype(m)::value>(prob->d, own, [&](auto dd) { launch(m, dd); });
         });
         if (!done) launch(IC<-1>{}, IC<0>{});
     };
-    if (L.use64) {
-        // d > 16: the run-time form reads the own points coordinate by coordinate; the matrix-core
-        // operand copies (n d and m d doubles or more) are not needed any more
-        xs = OwnPts{at<double>(ws, L.xop64), 1, kc.n};
-        ys = OwnPts{at<double>(ws, L.yop64), 1, kc.m};
-        hipLaunchKernelGGL(transpose_points, grid1(kc.n * prob->d), dim3(BLOCK), 0, st, (const double*)at<double>(ws, L.xc),
-                           kc.n, prob->d, at<double>(ws, L.xop64));
-        hipLaunchKernelGGL(transpose_points, grid1(kc.m * prob->d), dim3(BLOCK), 0, st, (const double*)at<double>(ws, L.yc),
-                           kc.m, prob->d, at<double>(ws, L.yop64));
-    }
+    // d > 16: the run-time form reads the own points coordinate by coordinate; the matrix-core operand copies
+    // (n d and m d doubles or more) are not needed any more
+    auto own_pts = [&](const double* src, double* room, int64_t len) {
+        return cert_compiled(kc.metric, prob->d, len) ? OwnPts{src, prob->d, 1} : own_points(L, src, room, len, prob->d, st);
+    };
+    const OwnPts xs = own_pts(at<double>(ws, L.xc), at<double>(ws, L.xop64), kc.n);
+    const OwnPts ys = own_pts(at<double>(ws, L.yc), at<double>(ws, L.yop64), kc.m);
     // explicit cost: the row-wise passes in the row sweep's layout (coalesced reads of C)
     const dim3 cost_rows_grid((unsigned)cdiv(kc.n, 4 * COST_ROWS));
     if (L.cost) {
@@ -2207,7 +2224,7 @@ lamp_status lamp_certificate(const lamp_problem* prob, const lamp_params* params
                            prob->r, state->nu, state->theta, vals, psum, mu);
         });
     } else {
-        by_md([&](auto m, auto dd) {
+        by_md(kc.n, [&](auto m, auto dd) {
             hipLaunchKernelGGL((cert_rows<decltype(m)::value, decltype(dd)::value>), split_grid, dim3(BLOCK), 0,
                                st, kc, prob->d, cA, xs, at<double>(ws, L.yc),
                                at<double>(ws, L.xn2), at<double>(ws, L.yn2), gA, at<double>(ws, L.H), state->nu,
@@ -2231,7 +2248,7 @@ lamp_status lamp_certificate(const lamp_problem* prob, const lamp_params* params
                            0, st, kc, cA, gA, at<double>(ws, L.H), prob->r, xr, rpart, L.split_cx);
         });
     } else {
-        by_md([&](auto m, auto dd) {
+        by_md(kc.m, [&](auto m, auto dd) {
             hipLaunchKernelGGL((round_cols<decltype(m)::value, decltype(dd)::value>),
                                dim3(sweep_grid(kc.m, L.P_c)), dim3(BLOCK), 0, st, kc, prob->d, cA,
                                at<double>(ws, L.xc), ys, gA, at<double>(ws, L.H), (const float*)wf, rpart, L.split_c);
@@ -2247,7 +2264,7 @@ lamp_status lamp_certificate(const lamp_problem* prob, const lamp_params* params
                            prob->r, xr, yf, dr, cpp);
         });
     } else {
-        by_md([&](auto m, auto dd) {
+        by_md(kc.n, [&](auto m, auto dd) {
             hipLaunchKernelGGL((round_rows<decltype(m)::value, decltype(dd)::value>), split_grid, dim3(BLOCK), 0,
                                st, kc, prob->d, cA, xs, at<double>(ws, L.yc),
                                at<double>(ws, L.xn2), at<double>(ws, L.yn2), gA, at<double>(ws, L.H),
@@ -2267,7 +2284,7 @@ lamp_status lamp_certificate(const lamp_problem* prob, const lamp_params* params
         hipLaunchKernelGGL(round_rank_one, grid1(kc.n), dim3(BLOCK), 0, st, kc, prob->d, at<double>(ws, L.xc),
                            at<double>(ws, L.xn2), dr, S, tr1, absdr);
     } else {
-        by_md([&](auto m, auto dd) {
+        by_md(kc.n, [&](auto m, auto dd) {
             if constexpr (decltype(m)::value != METRIC_SQEUCLID)
                 hipLaunchKernelGGL((round_rank_one_pairs<decltype(m)::value, decltype(dd)::value>), split_grid,
                                    dim3(BLOCK), 0, st, kc, prob->d, xs, at<double>(ws, L.yc), dc, part, L.split_r);
@@ -2286,7 +2303,7 @@ lamp_status lamp_certificate(const lamp_problem* prob, const lamp_params* params
     const bool soft = params->eta > 0.0;
     if (soft) {
         double* sv = vals;   // 2n (the row values above are reduced)
-        by_md([&](auto m, auto dd) {
+        by_md(kc.n, [&](auto m, auto dd) {
             hipLaunchKernelGGL((cert_soft_rows<decltype(m)::value, decltype(dd)::value>), split_grid, dim3(BLOCK),
                                0, st, kc, prob->d, 1.0 / params->eta, xs, at<double>(ws, L.yc), at<double>(ws, L.xn2),
                                at<double>(ws, L.yn2), state->nu, state->theta, (const double*)mu, part, L.split_r);
