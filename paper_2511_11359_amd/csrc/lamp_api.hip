@@ -557,9 +557,9 @@ bool by_metric(int metric, F&& f) {
 // The certificate's pair passes: those, and 32 and 64 coordinates.  The run-time form fetches the own points anew for
 // every eight streamed ones, from the L2s while the cloud is small enough.  A certificate, run-time / compiled:
 // 12000 x 9000 x 32 1.9 / 1.5 ms, 30000 x 30000 11.5 / 9.9, 65536 x 65536 84.6 / 45.3; x 64 30000 x 30000 22.6 / 26.2,
-// 50000 x 50000 74.1 / 74.3, 65536 x 65536 169 / 123, 131072 x 30000 148 / 114, 16000 x 131072 57.9 / 64.8.
+// 60000 x 4000 6.7 / 7.0, x 30000 49.2 / 47.6, 65536 x 4000 10.3 / 7.8, x 65536 169 / 123, 131072 x 30000 148 / 114.
 bool cert_compiled(int metric, int d, int64_t own) {
-    return metric == LAMP_SQEUCLID && (d == 32 || (d == 64 && own >= 49152));   // 24 MiB of points
+    return metric == LAMP_SQEUCLID && (d == 32 || (d == 64 && own >= 61440));   // 30 MiB of points
 }
 
 template <int M, typename F>
