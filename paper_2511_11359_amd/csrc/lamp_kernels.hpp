@@ -1741,18 +1741,29 @@ __global__ void cert_rows_merge(Consts kc, int P, const double* __restrict__ r, 
 // FP64 across them and across the splits (in order).
 //   part[p][i] = (split p's sum for theta, for nu);  vals[0][i] = r_i softmin_i(theta), vals[1][i] likewise.
 // ---------------------------------------------------------------------------
-// The exponent is -lam LOG2E ((C_ij + K v_j) - mu_i), the parenthesis formed with the operations that gave
-// mu_i: it is exactly 0 at the minimum and not negative elsewhere, so that a row's sum lies in [1, m] for
-// every lam.  With lam LOG2E multiplied into each part before they meet (15 instead of 20 vector slots a
-// pair, 1.8 instead of 2.4 ms at 65536 x 65536 x 3) lam times the parts' rounding is left over: from
-// eta = 1e-18 down the sum was 0 or inf.
+// exact: the exponent is f ((C_ij + K v_j) - mu_i), f = -lam LOG2E, the parenthesis formed with the operations
+// that gave mu_i: it is exactly 0 at the minimum and not positive elsewhere, so that a row's sum lies in [1, m]
+// for every lam.  Else it is (2 s lam LOG2E P_ij + b_j) + (f s |x~_i|^2 - f mu_i) with
+// b_j = f (s |y~_j|^2 + K v_j) per column from cert_soft_cols: 15 vector slots a pair at d = 3 instead of 20,
+// 1.8 instead of 2.4 ms at 65536 x 65536, but f times the parts' rounding is left over, which from
+// eta = 1e-18 down ran out of the FP32 exponents (soft_exact has the line).
+__global__ void cert_soft_cols(Consts kc, double lam, const double* __restrict__ yn2,
+                               const double* __restrict__ nu, const double* __restrict__ theta,
+                               double2* __restrict__ out) {
+    const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (j >= kc.m) return;
+    const double f = -lam * LOG2E, b = kc.s * yn2[j];
+    out[j] = make_double2(f * (b + kc.K * theta[j]), f * (b + kc.K * nu[j]));
+}
+
 template <int M, int D>
-__global__ __launch_bounds__(BLOCK) void cert_soft_rows(Consts kc, int Dm, double lam, OwnPts xs,
+__global__ __launch_bounds__(BLOCK) void cert_soft_rows(Consts kc, int Dm, double lam, bool exact, OwnPts xs,
                                                         const double* __restrict__ yc,
                                                         const double* __restrict__ xn2,
                                                         const double* __restrict__ yn2,
                                                         const double* __restrict__ nu,
                                                         const double* __restrict__ theta,
+                                                        const double2* __restrict__ cols,
                                                         const double* __restrict__ mu,
                                                         double* __restrict__ part, int64_t split) {
     const SweepBlock sb = sweep_block(kc.m, split);
@@ -1764,25 +1775,36 @@ __global__ __launch_bounds__(BLOCK) void cert_soft_rows(Consts kc, int Dm, doubl
     const double f = -lam * LOG2E, xi2 = xn2[i], mth = mu[i], mnu = mu[kc.n + i];
     double sth = 0.0, snu = 0.0;
     float at = 0.f, an = 0.f;
-    double K = kc.K;
-    asm("" : "+v"(K));   // one scalar operand an instruction: the column's
-    auto term = [&](double dot, int64_t j) {
-        const double cij = kc.s * (xi2 + yn2[j] - 2.0 * dot);
-        at += fexp2(f * (fma(K, theta[j], cij) - mth));
-        an += fexp2(f * (fma(K, nu[j], cij) - mnu));
-    };
     auto carry = [&] {
         sth += (double)at;
         snu += (double)an;
         at = an = 0.f;
     };
-    int64_t j = j0;
-    for (; j + UNROLL <= j1; j += UNROLL) {
-        terms(own, yc, Dm, j, term);
+    auto run = [&](auto&& term) {
+        int64_t j = j0;
+        for (; j + UNROLL <= j1; j += UNROLL) {
+            terms(own, yc, Dm, j, term);
+            carry();
+        }
+        for (; j < j1; ++j) term(own.pair(yc + j * Dm), j);
         carry();
+    };
+    if (exact) {
+        double K = kc.K;
+        asm("" : "+v"(K));   // one scalar operand an instruction: the column's
+        run([&](double dot, int64_t j) {
+            const double cij = kc.s * (xi2 + yn2[j] - 2.0 * dot);
+            at += fexp2(f * (fma(K, theta[j], cij) - mth));
+            an += fexp2(f * (fma(K, nu[j], cij) - mnu));
+        });
+    } else {
+        const double c = -2.0 * f * kc.s, rth = f * (kc.s * xi2 - mth), rnu = f * (kc.s * xi2 - mnu);
+        run([&](double dot, int64_t j) {
+            const double2 b = cols[j];
+            at += fexp2(fma_su(dot, c, b.x) + rth);
+            an += fexp2(fma_su(dot, c, b.y) + rnu);
+        });
     }
-    for (; j < j1; ++j) term(own.pair(yc + j * Dm), j);
-    carry();
     double* o = part + (sb.p * kc.n + i) * 2;
     o[0] = sth;
     o[1] = snu;
