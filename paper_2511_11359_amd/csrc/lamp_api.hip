@@ -1181,26 +1181,33 @@ void launch_offsets(const Layout& L, Consts kc, int d, void* ws, hipStream_t st,
 // the graph is short, nothing is queued past the call's last iteration, and the first GRAPH_ITERS
 // iterations are launched directly: the GPU runs them while the host captures.  Fewer than
 // 3 GRAPH_ITERS iterations are all launched directly (12 us of host time each, below the GPU's 17 and
-// more).  The graph is destroyed on every return path.
+// more), but not in call after call of a solve that checks often: after 4 GRAPH_ITERS it has a graph too, of as
+// many iterations as a call asks for (64 x 64 x 2, 178 iterations, by check_every 1, 2, 4, 8: 7.10, 4.88, 3.95, 3.42 ->
+// 5.33, 3.94, 3.36, 3.18 ms).  The graph is destroyed on every return path.
 constexpr int GRAPH_ITERS = 8;
 
 struct IterLoop {
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
+    int64_t len = 0;      // its iterations
+    int64_t direct = 0;   // iterations of earlier calls that went without it
 
     template <typename F>
     lamp_status queue(int64_t count, hipStream_t st, F&& iteration) {
-        if (!exec && count >= 3 * GRAPH_ITERS) {
-            for (int k = 0; k < GRAPH_ITERS; ++k) iteration();
-            count -= GRAPH_ITERS;
+        if (!exec && count >= (direct < 4 * GRAPH_ITERS ? 3 * GRAPH_ITERS : 1)) {
+            len = std::min<int64_t>(GRAPH_ITERS, count);
+            for (int64_t k = 0; k < len; ++k) iteration();
+            count -= len;
             HIPCHK(hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal));
-            for (int k = 0; k < GRAPH_ITERS; ++k) iteration();
+            for (int64_t k = 0; k < len; ++k) iteration();
             const hipError_t ce = hipStreamEndCapture(st, &graph);
             if (ce != hipSuccess) return fail(LAMP_EDEVICE, "graph capture failed: %s", hipGetErrorString(ce));
             HIPCHK(hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0));
         }
         if (exec)
-            for (; count >= GRAPH_ITERS; count -= GRAPH_ITERS) HIPCHK(hipGraphLaunch(exec, st));
+            for (; count >= len; count -= len) HIPCHK(hipGraphLaunch(exec, st));
+        else
+            direct += count;
         for (; count > 0; --count) iteration();
         HIPCHK(hipGetLastError());
         return LAMP_OK;
