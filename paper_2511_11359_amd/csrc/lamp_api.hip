@@ -1183,7 +1183,7 @@ void launch_offsets(const Layout& L, Consts kc, int d, void* ws, hipStream_t st,
 // 3 GRAPH_ITERS iterations are all launched directly (12 us of host time each, below the GPU's 17 and
 // more), but not in call after call of a solve that checks often: after 4 GRAPH_ITERS it has a graph too, of as
 // many iterations as a call asks for (64 x 64 x 2, 178 iterations, by check_every 1, 2, 4, 8: 7.10, 4.88, 3.95, 3.42 ->
-// 5.33, 3.94, 3.36, 3.18 ms).  The graph is destroyed on every return path.
+// 4.73, 3.46, 2.92, 2.71 ms).  The graph is destroyed on every return path.
 constexpr int GRAPH_ITERS = 8;
 
 struct IterLoop {

@@ -1283,13 +1283,13 @@ struct TraceCols {
     double *col_a, *col_b, *theta_bar, *theta_hat;
 };
 
-// The sums of a and b over the block (up to BLOCK threads, whole waves), valid in thread 0.
-__device__ __forceinline__ double2 block_sums(double a, double b) {
+// The sums of a and (if asked for) b over the block (up to BLOCK threads, whole waves), valid in thread 0.
+__device__ __forceinline__ double2 block_sums(double a, double b, bool both) {
     __shared__ double2 sh[BLOCK / 64];
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) {
         a += __shfl_xor(a, o, 64);
-        b += __shfl_xor(b, o, 64);
+        if (both) b += __shfl_xor(b, o, 64);
     }
     if (blockDim.x > 64) {
         __syncthreads();   // an earlier call's sums are read
@@ -1366,7 +1366,7 @@ __device__ __forceinline__ void dual_update_body(Ctrl* ctrl, const Sched* sched,
         if (tr.theta_hat) tr.theta_hat[j] = that;
     }
     // block reduction of the residual (and D_t summand; fixed order: deterministic)
-    const double2 tot = block_sums(res, dtj);
+    const double2 tot = block_sums(res, dtj, dtpart != nullptr);
     if (threadIdx.x == 0) {
         respart[bx_] = tot.x;
         if (dtpart) dtpart[bx_] = tot.y;
@@ -1391,6 +1391,10 @@ __device__ __forceinline__ void complete_iteration(Ctrl* ctrl, const Sched* sche
     constexpr int R = BLOCK / THREADS, U = 16 / R;
     double a[R] = {}, b[R] = {};
     auto add = [&](const double* __restrict__ v, double (&sum)[R]) {
+        if (nb <= 64) {
+            if (threadIdx.x < nb) sum[0] = v[threadIdx.x];
+            return;
+        }
         for (int64_t k = threadIdx.x; k < nb; k += BLOCK * U) {
             double x[U][R];
 #pragma unroll
@@ -1411,7 +1415,8 @@ __device__ __forceinline__ void complete_iteration(Ctrl* ctrl, const Sched* sche
     double2 sums = make_double2(0.0, 0.0);
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-        const double2 g = block_sums(a[r], b[r]);
+        if (r * THREADS >= nb) break;   // groups without a partial add 0
+        const double2 g = block_sums(a[r], b[r], dtpart != nullptr);
         sums.x += g.x;
         sums.y += g.y;
     }
