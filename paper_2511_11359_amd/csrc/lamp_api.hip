@@ -186,9 +186,11 @@ Layout layout(int64_t n, int64_t m, int d, int prec = LAMP_FP32, int64_t target 
               (uint64_t)std::max(L.n_pad64, L.m_pad64) * (uint64_t)(L.KP64 * 8) < (1ull << 32) &&
               std::max(n, m) < ((int64_t)1 << 28);
     // Coarse products pay once the FP64 pass (0.11 ms per 2^31 padded products) outlasts their six
-    // extra launches; operand planes below 4 GiB as above.
+    // extra launches, and the digits of the targets where there are rows to use them (the maximum in FP64 products /
+    // with digits: 64 x 10^6 x 64 3.0 / 3.5 ms, 128 x 10^6 3.2 / 3.4, 250 x 500000 1.8 / 1.7); operand planes below
+    // 4 GiB as above.
     L.KP8 = d <= 64 ? 64 : 128;
-    L.coarse = L.use64 && (double)n * (double)m * L.KP64 >= 0x1p31 &&
+    L.coarse = L.use64 && n >= 192 && (double)n * (double)m * L.KP64 >= 0x1p31 &&
                (uint64_t)std::max(L.n_pad64, L.m_pad64) * (uint64_t)(COARSE_DIGITS * L.KP8) < (1ull << 32);
     L.cost = metric == METRIC_EXPLICIT;
     if (L.cost) {
@@ -438,9 +440,19 @@ lamp_status prep_L(const lamp_problem* p, const Layout& L, void* ws, hipStream_t
         HIPCHK(hipGetLastError());
         return LAMP_OK;
     }
-    hipLaunchKernelGGL(prep_points, grid1(p->n + p->m), dim3(BLOCK), 0, st, p->x, p->n, p->y, p->m, p->d,
-                       at<double>(ws, L.xc), at<double>(ws, L.xn2), at<float>(ws, L.xcf), at<double>(ws, L.yc),
-                       at<double>(ws, L.yn2), at<float>(ws, L.ycf), p->metric, mx);
+    auto prep = [&](int64_t n, int64_t m) {
+        hipLaunchKernelGGL(prep_points, grid1(n + m), dim3(BLOCK), 0, st, p->x, n, p->y, m, p->d,
+                           at<double>(ws, L.xc), at<double>(ws, L.xn2), at<float>(ws, L.xcf), at<double>(ws, L.yc),
+                           at<double>(ws, L.yn2), at<float>(ws, L.ycf), p->metric, mx);
+    };
+    // one launch for both clouds, or one each where their strided lines together overrun the L2s (65536 and 65536
+    // points at d = 16 63 / 28 us, 64 313 / 236; at d = 8 12 / 15, 8192 and 8192 at d = 64 36 / 68)
+    if (p->d >= 16 && std::min(p->n, p->m) * p->d >= (1 << 20)) {
+        prep(p->n, 0);
+        prep(0, p->m);
+    } else {
+        prep(p->n, p->m);
+    }
     if (L.use64) {
         hipLaunchKernelGGL(prep_operands64, grid1(L.n_pad64 * L.KP64), dim3(BLOCK), 0, st, at<double>(ws, L.xc),
                            p->n, p->d, L.KP64, L.n_pad64, at<double>(ws, L.xop64));
