@@ -1293,8 +1293,9 @@ struct IterArgs {
     bool fused;   // the next iteration's row_finish completes this one (launch_finish after the last)
 };
 
-// <C, Xbar^{t+1}> of the running iteration into ctrl->dt_cost (D_t tracking); runs after
-// the row sweep, with the offsets and column table that sweep used.
+// <C, Xbar^{t+1}> of the running iteration into ctrl->dt_cost (D_t tracking) for the cost matrix and the run-time
+// dimensions (launch_row_sweep_dt has the others); runs after the row sweep, with the offsets and column table that
+// sweep used.
 void launch_dt_cost(const lamp_problem* p, const Layout& L, Consts kc, void* ws, hipStream_t st) {
     Ctrl* ctrl = at<Ctrl>(ws, L.ctrl);
     const Sched* sch = at<Sched>(ws, L.sched);
@@ -1315,15 +1316,8 @@ void launch_dt_cost(const lamp_problem* p, const Layout& L, Consts kc, void* ws,
         hipLaunchKernelGGL(dt_cost_total, dim3(1), dim3(1024), 0, st, ctrl, (const double*)out, kc.n);
         return;
     }
-    const bool done = by_metric(kc.metric, [&](auto m) {
-        return valu_dispatch<decltype(m)::value>(d, [&](auto dd) {
-            hipLaunchKernelGGL((dt_cost_rows<decltype(m)::value, decltype(dd)::value>), grid1(kc.n), dim3(BLOCK), 0,
-                               st, ctrl, sch, kc, xc, yc, xn2, yn2, gt, H, p->r, out);
-        });
-    });
-    if (!done)
-        hipLaunchKernelGGL(dt_cost_rows_dyn, grid1(kc.n), dim3(BLOCK), 0, st, ctrl, sch, kc, d, xc, yc, xn2, yn2, gt,
-                           H, p->r, out);
+    hipLaunchKernelGGL(dt_cost_rows_dyn, grid1(kc.n), dim3(BLOCK), 0, st, ctrl, sch, kc, d, xc, yc, xn2, yn2, gt, H,
+                       p->r, out);
     hipLaunchKernelGGL(dt_cost_total, dim3(1), dim3(1024), 0, st, ctrl, (const double*)out, kc.n);
 }
 
@@ -1918,8 +1912,8 @@ lamp_status batch_tune(const lamp_problem* probs, int count, const lamp_params* 
         HIPCHK(hipEventSynchronize(e1));
         float ms = 0.f;
         HIPCHK(hipEventElapsedTime(&ms, e0, e1));
-        // half a percent is within the noise of the timing: the earlier shape keeps the place, so
-        // that the splits, and with them the FP32 sums, do not change from process to process
+        // the earlier shape keeps its place within half a percent, so that a tie mostly goes the same way from process
+        // to process; a timing that is off by more still changes the splits, and with them the last bits of the sums
         if (ms < 0.995f * best_ms) {
             best_ms = ms;
             best_c = c;

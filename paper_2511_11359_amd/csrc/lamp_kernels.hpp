@@ -1097,45 +1097,6 @@ __global__ __launch_bounds__(BLOCK) void col_sweep_dyn(const Ctrl* ctrl, const S
 // Same arithmetic as the row sweep (FP64 exponent, FP32 exponential and per-block
 // sums, FP64 across blocks); one thread per row over all columns.
 // ---------------------------------------------------------------------------
-template <int M, int D>
-__global__ __launch_bounds__(BLOCK) void dt_cost_rows(const Ctrl* ctrl, const Sched* sched, Consts kc,
-                                                      const double* __restrict__ xc,
-                                                      const double* __restrict__ yc,
-                                                      const double* __restrict__ xn2,
-                                                      const double* __restrict__ yn2,
-                                                      const double2* __restrict__ gtab2,
-                                                      const double* __restrict__ H,
-                                                      const double* __restrict__ r,
-                                                      double* __restrict__ out) {
-    if (halted(ctrl)) return;
-    const int64_t t = ctrl->t;
-    const Sched sc = sched[t - ctrl->t_base];
-    const double cB = 2.0 * kc.s * sc.lamB * LOG2E;
-    const double2* __restrict__ g = gtab2 + (t & 1) * kc.m;
-    const int64_t i = (int64_t)blockIdx.x * BLOCK + threadIdx.x;
-    const int64_t ii = i < kc.n ? i : kc.n - 1;
-    double x[D];
-#pragma unroll
-    for (int k = 0; k < D; ++k) x[k] = xc[ii * D + k];
-    const double h = H[ii];
-    const double xa = kc.s * xn2[ii];
-    double S = 0.0, T = 0.0;
-    for (int64_t jb = 0; jb < kc.m; jb += UNROLL) {
-        float aS = 0.f, aT = 0.f;
-        const int64_t je = min(kc.m, jb + UNROLL);
-        for (int64_t j = jb; j < je; ++j) {
-            const double dot = pair_term<M, D>(x, yc + j * D, 0.0);
-            const float p = fexp2(fma(cB, h + dot, g[j].y));
-            const double cij = fma(-2.0 * kc.s, dot, xa + kc.s * yn2[j]);
-            aS += p;
-            aT = fmaf(p, (float)cij, aT);
-        }
-        S += (double)aS;
-        T += (double)aT;
-    }
-    if (i < kc.n) out[i] = r[i] * T / S;
-}
-
 __global__ __launch_bounds__(BLOCK) void dt_cost_rows_dyn(const Ctrl* ctrl, const Sched* sched, Consts kc, int D,
                                                           const double* __restrict__ xc,
                                                           const double* __restrict__ yc,
@@ -2045,14 +2006,6 @@ __global__ void round_rank_one(Consts kc, int D, const double* __restrict__ xc, 
     for (int k = 0; k < D; ++k) xs = fma(xc[i * D + k], S[k], xs);
     t[i] = dr[i] * kc.s * (xn2[i] * S[D] + S[D + 1] - 2.0 * xs);
     absdr[i] = fabs(dr[i]);
-}
-
-// g^A_j for an arbitrary (lam, v): gA_j = -lam LOG2E (s yn2_j + K v_j).
-__global__ void col_table_single(Consts kc, double lam, const double* __restrict__ yn2,
-                                 const double* __restrict__ v, double* __restrict__ gA) {
-    int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= kc.m) return;
-    gA[j] = -lam * LOG2E * (kc.s * yn2[j] + kc.K * v[j]);
 }
 
 // c_j * theta_j products for <c, theta>, <c, nu>.

@@ -110,3 +110,12 @@ def test_batch_with_problems_of_the_coarse_passes(kind):
         tol = 8e-6 * col / (1.0 / prob.m + 0.01 / prob.m) + 1e-12
         assert np.all(np.abs(to_np(s.theta) - to_np(one.theta)) <= tol)
         assert np.all(np.abs(to_np(s.nu) - to_np(one.nu)) <= tol)
+
+
+@pytest.mark.parametrize("n", [191, 192])
+def test_maximum_on_both_sides_of_the_fewest_rows(n):
+    m, d = 180001, 64
+    x, y = _clouds("normal", n, m, d)
+    whole = P.cost_scale(P.Problem(x, y, _uniform(n), _uniform(m)))[1]
+    parts = [torch.cat([x[:1], x[a:a + 64]]) for a in range(1, n, 64)]
+    assert whole == max(P.cost_scale(P.Problem(q, y, _uniform(len(q)), _uniform(m)))[1] for q in parts)
