@@ -1513,12 +1513,6 @@ lamp_status state_normalisers(const lamp_problem* p, const lamp_params* q, const
     return LAMP_OK;
 }
 
-// Which form of the entropic pass's exponents cert_soft_rows takes.  The parts of the faster one are s |x~|^2,
-// s |y~|^2 (a centred point lies within 1.5 of the largest distance: 2.25 ||C||_inf) and K v: up to this line their
-// rounding moves an exponent by some 2^-15, and a dual value, eta times that, by less than its own rounding.  The
-// sums fail only another 2^22 further on.
-bool soft_exact(double eta, const Resolved& R) { return !((R.cnorm + R.K) / eta <= 0x1p36); }
-
 // g^A_j = -lam_t LOG2E (s |y~_j|^2 + K nu_j): the column term of X^t's exponents (base 2).
 __global__ void state_col_term(Consts kc, double lam, const double* __restrict__ yn2,
                                const double* __restrict__ nu, double* __restrict__ gA) {
@@ -2323,15 +2317,15 @@ lamp_status lamp_certificate(const lamp_problem* prob, const lamp_params* params
     const bool soft = params->eta > 0.0;
     if (soft) {
         double* sv = vals;   // 2n (the row values above are reduced)
-        const bool exact = soft_exact(params->eta, R);
-        if (!exact)
-            hipLaunchKernelGGL(cert_soft_cols, grid1(kc.m), dim3(BLOCK), 0, st, kc, 1.0 / params->eta,
-                               at<double>(ws, L.yn2), state->nu, state->theta, soft_cols);
+        auto* largest = reinterpret_cast<unsigned long long*>(small + 13);
+        hipLaunchKernelGGL(split_scale_clear, dim3(1), dim3(1), 0, st, largest);
+        hipLaunchKernelGGL(cert_soft_cols, grid1(std::min<int64_t>(kc.m, 64 * BLOCK)), dim3(BLOCK), 0, st, kc,
+                           1.0 / params->eta, at<double>(ws, L.yn2), state->nu, state->theta, soft_cols, largest);
         by_md(kc.n, [&](auto m, auto dd) {
             hipLaunchKernelGGL((cert_soft_rows<decltype(m)::value, decltype(dd)::value>), split_grid, dim3(BLOCK),
-                               0, st, kc, prob->d, 1.0 / params->eta, exact, xs, at<double>(ws, L.yc),
-                               at<double>(ws, L.xn2), at<double>(ws, L.yn2), state->nu, state->theta,
-                               (const double2*)soft_cols, (const double*)mu, part, L.split_r);
+                               0, st, kc, prob->d, 1.0 / params->eta, xs, at<double>(ws, L.yc), at<double>(ws, L.xn2),
+                               at<double>(ws, L.yn2), state->nu, state->theta, (const double2*)soft_cols,
+                               (const double*)largest, (const double*)mu, part, L.split_r);
         });
         hipLaunchKernelGGL(cert_soft_merge, grid1(kc.n), dim3(BLOCK), 0, st, kc, (int)L.P_r, 1.0 / params->eta,
                            prob->r, (const double*)mu, (const double*)part, sv);

@@ -1715,29 +1715,40 @@ __global__ void cert_rows_merge(Consts kc, int P, const double* __restrict__ r, 
 // FP64 across them and across the splits (in order).
 //   part[p][i] = (split p's sum for theta, for nu);  vals[0][i] = r_i softmin_i(theta), vals[1][i] likewise.
 // ---------------------------------------------------------------------------
-// exact: the exponent is f ((C_ij + K v_j) - mu_i), f = -lam LOG2E, the parenthesis formed with the operations
-// that gave mu_i: it is exactly 0 at the minimum and not positive elsewhere, so that a row's sum lies in [1, m]
-// for every lam.  Else it is (2 s lam LOG2E P_ij + b_j) + (f s |x~_i|^2 - f mu_i) with
-// b_j = f (s |y~_j|^2 + K v_j) per column from cert_soft_cols: 15 vector slots a pair at d = 3 instead of 20,
-// 1.8 instead of 2.4 ms at 65536 x 65536, but f times the parts' rounding is left over, which from
-// eta = 1e-18 down ran out of the FP32 exponents (soft_exact has the line).
+// The exponent is f ((C_ij + K v_j) - mu_i), f = -lam LOG2E, the parenthesis formed with the operations that gave
+// mu_i: it is exactly 0 at the minimum and not positive elsewhere, so that a row's sum lies in [1, m] for every lam.
+// Where the parts are small enough it is (2 s lam LOG2E P_ij + b_j) + (f s |x~_i|^2 - f mu_i) instead, with
+// b_j = f (s |y~_j|^2 + K v_j) per column from cert_soft_cols: 15 vector slots a pair at d = 3 instead of 20, 1.8
+// instead of 2.4 ms at 65536 x 65536.  What f times the parts' rounding leaves over moves an exponent by
+// 2^-52 of their sum: with parts up to SOFT_PARTS by 2^-16, and a dual value, 1 / lam times that, by less than its own
+// rounding; 2^22 further on the sums would run out of the FP32 exponents.  (2 s lam LOG2E P_ij is no larger than the
+// other parts together, or the exponent is as large as it.)  Per wave, by its rows' parts and the largest of a column.
+constexpr double SOFT_PARTS = 0x1p36;
+
 __global__ void cert_soft_cols(Consts kc, double lam, const double* __restrict__ yn2,
                                const double* __restrict__ nu, const double* __restrict__ theta,
-                               double2* __restrict__ out) {
-    const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= kc.m) return;
-    const double f = -lam * LOG2E, b = kc.s * yn2[j];
-    out[j] = make_double2(f * (b + kc.K * theta[j]), f * (b + kc.K * nu[j]));
+                               double2* __restrict__ out, unsigned long long* __restrict__ largest) {
+    const double f = -lam * LOG2E;
+    double most = 0.0;
+    for (int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j < kc.m; j += (int64_t)gridDim.x * blockDim.x) {
+        const double b = kc.s * yn2[j], kt = kc.K * theta[j], kn = kc.K * nu[j];
+        out[j] = make_double2(f * (b + kt), f * (b + kn));
+        most = fmax(most, -f * (b + fmax(fabs(kt), fabs(kn))));
+    }
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) most = fmax(most, __shfl_xor(most, o, 64));
+    if ((threadIdx.x & 63) == 0) atomicMax(largest, (unsigned long long)__double_as_longlong(most));
 }
 
 template <int M, int D>
-__global__ __launch_bounds__(BLOCK) void cert_soft_rows(Consts kc, int Dm, double lam, bool exact, OwnPts xs,
+__global__ __launch_bounds__(BLOCK) void cert_soft_rows(Consts kc, int Dm, double lam, OwnPts xs,
                                                         const double* __restrict__ yc,
                                                         const double* __restrict__ xn2,
                                                         const double* __restrict__ yn2,
                                                         const double* __restrict__ nu,
                                                         const double* __restrict__ theta,
                                                         const double2* __restrict__ cols,
+                                                        const double* __restrict__ largest,
                                                         const double* __restrict__ mu,
                                                         double* __restrict__ part, int64_t split) {
     const SweepBlock sb = sweep_block(kc.m, split);
@@ -1763,7 +1774,8 @@ __global__ __launch_bounds__(BLOCK) void cert_soft_rows(Consts kc, int Dm, doubl
         for (; j < j1; ++j) term(own.pair(yc + j * Dm), j);
         carry();
     };
-    if (exact) {
+    const double parts = *largest - f * (kc.s * xi2 + fmax(fabs(mth), fabs(mnu)));
+    if (!__all(parts <= SOFT_PARTS)) {
         double K = kc.K;
         asm("" : "+v"(K));   // one scalar operand an instruction: the column's
         run([&](double dot, int64_t j) {

@@ -60,3 +60,16 @@ def test_cost_matrix(dtype):
     prob = P.Problem.from_cost(mat.cuda(), wl.r, wl.c, cost_scale=s, cost_norm=1.0)
     for eta in ETAS:
         _check(prob, s * full, at, st, wl.r, wl.c, eta, 1)
+
+
+@pytest.mark.parametrize("d,kind", [(3, "sqeuclid"), (24, "sqeuclid"), (5, "l1")])
+def test_costs_far_above_the_stated_norm(d, kind):
+    """What bounds the exponents' parts is the data, whatever cost_norm says: costs of 1e30 at eta = 1e-3 are as
+    eta = 1e-33 for costs of 1."""
+    wl = W.random_small(90, 76, d, seed=7, eta=1e-2)
+    big = 1e15 if kind == "sqeuclid" else 1e30
+    prob = P.Problem(wl.x * np.float32(big), wl.y * np.float32(big), wl.r, wl.c, cost_scale=1.0, cost_norm=1.0, metric=kind)
+    z = torch.zeros(76, dtype=torch.float64, device="cuda")
+    cert = P.certificate(prob, P.make_params(eta=1e-3), P.State(z, z.clone(), 3, 2.5))
+    for key in ("theta", "nu"):
+        assert cert["dual_eta_" + key] == pytest.approx(cert["dual_" + key], rel=1e-12)
