@@ -300,9 +300,9 @@ __global__ __launch_bounds__(BLOCK, 2) void row_extreme_coarse(Consts kc, int d,
                 }
             }
             if constexpr (PICK) {
-                // A near tile costs 2.2 times its share of the FP64 pass (65536 x 65536 x 64, all of them: 31.7 ms against
-                // 14.6, after 3.4 ms of coarse passes): above 3/8 of them that pass is the shorter way.  A wave that
-                // meets as many says so, and stops its block once as many of the reporting waves have.
+                // A near tile costs 2.2 times its share of the FP64 pass (65536 x 65536 x 64, all of them: 31.7 ms
+                // against 14.6, after 3.4 ms of coarse passes): above 3/8 of them that pass is the shorter way.
+                // A wave that meets as many says so, and stops its block once as many of the reporting waves have.
                 if (picked >= 8 && 8 * picked > 3 * RT * (jt - jt0 + 1) && lane == 0) {
                     if (report && !dense) {
                         const Count c = count_in(&watch->second, 1, 0);
