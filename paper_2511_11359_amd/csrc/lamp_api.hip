@@ -445,9 +445,10 @@ lamp_status prep_L(const lamp_problem* p, const Layout& L, void* ws, hipStream_t
                            at<double>(ws, L.xc), at<double>(ws, L.xn2), at<float>(ws, L.xcf), at<double>(ws, L.yc),
                            at<double>(ws, L.yn2), at<float>(ws, L.ycf), p->metric, mx);
     };
-    // one launch for both clouds, or one each where their strided lines together overrun the L2s (65536 and 65536
-    // points at d = 16 63 / 28 us, 64 313 / 236; at d = 8 12 / 15, 8192 and 8192 at d = 64 36 / 68)
-    if (p->d >= 16 && std::min(p->n, p->m) * p->d >= (1 << 20)) {
+    // one launch for both clouds, or one each where their strided lines together overrun the L2s and either fills the
+    // chip by itself (65536 and 65536 points at d = 16 63 / 28 us, 64 313 / 236; at d = 8 12 / 15, 8192 and 8192 at
+    // d = 64 36 / 68, 12000 and 9000 at d = 128 85 / 134)
+    if (p->d >= 16 && std::min(p->n, p->m) >= 32768) {
         prep(p->n, 0);
         prep(0, p->m);
     } else {
@@ -2247,7 +2248,9 @@ lamp_status lamp_certificate(const lamp_problem* prob, const lamp_params* params
         hipLaunchKernelGGL(cert_rows_merge, grid1(kc.n), dim3(BLOCK), 0, st, kc, (int)L.P_r, prob->r,
                            (const double*)part, vals, psum, mu);
     }
-    hipLaunchKernelGGL(col_products, grid1(kc.m), dim3(BLOCK), 0, st, kc, prob->c, state->theta, state->nu, prods);
+    auto* largest = reinterpret_cast<unsigned long long*>(small + 13);   // of cert_soft_cols, cleared here
+    hipLaunchKernelGGL(col_products, grid1(kc.m), dim3(BLOCK), 0, st, kc, prob->c, state->theta, state->nu, prods,
+                       largest);
     hipLaunchKernelGGL(reduce_sums, dim3(4), dim3(1024), 0, st, vals, kc.n, kc.n, small);
     hipLaunchKernelGGL(reduce_sums, dim3(1), dim3(1024), 0, st, colres, kc.m, kc.m, small + 4);
     hipLaunchKernelGGL(reduce_sums, dim3(2), dim3(1024), 0, st, prods, kc.m, kc.m, small + 5);
@@ -2317,8 +2320,6 @@ lamp_status lamp_certificate(const lamp_problem* prob, const lamp_params* params
     const bool soft = params->eta > 0.0;
     if (soft) {
         double* sv = vals;   // 2n (the row values above are reduced)
-        auto* largest = reinterpret_cast<unsigned long long*>(small + 13);
-        hipLaunchKernelGGL(split_scale_clear, dim3(1), dim3(1), 0, st, largest);
         hipLaunchKernelGGL(cert_soft_cols, grid1(std::min<int64_t>(kc.m, 64 * BLOCK)), dim3(BLOCK), 0, st, kc,
                            1.0 / params->eta, at<double>(ws, L.yn2), state->nu, state->theta, soft_cols, largest);
         by_md(kc.n, [&](auto m, auto dd) {

@@ -2020,10 +2020,12 @@ __global__ void round_rank_one(Consts kc, int D, const double* __restrict__ xc, 
     absdr[i] = fabs(dr[i]);
 }
 
-// c_j * theta_j products for <c, theta>, <c, nu>.
+// c_j * theta_j products for <c, theta>, <c, nu>; clears a word for a later maximum.
 __global__ void col_products(Consts kc, const double* __restrict__ c, const double* __restrict__ a,
-                             const double* __restrict__ b, double* __restrict__ out) {
+                             const double* __restrict__ b, double* __restrict__ out,
+                             unsigned long long* __restrict__ clear) {
     int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (j == 0) *clear = 0ull;
     if (j >= kc.m) return;
     out[j] = c[j] * a[j];
     out[kc.m + j] = c[j] * b[j];
