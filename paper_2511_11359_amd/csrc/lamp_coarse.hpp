@@ -20,7 +20,7 @@
 // instead, on the device's own word for the offsets and after the host's wait for the maximum.  One step /
 // the maximum, tile by tile -> given up, against the FP64 pass from the start: one-hot 65536 x 65536 x 64
 // 52.1 -> 32.7 (32.5) / 16.6 -> 15.5 (15.0) ms, x 24 26.5 -> 18.2 (17.9) / 9.3 -> 8.3 (7.8), 8192 x 8192 x 64
-// 0.98 -> 0.92 (0.78) / 0.45 (0.38); an outlier, 40000 x 30000 x 100 31.0 -> 18.6 (18.5) / 1.1 (8.6).
+// 0.98 -> 0.79 (0.78) / 0.45 (0.38); an outlier, 40000 x 30000 x 100 31.0 -> 18.6 (18.5) / 1.1 (8.6).
 //
 // Per pair of points: 6 KP / 64 x 16 matrix cycles a 16 x 16 tile and 6 vector slots (a shift, two
 // conversions, two FMAs, a minimum or a comparison): at 2^16, d = 64 1.7 ms a pass, 2.4 ms with the
@@ -40,7 +40,7 @@ struct CoarseWatch {
     int tiles;                // row tiles that can hold the maximum
     int bad;                  // a coordinate without digits
     int many;                 // too many near tiles: the coarse passes are given up
-    int pad;
+    int pairs;                // first pass, offsets: near pairs in the near tiles
     // of the reporting blocks, counts in the halves of a word: those seen above, the near ones below
     unsigned long long first;    // row tiles (offsets) or waves (maximum) of the first pass
     unsigned long long second;   // waves of the second pass, those that meet near tiles most of the time
@@ -326,41 +326,45 @@ __global__ __launch_bounds__(BLOCK, 2) void row_extreme_coarse(Consts kc, int d,
         }
     }
     if constexpr (!PICK) {
-        // What the split says of the data.  Offsets: whether its last tile, still in LDS, is near the split's
-        // minima (more often than near the rows', and 22% of the tiles are by their 16 rows' minima alone where a
-        // split has 64: three in four have to be).  Maximum: whether the wave's largest row value ties with that
-        // of the blocks before.
+        // What the split says of the data.  Offsets: whether its last tile, still in LDS, is near the split's minima
+        // (more often than near the rows').  Of T tiles 1 - (1 - 1 / T)^16 are by the minima of their 16 rows alone,
+        // with 16 / T pairs: 64% and 1 at the fewest asked, 16.  So three in four tiles have to be, with a pair a
+        // tile beyond twice that.  Maximum: whether the wave's largest row value ties with that of the blocks before.
         __shared__ double tops[4];
-        __shared__ int nears[4];
+        __shared__ int nears[4], pairs[4];
         // (The maximum only where blocks are still to start and ask: 12000 x 9000 x 24 58 us, 65 with the question.)
         const bool for_max = xn2 != nullptr;
-        if (report && (for_max ? gridDim.x > 512 && tiles_per_split >= 32 : jt1 - jt0 >= 64)) {
+        if (report && (for_max ? gridDim.x > 512 && tiles_per_split >= 32 : jt1 - jt0 >= 16)) {
             Digits<KP> bv;
             double aval, top = 0.0;
-            int near_tiles = 0;
+            int near_tiles = 0, near_pairs = 0;
             tile_load((jt1 - jt0) & 1, jl, bv, aval);
 #pragma unroll
             for (int u = 0; u < RT; ++u) {
                 double v[4];
                 if (!for_max) values(u, bv, aval, v);
-                bool near = false;
+                int cnt = 0;
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
                     double m = best[u][r];
 #pragma unroll
                     for (int o = 8; o > 0; o >>= 1) m = fmin(m, __shfl_xor(m, o, 64));
                     const int64_t i = (rt0 + u) * 16 + 4 * grp + r;
-                    if (i >= kc.n) continue;
-                    if (for_max) top = fmax(top, xn2[i] - 2.0 * m);
-                    else near = near || v[r] <= m + slack;
+                    if (for_max) {
+                        if (i < kc.n) top = fmax(top, xn2[i] - 2.0 * m);
+                    } else {
+                        cnt += __popcll(__ballot(i < kc.n && v[r] <= m + slack));
+                    }
                 }
-                near_tiles += __any(near) ? 1 : 0;
+                near_tiles += cnt > 0;
+                near_pairs += cnt;
             }
 #pragma unroll
             for (int o = 32; o >= 16; o >>= 1) top = fmax(top, __shfl_xor(top, o, 64));
             if (lane == 0) {
                 tops[threadIdx.x >> 6] = top;
                 nears[threadIdx.x >> 6] = near_tiles;
+                pairs[threadIdx.x >> 6] = near_pairs;
             }
             __syncthreads();
             if (threadIdx.x == 0) {
@@ -371,8 +375,11 @@ __global__ __launch_bounds__(BLOCK, 2) void row_extreme_coarse(Consts kc, int d,
                         &watch->top, (unsigned long long)__double_as_longlong(most)));
                     for (int w = 0; w < 4; ++w) near += fabs(tops[w] - old) <= 2.0 * slack;
                 }
+                int all = pairs[0] + pairs[1] + pairs[2] + pairs[3];
+                if (!for_max) all += atomicAdd(&watch->pairs, all);
                 const Count c = count_in(&watch->first, near, for_max ? 4 : 4 * RT);
-                if (c.seen >= 128 && 4 * c.near > 3 * c.seen) give_up(&watch->many);
+                const bool plenty = for_max || (double)all * tiles_per_split > (32.0 + tiles_per_split) * c.seen;
+                if (c.seen >= 128 && 4 * c.near > 3 * c.seen && plenty) give_up(&watch->many);
             }
         }
     }
