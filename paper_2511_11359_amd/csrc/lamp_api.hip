@@ -1453,6 +1453,13 @@ void launch_open(const Layout& L, Consts kc, void* ws, const double* nu, const d
                        is_mfma(L.prec) ? (double*)nullptr : at<double>(ws, L.scratch), init);
 }
 
+// A call stopped by its marginals (err bit 1): their statistics, judged.
+lamp_status stopped_by_marginals(const Layout& L, void* ws, hipStream_t st) {
+    Scalars sc;
+    lamp_status e = read_scalars(L, ws, st, &sc);
+    return e != LAMP_OK ? e : judge_marginals(sc.marginals);
+}
+
 // Checks the arguments, prepares the points and resolves the constants.  The marginals are judged
 // here if the host has to wait for the device anyway or `defer` is null; else *defer points to their
 // statistics, which the call's first kernel judges on the device (a wait less).
@@ -1474,14 +1481,10 @@ lamp_status common_setup(const lamp_problem* p, const lamp_params* q, void* ws, 
     } else {
         *defer = marginals_ptr(L, ws);
     }
-    return resolve(p, q, L, sc.top, sc.range, R);
-}
-
-// A call stopped by its marginals (err bit 1): their statistics, judged.
-lamp_status stopped_by_marginals(const Layout& L, void* ws, hipStream_t st) {
-    Scalars sc;
-    lamp_status e = read_scalars(L, ws, st, &sc);
-    return e != LAMP_OK ? e : judge_marginals(sc.marginals);
+    if ((e = resolve(p, q, L, sc.top, sc.range, R)) == LAMP_OK || !defer || !*defer) return e;
+    // refused before any kernel judges the marginals: a fault of theirs is the one to report
+    const lamp_status bad = stopped_by_marginals(L, ws, st);
+    return bad != LAMP_OK ? bad : resolve(p, q, L, sc.top, sc.range, R);
 }
 
 lamp_status check_state(const lamp_state* s) {
