@@ -1718,7 +1718,7 @@ __global__ void cert_rows_merge(Consts kc, int P, const double* __restrict__ r, 
 // The exponent is f ((C_ij + K v_j) - mu_i), f = -lam LOG2E, the parenthesis formed with the operations that gave
 // mu_i: it is exactly 0 at the minimum and not positive elsewhere, so that a row's sum lies in [1, m] for every lam.
 // Where the parts are small enough it is (2 s lam LOG2E P_ij + b_j) + (f s |x~_i|^2 - f mu_i) instead, with
-// b_j = f (s |y~_j|^2 + K v_j) per column from cert_soft_cols: 15 vector slots a pair at d = 3 instead of 20, 1.8
+// b_j = f (s |y~_j|^2 + K v_j) per column from cert_soft_cols: 15 vector slots a pair at d = 3 instead of 20, 1.9
 // instead of 2.4 ms at 65536 x 65536.  What f times the parts' rounding leaves over moves an exponent by
 // 2^-52 of their sum: with parts up to SOFT_PARTS by 2^-16, and a dual value, 1 / lam times that, by less than its own
 // rounding; 2^22 further on the sums would run out of the FP32 exponents.  (2 s lam LOG2E P_ij is no larger than the
